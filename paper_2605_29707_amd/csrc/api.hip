@@ -191,6 +191,10 @@ Plans make_plans_rows(const domino_model *m, int M, int Mlm, int Ma) {
   p.gateup = plan_proj(m, m->gateup[0], M, EPI_SWIGLU, 1);
   p.down = plan_proj(m, m->down[0], M, EPI_STORE, kMaxSplit);
   p.lm = plan_proj(m, m->lm, Mlm, EPI_STORE, 1);
+  if (p.lm.wide && Mlm <= kStreamMaxRows) {
+    const GemmPlan s = plan_gemm(m->lm.NT, m->lm.KS, Mlm, EPI_STORE, m->n_cu, 1);
+    if (s.pgrid > 0) p.lm = s;
+  }
   p.fc = GemmPlan();
   p.fc.ksplit = 0;
   return p;

@@ -46,9 +46,9 @@ struct GemmArgs {
 };
 
 struct GemmPlan {
-  int MT, WPT, groups, mgroups, ksplit;
+  int MT, WPT, groups, mgroups, ksplit;  // (wide: MT row blocks per wave, 64 MT rows per workgroup)
   int kcm;  // k-steps per staged chunk (16/MT, or 8/MT for finer K splits)
-  int nw;   // waves (= tiles) per workgroup: 8 or 6
+  int nw;   // weight tiles per workgroup (skinny: a wave each, 8 or 6)
   int pgrid;  // > 0: that many workgroups loop over the groups (one pipeline across groups)
   int wide = 0;  // 1: the wide-activation kernel (gemm_wide.hip) runs this plan
 };
@@ -57,17 +57,23 @@ struct GemmPlan {
 // may be split up to max_split ways into partial outputs.
 GemmPlan plan_gemm(int ntiles, int KS, int M, int epi, int n_cu, int max_split);
 void launch_gemm(bool bf16, int epi, const GemmArgs &a, const GemmPlan &p, hipStream_t st);
-// Wide activations (bf16 weights; more rows than the skinny kernel's 64 per
-// m-group): the activations are first split into hi/lo bf16 fragment planes
-// (in a.xf), then workgroup tiles of 256 columns x 256 rows multiply them with
-// the same packed weights; K-split partials as above.
+// Wide activations (bf16 weights; more than kSkinnyMaxRows rows): the activations are first split into hi/lo bf16 fragment planes
+// (in a.xf), then workgroup tiles of up to 208 columns x 256 rows multiply them
+// with the same packed weights; K-split partials as above.
 GemmPlan plan_gemm_wide(int ntiles, int KS, int M, int epi, int n_cu, int max_split);
 // false (nothing launched) when the arguments break the kernel's assumptions
 // (K not 32 KS, no rows, no fragment scratch)
 bool launch_gemm_wide(int epi, const GemmArgs &a, const GemmPlan &p, hipStream_t st);
 size_t gemm_wide_scratch_bytes(int M, int K);
-// above this many rows a bf16 GEMM whose K is a multiple of 32 runs the wide kernel
-constexpr int kSkinnyMaxRows = 64;
+// Above this many rows a bf16 GEMM whose K is a multiple of 32 runs the wide
+// kernel.  At 64 rows it takes 43 us against the skinny kernel's 64 on gate/up of
+// the 8B shape, 14 against 19 on QKV, 24 against 32 on down; at 32 rows 38 against
+// 43, but there the skinny kernel's projections also end with the residual update
+// and the next norm's statistics, which saves two launches a layer.
+constexpr int kSkinnyMaxRows = 32;
+// Up to this many rows the LM head stays on the skinny kernel where that runs as
+// one persistent launch (226 against 239 us at 64 rows, 196 against 227 at 32).
+constexpr int kStreamMaxRows = 64;
 void launch_pack(bool bf16, const void *W, int N, int K, int ldw, void *P, int NT, int KS,
                  int tile_mul, int tile_off, hipStream_t st);
 inline int kstep_of(bool bf16) { return bf16 ? 32 : 16; }
