@@ -229,7 +229,11 @@ bool layout(const domino_model *m, int bs, int max_ctx, int max_new, int beta, W
   w.X = take((size_t)M * D.d * 4);
   w.X2 = take((size_t)M * D.d * 4);
   const int Ma = M + bs * max_new;  // block rows, then the appended context rows
-  w.A = take((size_t)Ma * D.d * 4);
+  // a wide projection's input may be fragment planes (whole row blocks) in the place of fp32 rows
+  auto rows_bytes = [](int rows, int width) {
+    return std::max((size_t)rows * width * 4, gemm_wide_scratch_bytes(rows, width));
+  };
+  w.A = take(rows_bytes(Ma, D.d));
   w.FC = take((size_t)p.fc.ksplit * bs * max_new * D.d * 4);
   w.HP = take(head_part_floats(D) * 4);  // state GEMM partials (batches above kHeadFusedBatch)
   w.QKV = take((size_t)p.qkv.ksplit * Ma * qkvw * 4);
@@ -237,12 +241,12 @@ bool layout(const domino_model *m, int bs, int max_ctx, int max_new, int beta, W
   w.Kb = take((size_t)M * D.nkv * D.dh * 4);
   w.Vb = take((size_t)M * D.nkv * D.dh * 4);
   w.attn = take(attn_part_floats(D, max_ctx) * 4);
-  w.O = take((size_t)M * D.nq * D.dh * 4);
+  w.O = take(rows_bytes(M, D.nq * D.dh));
   w.WOp = take((size_t)p.wo.ksplit * M * D.d * 4);
-  w.F = take((size_t)M * D.ffn * 4);
+  w.F = take(rows_bytes(M, D.ffn));
   w.DNp = take((size_t)p.down.ksplit * M * D.d * 4);
   w.SSQ = take((size_t)kNormGroups * M * 4);
-  w.H = take((size_t)Mh * D.d * 4);
+  w.H = take(rows_bytes(Mh, D.d));
   w.ldl = m->lm.NT * 16;
   w.LP = take((size_t)Mh * w.ldl * 4);  // [L_base | pad | P] per draft row
   w.hbuf = take((size_t)2 * bs * D.ds * 4);
@@ -295,17 +299,20 @@ bool target_layout(const domino_model *m, int bs, int nn, int max_ctx, TargetLay
   const int qkvw = (D.nq + 2 * D.nkv) * D.dh;
   w.X = take((size_t)M * D.d * 4);
   w.X2 = take((size_t)M * D.d * 4);
-  w.A = take((size_t)M * D.d * 4);
+  auto rows_bytes = [](int rows, int width) {
+    return std::max((size_t)rows * width * 4, gemm_wide_scratch_bytes(rows, width));
+  };
+  w.A = take(rows_bytes(M, D.d));
   w.QKV = take((size_t)p.qkv.ksplit * M * qkvw * 4);
   w.Q = take((size_t)M * D.nq * D.dh * 4);
   w.Kb = take((size_t)M * D.nkv * D.dh * 4);
   w.Vb = take((size_t)M * D.nkv * D.dh * 4);
   w.attn = take(attn_part_floats(D, max_ctx) * 4);
-  w.O = take((size_t)M * D.nq * D.dh * 4);
+  w.O = take(rows_bytes(M, D.nq * D.dh));
   w.WOp = take((size_t)p.wo.ksplit * M * D.d * 4);
-  w.F = take((size_t)M * D.ffn * 4);
+  w.F = take(rows_bytes(M, D.ffn));
   w.DNp = take((size_t)p.down.ksplit * M * D.d * 4);
-  w.H = take((size_t)M * D.d * 4);
+  w.H = take(rows_bytes(M, D.d));
   w.ldl = m->lm.NT * 16;
   w.LP = take((size_t)M * w.ldl * 4);
   w.XF = take(wide_scratch(m, p, M, 0));
@@ -664,9 +671,15 @@ domino_status run_layers(domino_model_t m, const Dims &D, const Plans &p, const 
   }
 
   const size_t rstride = (size_t)M * D.d;  // partial-output stride of the residual projections
-  // every projection of the step: wide plans split their activations into the workspace's fragment planes
-  auto proj = [&](int epi, GemmArgs a, const GemmPlan &pl) {
-    a.xf = ws + w.XF;
+  // Every projection of the step.  A wide projection reads fragment planes: its
+  // producer writes them in the place of the fp32 rows (the GEMM then gets no X),
+  // except that QKV's input with appended context rows, which other launches
+  // write, stays fp32 and is split by the projection.
+  const bool fa = p.qkv.wide && n_new == 0, fo = p.wo.wide, fg = p.gateup.wide, ff = p.gateup.wide && p.down.wide,
+             fh = p.lm.wide;
+  auto proj = [&](int epi, GemmArgs a, const GemmPlan &pl, bool planes) {
+    a.xf = planes ? (void *)a.X : (void *)(ws + w.XF);
+    if (planes) a.X = nullptr;
     return launch_proj(m, epi, a, pl, st);
   };
   // the residual stream ping-pongs between two buffers: every RMSNorm launch
@@ -708,9 +721,10 @@ domino_status run_layers(domino_model_t m, const Dims &D, const Plans &p, const 
     if (l == 0 || !fuse) {
       prof_begin(m, DOMINO_KC_NORM, st);
       // (layer 0: the residual starts as the embedding of [anchor, MASK, ...])
-      launch_add_norm(D, xc, xn, D.d, F(w.DNp), l > 0 ? p.down.ksplit : 0, rstride, m->attn_norm[l], F(w.A), D.d,
+      launch_add_norm(D, xc, xn, D.d, F(w.DNp), l > 0 ? p.down.ksplit : 0, rstride, m->attn_norm[l],
+                      fa ? nullptr : F(w.A), D.d,
                       M, D.d, false, l == 0 ? m->embed : nullptr, anchor_ids, err, st, spec.tokens,
-                      l == 0 && clear_header ? (uint32_t *)ws : nullptr, (int)w.hdr_words);
+                      l == 0 && clear_header ? (uint32_t *)ws : nullptr, (int)w.hdr_words, fa ? F(w.A) : nullptr);
       std::swap(xc, xn);
       prof_end(m, DOMINO_KC_NORM, st);
     }
@@ -719,7 +733,7 @@ domino_status run_layers(domino_model_t m, const Dims &D, const Plans &p, const 
     GemmArgs a = gemm_args(base + m->qkv[l].off, m->qkv[l], 0, m->qkv[l].NT, qkvw, F(w.A), D.d, Ma, D.d, F(w.QKV),
                            qkvw, p.qkv);
     if (fuse && l > 0) deferred(a, p.down.groups);
-    if (!proj(EPI_STORE, a, p.qkv)) return fail(DOMINO_ERR_UNSUPPORTED, "qkv projection refused");
+    if (!proj(EPI_STORE, a, p.qkv, fa)) return fail(DOMINO_ERR_UNSUPPORTED, "qkv projection refused");
     prof_end(m, DOMINO_KC_QKV, st);
 
     prof_begin(m, DOMINO_KC_ROPE, st);
@@ -728,24 +742,25 @@ domino_status run_layers(domino_model_t m, const Dims &D, const Plans &p, const 
     prof_end(m, DOMINO_KC_ROPE, st);
 
     prof_begin(m, DOMINO_KC_ATTN, st);
-    launch_attention(D, F(w.Q), F(w.Kb), F(w.Vb), ck, cv, ctx_lens, max_ctx, F(w.attn), F(w.O), err, st, spec.amask);
+    launch_attention(D, F(w.Q), F(w.Kb), F(w.Vb), ck, cv, ctx_lens, max_ctx, F(w.attn), F(w.O), err, st, spec.amask,
+                     fo ? F(w.O) : nullptr);
     prof_end(m, DOMINO_KC_ATTN, st);
 
     prof_begin(m, DOMINO_KC_WO, st);
     a = gemm_args(base + m->wo[l].off, m->wo[l], 0, m->wo[l].NT, D.d, F(w.O), qd, M, qd, F(w.WOp), D.d, p.wo);
     if (fuse) {  // residual += attention output, and the FFN RMSNorm's statistics
       resid(a, m->ffn_norm[l], 2 * l);
-      if (!proj(EPI_RESID, a, p.wo)) return fail(DOMINO_ERR_UNSUPPORTED, "wo projection refused");
+      if (!proj(EPI_RESID, a, p.wo, fo)) return fail(DOMINO_ERR_UNSUPPORTED, "wo projection refused");
       std::swap(xc, xn);
-    } else if (!proj(EPI_STORE, a, p.wo)) {
+    } else if (!proj(EPI_STORE, a, p.wo, fo)) {
       return fail(DOMINO_ERR_UNSUPPORTED, "wo projection refused");
     }
     prof_end(m, DOMINO_KC_WO, st);
 
     if (!fuse) {  // residual += attention output, then the FFN RMSNorm
       prof_begin(m, DOMINO_KC_NORM, st);
-      launch_add_norm(D, xc, xn, D.d, F(w.WOp), p.wo.ksplit, rstride, m->ffn_norm[l], F(w.A), D.d, M, D.d, false,
-                      nullptr, nullptr, err, st);
+      launch_add_norm(D, xc, xn, D.d, F(w.WOp), p.wo.ksplit, rstride, m->ffn_norm[l], fg ? nullptr : F(w.A), D.d, M,
+                      D.d, false, nullptr, nullptr, err, st, nullptr, nullptr, 0, fg ? F(w.A) : nullptr);
       std::swap(xc, xn);
       prof_end(m, DOMINO_KC_NORM, st);
     }
@@ -754,7 +769,8 @@ domino_status run_layers(domino_model_t m, const Dims &D, const Plans &p, const 
     a = gemm_args(base + m->gateup[l].off, m->gateup[l], 0, m->gateup[l].NT, D.ffn, F(w.A), D.d, M, D.d, F(w.F),
                   D.ffn, p.gateup);
     if (fuse) deferred(a, p.wo.groups);
-    if (!proj(EPI_SWIGLU, a, p.gateup)) return fail(DOMINO_ERR_UNSUPPORTED, "gateup projection refused");
+    if (ff) a.yf = F(w.F);
+    if (!proj(EPI_SWIGLU, a, p.gateup, fg)) return fail(DOMINO_ERR_UNSUPPORTED, "gateup projection refused");
     prof_end(m, DOMINO_KC_GATEUP, st);
 
     prof_begin(m, DOMINO_KC_DOWN, st);
@@ -762,26 +778,27 @@ domino_status run_layers(domino_model_t m, const Dims &D, const Plans &p, const 
                   p.down);
     if (fuse && l + 1 < m->cfg.n_layers) {  // residual += FFN output, and the next attention RMSNorm's statistics
       resid(a, m->attn_norm[l + 1], 2 * l + 1);
-      if (!proj(EPI_RESID, a, p.down)) return fail(DOMINO_ERR_UNSUPPORTED, "down projection refused");
+      if (!proj(EPI_RESID, a, p.down, ff)) return fail(DOMINO_ERR_UNSUPPORTED, "down projection refused");
       std::swap(xc, xn);
-    } else if (!proj(EPI_STORE, a, p.down)) {
+    } else if (!proj(EPI_STORE, a, p.down, ff)) {
       return fail(DOMINO_ERR_UNSUPPORTED, "down projection refused");
     }
     prof_end(m, DOMINO_KC_DOWN, st);
   }
 
   // residual += last down projection; final RMSNorm of the draft rows -> H
-  float *H = (debug && debug->hidden) ? debug->hidden : F(w.H);
+  float *Hd = debug ? debug->hidden : nullptr;
+  float *H = fh ? F(w.H) : Hd ? Hd : F(w.H);  // the LM head's input: fp32 rows or planes
   prof_begin(m, DOMINO_KC_NORM, st);
-  launch_add_norm(D, xc, nullptr, D.d, F(w.DNp), p.down.ksplit, rstride, m->final_norm, H, D.d, Mh, D.d, !spec.all_rows,
-                  nullptr, nullptr, err, st);
+  launch_add_norm(D, xc, nullptr, D.d, F(w.DNp), p.down.ksplit, rstride, m->final_norm, fh ? Hd : H, D.d, Mh, D.d,
+                  !spec.all_rows, nullptr, nullptr, err, st, nullptr, nullptr, 0, fh ? H : nullptr);
   prof_end(m, DOMINO_KC_NORM, st);
 
   // LM head and W1's H half in one pass over H: columns [0, V) are L_base, [ldl - r, ldl) are P
   float *LP = F(w.LP);
   prof_begin(m, DOMINO_KC_LMHEAD, st);
   GemmArgs a = gemm_args(base + m->lm.off, m->lm, 0, m->lm.NT, w.ldl, H, D.d, Mh, D.d, LP, w.ldl, p.lm);
-  if (!proj(EPI_STORE, a, p.lm)) return fail(DOMINO_ERR_UNSUPPORTED, "lm projection refused");
+  if (!proj(EPI_STORE, a, p.lm, fh)) return fail(DOMINO_ERR_UNSUPPORTED, "lm projection refused");
   prof_end(m, DOMINO_KC_LMHEAD, st);
   if (!spec.all_rows && debug && debug->base_logits) {
     hipError_t ce = hipMemcpy2DAsync(debug->base_logits, (size_t)D.V * 4, LP, (size_t)w.ldl * 4, (size_t)D.V * 4, Mh,

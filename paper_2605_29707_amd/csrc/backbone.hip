@@ -4,6 +4,7 @@
 // All arithmetic is fp32; RoPE angles are formed and range-reduced in fp64 so
 // that positions in the thousands keep full fp32 accuracy in the rotated values.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 #include "kernels.h"
@@ -37,8 +38,16 @@ __global__ __launch_bounds__(256) void embed_block_kernel(const WT *__restrict__
 // workgroups of one row each write a slice while the others still read x.  With `embed` given, the row is first replaced by the embedding
 // row of its token: tokens[row] when `tokens` is given, else the anchor for
 // block position 0 and MASK otherwise.  One
-// workgroup per output row; a thread keeps its 16 columns in registers and
-// issues all of its loads together.
+// workgroup per output row (or slice of one); a thread keeps its 16 columns in
+// registers and issues all of its loads together.
+//
+// `planes` (optional, beside or instead of y): the hi/lo bf16 fragment planes
+// that the wide GEMM reads (nrb row blocks, width / 32 k-steps).  A thread's 8
+// columns are exactly one lane's 16 bytes of a fragment, so writing them here
+// saves the launch that split y again (5 us, 9 for the widest) and y's round
+// trip.  The 16 bytes of different rows make up one line, so with planes a row
+// block's 16 rows are all written by workgroups of one XCD (workgroup L on XCD
+// L % 8): the line is assembled in one L2.
 template <typename WT, int MAXP>
 __global__ __launch_bounds__(512) void add_norm_kernel(const float *__restrict__ x, float *__restrict__ x_out,
                                                        int ldx,
@@ -48,25 +57,35 @@ __global__ __launch_bounds__(512) void add_norm_kernel(const float *__restrict__
                                                        int skip_anchor, int depth, const WT *__restrict__ embed,
                                                        const int32_t *__restrict__ anchor, int mask_id, int V,
                                                        int32_t *err, const int32_t *__restrict__ tokens,
-                                                       int nsplit, uint32_t *hdr, int hdr_words) {
+                                                       int nsplit, uint32_t *hdr, int hdr_words, int rows,
+                                                       u32x4 *__restrict__ planes) {
   // nsplit workgroups per row: each forms the whole row's sum of squares but
   // writes only its slice of the columns
-  const int i = blockIdx.x / nsplit, part = blockIdx.x % nsplit;
+  int i = blockIdx.x / nsplit;
+  const int part = blockIdx.x % nsplit;
+  if (planes) {  // row blocks over the XCDs (nsplit is 1, 2 or 4: L % 8 covers 8 / nsplit row blocks)
+    const int per = 8 / nsplit, x = (blockIdx.x & 7) / nsplit, r = blockIdx.x >> 3;
+    i = 16 * (x + per * (r >> 4)) + (r & 15);
+  }
   // hdr: the step's workspace header (word 0 the error word) is cleared here
-  // instead of by a launch of its own; then only thread 0 of workgroup 0 checks
-  // the tokens, after clearing the error word, so no error raised in this launch
-  // is lost to the clear
+  // instead of by a launch of its own; then only workgroup 0 checks the tokens,
+  // after its clear of the error word is complete, so no error raised in this
+  // launch is lost to the clear.  A thread per row: one thread walking the rows
+  // took 25 of this launch's 31 us at 256 rows.
   if (hdr) {
     for (int e = blockIdx.x * blockDim.x + threadIdx.x + 1; e < hdr_words; e += gridDim.x * blockDim.x) hdr[e] = 0u;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-      hdr[0] = 0u;
+    if (blockIdx.x == 0) {
+      if (threadIdx.x == 0) atomicExch(hdr, 0u);
+      __builtin_amdgcn_s_waitcnt(0);
+      __syncthreads();
       const int B = depth + 1;
-      for (int row = 0; row < (int)gridDim.x / nsplit; ++row) {
+      for (int row = threadIdx.x; row < rows; row += blockDim.x) {
         const int tk = tokens ? tokens[row] : (row % B == 0 ? anchor[row / B] : 0);
         if (tk < 0 || tk >= V) raise_error(err, DEV_BAD_TOKEN);
       }
     }
   }
+  if (i >= rows) return;  // workgroup-uniform
   const bool raise = hdr == nullptr;
   const int cs = width / nsplit;  // columns per slice (a multiple of 8)
   const int in_row = skip_anchor ? i + i / depth + 1 : i;
@@ -152,9 +171,19 @@ __global__ __launch_bounds__(512) void add_norm_kernel(const float *__restrict__
     float o[PER];
 #pragma unroll
     for (int e = 0; e < PER; ++e) o[e] = v[it][e] * inv * gv[it][e];
-    float *yr = y + (size_t)i * ldy + c0;
-    *(float4 *)(yr) = make_float4(o[0], o[1], o[2], o[3]);
-    *(float4 *)(yr + 4) = make_float4(o[4], o[5], o[6], o[7]);
+    if (y) {
+      float *yr = y + (size_t)i * ldy + c0;
+      *(float4 *)(yr) = make_float4(o[0], o[1], o[2], o[3]);
+      *(float4 *)(yr + 4) = make_float4(o[4], o[5], o[6], o[7]);
+    }
+    if (planes) {
+      bf16x8 hi, lo;
+      split8(o, hi, lo);
+      const int KS = width / 32, nrb = (rows + 15) / 16;
+      const size_t at = ((size_t)(i >> 4) * KS + (c0 >> 5)) * 64 + 16 * ((c0 >> 3) & 3) + (i & 15);
+      planes[at] = __builtin_bit_cast(u32x4, hi);
+      planes[(size_t)nrb * KS * 64 + at] = __builtin_bit_cast(u32x4, lo);
+    }
   }
 }
 
@@ -667,8 +696,11 @@ __global__ __launch_bounds__(kAttnThreads) void attn_partial_kernel(
 
 // ---------------------------------------------------------------------------
 // Context attention over a bf16 cache, one online-softmax pass per workgroup
-// (batched steps): workgroup (c, kv head, batch row) takes keys
-// [c * kpw, (c + 1) * kpw) of the sequence context[0, n) + block[0, B) and
+// (every step over one): workgroup (c, kv head, batch row) takes keys
+// [c * kpw, (c + 1) * kpw) of the sequence context[0, n) + block[0, B), kpw =
+// flash_run(n + B, runs): the row's own keys in equal runs, whatever the cache's
+// capacity (sized by max_ctx, a cache of 3072 positions holding 2048 gave 1600 keys
+// to one workgroup and 464 to the other: 114 us a layer at bs 32), and
 // writes the same partial (unnormalised output, row max, row sum) as
 // attn_partial_kernel, for the same merge.
 //
@@ -683,6 +715,8 @@ __global__ __launch_bounds__(kAttnThreads) void attn_partial_kernel(
 // 16 + 4 g .. 16 + 4 g + 3); V's B fragment is read in that order from the
 // transposed copy.  The block's own keys (fp32) come last, in one more block
 // with hi and lo parts in the two buffers and three products per tile.
+// MASKED (a verify forward's tree mask, as in attn_partial_kernel): a lane's 16
+// mask bytes of its row and the block keys it scores are loaded with those keys.
 // ---------------------------------------------------------------------------
 constexpr int kFlashKB = 64;                 // keys per block
 constexpr int kFlashKP = 128 + 8;            // K row stride (bf16): conflict-free 16-byte fragment reads
@@ -690,16 +724,23 @@ constexpr int kFlashVP = kFlashKB + 4;       // transposed V row stride (bf16): 
 constexpr size_t kFlashK = (size_t)kFlashKB * kFlashKP, kFlashV = (size_t)128 * kFlashVP;  // bf16 per buffer part
 constexpr size_t kFlashLds = 2 * (kFlashK + kFlashV) * sizeof(uint16_t);
 
+// keys per run when `total` keys are cut into at most `runs` runs of whole blocks
+DEVI int flash_run(int total, int runs) {
+  const int blocks = (total + kFlashKB - 1) / kFlashKB;
+  return (blocks + runs - 1) / runs * kFlashKB;
+}
+
 DEVI uint32_t pack_lo16(uint32_t a, uint32_t b) { return (a & 0xffffu) | (b << 16); }
 DEVI uint32_t pack_hi16(uint32_t a, uint32_t b) { return (a >> 16) | (b & 0xffff0000u); }
 
-template <int NW, int PD>
+template <int NW, int PD, bool MASKED>
 __global__ __launch_bounds__(NW * 64) void attn_flash_kernel(const float *__restrict__ Q, const float *__restrict__ Kb,
                                                              const float *__restrict__ Vb, const bf16_t *__restrict__ ck,
                                                              const bf16_t *__restrict__ cv,
                                                              const int32_t *__restrict__ ctx_lens, int max_ctx,
                                                              float *__restrict__ part, int B, int nq, int nkv, int nch,
-                                                             float scale, int kpw) {
+                                                             float scale, int runs,
+                                                             const uint8_t *__restrict__ amask) {
   constexpr int DH = 128, T = NW * 64, KCH = kFlashKB * DH / 8 / T;  // 16-byte K chunks per thread per block
   extern __shared__ __align__(16) uint16_t fsm[];
   auto Kbuf = [&](int bb) { return fsm + bb * (kFlashK + kFlashV); };  // buffer bb: K, then transposed V
@@ -709,7 +750,7 @@ __global__ __launch_bounds__(NW * 64) void attn_flash_kernel(const float *__rest
   const int G = nq / nkv;
   int n = ctx_lens[b];
   n = n < 0 ? 0 : (n > max_ctx ? max_ctx : n);
-  const int total = n + B;
+  const int total = n + B, kpw = flash_run(total, runs);
   const int k0 = c * kpw, k1 = min(total, k0 + kpw);
   if (k0 >= total) return;  // workgroup-uniform
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, cc = lane & 15;
@@ -719,6 +760,7 @@ __global__ __launch_bounds__(NW * 64) void attn_flash_kernel(const float *__rest
 #pragma unroll
   for (int x = 0; x < DH / 16; ++x) oacc[x] = floatx4{0.f, 0.f, 0.f, 0.f};
   float m_run = -INFINITY, l_run = 0.f;  // of query row cc (the same in every g)
+  uint32_t mbits = 0;  // MASKED: bit 4 t + e: block key b0 + 16 t + 4 g + e is visible to query row cc
 
   // scores of one block against this wave's rows -> online softmax -> P V.
   // HILO: the block's keys are fp32 (hi parts in buffer 0, lo parts in buffer 1).
@@ -749,13 +791,15 @@ __global__ __launch_bounds__(NW * 64) void attn_flash_kernel(const float *__rest
     for (int t = 0; t < kFlashKB / 16; ++t)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const float v = 16 * t + 4 * g + e < nvalid ? sacc[t][e] * scale : -INFINITY;
+        const bool vis = !MASKED || !hilo || ((mbits >> (4 * t + e)) & 1);
+        const float v = 16 * t + 4 * g + e < nvalid && vis ? sacc[t][e] * scale : -INFINITY;
         sacc[t][e] = v;
         mb = fmaxf(mb, v);
       }
     mb = fmaxf(mb, __shfl_xor(mb, 16, 64));
     mb = fmaxf(mb, __shfl_xor(mb, 32, 64));
-    const float mn = fmaxf(m_run, mb);  // finite: every block has a valid key
+    // finite unless MASKED hides every key so far from the row: its p and sums then stay 0
+    const float mn = fmaxf(m_run, mb);
     const float alpha = m_run == -INFINITY ? 0.f : expf(m_run - mn);
     m_run = mn;
     float p[kFlashKB / 16][4], lb = 0.f;
@@ -860,6 +904,14 @@ __global__ __launch_bounds__(NW * 64) void attn_flash_kernel(const float *__rest
       pk[q] = *(const float4 *)(Kb + row + 4 * d4);
       pv[q] = *(const float4 *)(Vb + row + 4 * d4);
     }
+    if constexpr (MASKED) {
+      const uint8_t *mr = amask + ((size_t)b * B + (16 * wave + cc) % B) * B + b0;
+      uint8_t mv[kFlashKB / 4];
+#pragma unroll
+      for (int q = 0; q < kFlashKB / 4; ++q) mv[q] = mr[min(16 * (q / 4) + 4 * g + q % 4, nb - 1)];
+#pragma unroll
+      for (int q = 0; q < kFlashKB / 4; ++q) mbits |= (mv[q] != 0 ? 1u : 0u) << q;
+    }
   }
   // this wave's query rows: Q^T fragments (dims 32 s + 8 g .. of row 16 wave + cc),
   // loaded after the first block's keys so the two memory round trips overlap
@@ -953,29 +1005,37 @@ __global__ __launch_bounds__(NW * 64) void attn_flash_kernel(const float *__rest
 // row, 8 or 24 after the one-pass kernel), so a context of up to CB chunks costs
 // one memory round trip: lane c folds chunks c, c + 64, ... into a
 // running (max, sum) pair, the wave combines the pairs, then the rows are
-// weighted and summed in chunk order.
+// weighted and summed in chunk order.  `planes` (instead of O): the hi/lo bf16
+// fragment planes the wide GEMM reads; a lane's columns are neighbours, so four
+// rows of a workgroup fill 64 bytes of each line.
 template <int DH, int CB = 40>
 __global__ __launch_bounds__(256) void attn_combine_kernel(const float *__restrict__ part,
                                                            const int32_t *__restrict__ ctx_lens,
                                                            int max_ctx, float *__restrict__ O, int bs,
-                                                           int B, int nq, int nch, int CH) {
+                                                           int B, int nq, int nch, int CH, int runs,
+                                                           uint16_t *__restrict__ planes) {
   const int lane = threadIdx.x & 63;
   const int item = blockIdx.x * 4 + (threadIdx.x >> 6);  // (b, qh, j)
   if (item >= bs * nq * B) return;
   const int j = item % B, qh = (item / B) % nq, b = item / (B * nq);
   int n = ctx_lens[b];
   n = n < 0 ? 0 : (n > max_ctx ? max_ctx : n);
+  if (runs > 0) CH = flash_run(n + B, runs);  // the one-pass kernel's runs
   const int nc = (n + B + CH - 1) / CH;
   const float *base = part + (((size_t)b * nq + qh) * B + j) * nch * (DH + 2);
-  constexpr int PER = DH / 64;
+  constexpr int PER = DH / 64;  // this lane's columns: PER lane .. PER lane + PER - 1
+  struct alignas(4 * PER) Cols {
+    float v[PER];
+  };
   float w[CB], v[CB][PER];
-#pragma unroll
-  for (int u = 0; u < CB; ++u) {  // chunk u's max and this lane's output values (clamped, in flight together)
-    const int cu = min(u, nc - 1);
+  auto load = [&](int u, int cu) {  // chunk cu's max and this lane's output values
     w[u] = base[cu * (DH + 2) + DH];
+    const Cols x = *(const Cols *)(base + cu * (DH + 2) + PER * lane);
 #pragma unroll
-    for (int q = 0; q < PER; ++q) v[u][q] = base[cu * (DH + 2) + lane + 64 * q];
-  }
+    for (int q = 0; q < PER; ++q) v[u][q] = x.v[q];
+  };
+#pragma unroll
+  for (int u = 0; u < CB; ++u) load(u, min(u, nc - 1));  // (clamped, in flight together)
   float M = -INFINITY, den = 0.f;
   for (int c = lane; c < nc; c += 64) {
     const float m = base[c * (DH + 2) + DH], l = base[c * (DH + 2) + DH + 1];
@@ -997,12 +1057,7 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float *__restri
   }
   for (int c0 = CB; c0 < nc; c0 += CB) {  // longer contexts: further batches
 #pragma unroll
-    for (int u = 0; u < CB; ++u) {
-      const int cu = min(c0 + u, nc - 1);
-      w[u] = base[cu * (DH + 2) + DH];
-#pragma unroll
-      for (int q = 0; q < PER; ++q) v[u][q] = base[cu * (DH + 2) + lane + 64 * q];
-    }
+    for (int u = 0; u < CB; ++u) load(u, min(c0 + u, nc - 1));
 #pragma unroll
     for (int u = 0; u < CB; ++u) {
       const float wu = c0 + u < nc ? expf(w[u] - M) : 0.f;
@@ -1011,9 +1066,32 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float *__restri
     }
   }
   const float inv = 1.0f / den;
-  float *dst = O + ((size_t)(b * B + j) * nq + qh) * DH;
+  const int row = b * B + j;
+  if (planes) {
+    const int KS = nq * DH / 32, nrb = (bs * B + 15) / 16;
+    const int k = qh * DH + PER * lane;
+    const size_t at = (((size_t)(row >> 4) * KS + (k >> 5)) * 64 + 16 * ((k >> 3) & 3) + (row & 15)) * 8 + (k & 7);
+    uint16_t *ph = planes + at, *pl = ph + (size_t)nrb * KS * 512;
+    uint32_t hw = 0, lw = 0;
 #pragma unroll
-  for (int q = 0; q < PER; ++q) dst[lane + 64 * q] = acc[q] * inv;
+    for (int q = 0; q < PER; ++q) {
+      const float x = acc[q] * inv;
+      const __bf16 h = (__bf16)x, l = (__bf16)(x - (float)h);
+      hw |= (uint32_t)__builtin_bit_cast(uint16_t, h) << (16 * q);
+      lw |= (uint32_t)__builtin_bit_cast(uint16_t, l) << (16 * q);
+    }
+    if constexpr (PER == 2) {
+      *(uint32_t *)ph = hw;
+      *(uint32_t *)pl = lw;
+    } else {
+      *ph = (uint16_t)hw;
+      *pl = (uint16_t)lw;
+    }
+    return;
+  }
+  float *dst = O + ((size_t)row * nq + qh) * DH + PER * lane;
+#pragma unroll
+  for (int q = 0; q < PER; ++q) dst[q] = acc[q] * inv;
 }
 
 // ---------------------------------------------------------------------------
@@ -1034,30 +1112,40 @@ template <typename WT, int MAXP>
 static void add_norm_t(const Dims &D, const float *x, float *x_out, int ldx, const float *parts, int np, size_t pstride,
                        const void *gain, float *y, int ldy, int rows, int width, bool skip_anchor,
                        const void *embed, const int32_t *anchor, int32_t *err, hipStream_t st,
-                       const int32_t *tokens, uint32_t *hdr, int hdr_words) {
+                       const int32_t *tokens, uint32_t *hdr, int hdr_words, void *planes) {
   // a few workgroups per row when there are few rows: a GEMM that reads rows
   // written by one workgroup each was measured ~5 us slower (QKV after the
   // attention RMSNorm at 16 rows), with two or more per row it is not
   int split = 1;
   while (split < 4 && rows * split < 64 && width % (2 * split * 8) == 0) split *= 2;
-  hipLaunchKernelGGL((add_norm_kernel<WT, MAXP>), dim3(rows * split), dim3(512), 0, st, x, x_out, ldx, parts, np, pstride,
+  const int per = 8 / split, nrb = (rows + 15) / 16;  // with planes: groups of 8 / split row blocks
+  const int grid = planes ? (nrb + per - 1) / per * per * 16 * split : rows * split;
+  hipLaunchKernelGGL((add_norm_kernel<WT, MAXP>), dim3(grid), dim3(512), 0, st, x, x_out, ldx, parts, np, pstride,
                      (const WT *)gain, y, ldy, width, D.eps, (int)skip_anchor, D.B - 1, (const WT *)embed, anchor,
-                     D.mask_id, D.V, err, tokens, split, hdr, hdr_words);
+                     D.mask_id, D.V, err, tokens, split, hdr, hdr_words, rows, (u32x4 *)planes);
 }
 
 void launch_add_norm(const Dims &D, const float *x, float *x_out, int ldx, const float *parts, int np, size_t pstride,
                      const void *gain, float *y, int ldy, int rows, int width, bool skip_anchor,
                      const void *embed, const int32_t *anchor, int32_t *err, hipStream_t st,
-                     const int32_t *tokens, uint32_t *hdr, int hdr_words) {
+                     const int32_t *tokens, uint32_t *hdr, int hdr_words, void *planes) {
   if (rows <= 0) return;
   if (np < 0 || np > 16) return;  // partial counts come from the GEMM planner (<= 16)
-  if (D.bf16) {
-    if (np <= 8) add_norm_t<bf16_t, 8>(D, x, x_out, ldx, parts, np, pstride, gain, y, ldy, rows, width, skip_anchor, embed, anchor, err, st, tokens, hdr, hdr_words);
-    else add_norm_t<bf16_t, 16>(D, x, x_out, ldx, parts, np, pstride, gain, y, ldy, rows, width, skip_anchor, embed, anchor, err, st, tokens, hdr, hdr_words);
-  } else {
-    if (np <= 8) add_norm_t<float, 8>(D, x, x_out, ldx, parts, np, pstride, gain, y, ldy, rows, width, skip_anchor, embed, anchor, err, st, tokens, hdr, hdr_words);
-    else add_norm_t<float, 16>(D, x, x_out, ldx, parts, np, pstride, gain, y, ldy, rows, width, skip_anchor, embed, anchor, err, st, tokens, hdr, hdr_words);
-  }
+  // the least instance that holds every partial: slots past np are loaded all the same
+  auto go = [&](auto slots) {
+    constexpr int P = decltype(slots)::value;
+    if (D.bf16)
+      add_norm_t<bf16_t, P>(D, x, x_out, ldx, parts, np, pstride, gain, y, ldy, rows, width, skip_anchor, embed,
+                            anchor, err, st, tokens, hdr, hdr_words, planes);
+    else
+      add_norm_t<float, P>(D, x, x_out, ldx, parts, np, pstride, gain, y, ldy, rows, width, skip_anchor, embed,
+                           anchor, err, st, tokens, hdr, hdr_words, planes);
+  };
+  if (np <= 2) go(std::integral_constant<int, 2>{});
+  else if (np <= 4) go(std::integral_constant<int, 4>{});
+  else if (np <= 6) go(std::integral_constant<int, 6>{});
+  else if (np <= 8) go(std::integral_constant<int, 8>{});
+  else go(std::integral_constant<int, 16>{});
 }
 
 template <typename WT, int MAXP>
@@ -1077,13 +1165,19 @@ void launch_qk_norm_rope(const Dims &D, const float *qkv, int np, size_t pstride
                          float *Vb, int n_new, void *ck, void *cv, int32_t *err, hipStream_t st,
                          const int32_t *pos_rows, int n_store) {
   if (np < 1 || np > 16) return;  // partial counts come from the GEMM planner (1..16)
-  if (D.bf16) {
-    if (np <= 8) qk_norm_rope_t<bf16_t, 8>(D, qkv, np, pstride, q_norm, k_norm, ctx_lens, max_ctx, Q, Kb, Vb, n_new, ck, cv, err, st, pos_rows, n_store);
-    else qk_norm_rope_t<bf16_t, 16>(D, qkv, np, pstride, q_norm, k_norm, ctx_lens, max_ctx, Q, Kb, Vb, n_new, ck, cv, err, st, pos_rows, n_store);
-  } else {
-    if (np <= 8) qk_norm_rope_t<float, 8>(D, qkv, np, pstride, q_norm, k_norm, ctx_lens, max_ctx, Q, Kb, Vb, n_new, ck, cv, err, st, pos_rows, n_store);
-    else qk_norm_rope_t<float, 16>(D, qkv, np, pstride, q_norm, k_norm, ctx_lens, max_ctx, Q, Kb, Vb, n_new, ck, cv, err, st, pos_rows, n_store);
-  }
+  auto go = [&](auto slots) {  // as for add_norm
+    constexpr int P = decltype(slots)::value;
+    if (D.bf16)
+      qk_norm_rope_t<bf16_t, P>(D, qkv, np, pstride, q_norm, k_norm, ctx_lens, max_ctx, Q, Kb, Vb, n_new, ck, cv, err,
+                                st, pos_rows, n_store);
+    else
+      qk_norm_rope_t<float, P>(D, qkv, np, pstride, q_norm, k_norm, ctx_lens, max_ctx, Q, Kb, Vb, n_new, ck, cv, err,
+                               st, pos_rows, n_store);
+  };
+  if (np <= 2) go(std::integral_constant<int, 2>{});
+  else if (np <= 4) go(std::integral_constant<int, 4>{});
+  else if (np <= 8) go(std::integral_constant<int, 8>{});
+  else go(std::integral_constant<int, 16>{});
 }
 
 template <typename WT, int RPT, int CH, int DH, bool MASKED, bool MULTI>
@@ -1166,44 +1260,42 @@ bool attn_supported(int nq, int nkv, int B) {
 
 void launch_attention(const Dims &D, const float *Q, const float *Kb, const float *Vb,
                       const void *ck, const void *cv, const int32_t *ctx_lens, int max_ctx,
-                      float *part, float *O, int32_t *err, hipStream_t st, const uint8_t *amask) {
+                      float *part, float *O, int32_t *err, hipStream_t st, const uint8_t *amask, void *planes) {
   (void)err;
-  // batched steps over a bf16 cache: the one-pass kernel, about two
-  // workgroups per CU, each over a contiguous run of keys
+  // over a bf16 cache: the one-pass kernel, about two workgroups per CU, each
+  // over a contiguous run of keys; with a tree mask too (the 8B target's layer,
+  // with the merge: 31 nodes x 4 rows, contexts to 1500, 97 us with the chunked
+  // kernel, 32 with this one; 16 nodes x 1 row, context 1024, 17.3 and 14.9)
   {
     const int G = D.nq / D.nkv, R = G * D.B;
     const long pairs = (long)D.bs * D.nkv;
-    if (D.bf16 && D.dh == 128 && !amask && (R == 64 || R == 128) && pairs >= 8) {
+    if (D.bf16 && D.dh == 128 && (R == 64 || R == 128) && pairs >= 8) {
       const int n_cu = attn_cu_count();
       const int nkeys = max_ctx + D.B;
       // workgroups resident per CU: two of 4 waves (LDS), one of 8 (registers)
       const long target = std::max(1L, (R == 64 ? 2L : 1L) * n_cu / pairs);
-      const int kpw = (int)(((nkeys + target - 1) / target + kFlashKB - 1) / kFlashKB * kFlashKB);
-      const int ngrp = (nkeys + kpw - 1) / kpw;
+      const int ngrp = (int)std::min(target, (long)(nkeys + kFlashKB - 1) / kFlashKB);
       const int nch = attn_nchunks(max_ctx, D.B);
       const float scale = 1.0f / sqrtf(128.f);
       const dim3 grid(ngrp, D.nkv, D.bs);
-      if (R == 64) {
-        (void)hipFuncSetAttribute((const void *)attn_flash_kernel<4, 1>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  (int)kFlashLds);
-        hipLaunchKernelGGL((attn_flash_kernel<4, 1>), grid, dim3(256), kFlashLds, st, Q, Kb, Vb, (const bf16_t *)ck,
-                           (const bf16_t *)cv, ctx_lens, max_ctx, part, D.B, D.nq, D.nkv, nch, scale, kpw);
-      } else {
-        (void)hipFuncSetAttribute((const void *)attn_flash_kernel<8, 2>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  (int)kFlashLds);
-        hipLaunchKernelGGL((attn_flash_kernel<8, 2>), grid, dim3(512), kFlashLds, st, Q, Kb, Vb, (const bf16_t *)ck,
-                           (const bf16_t *)cv, ctx_lens, max_ctx, part, D.B, D.nq, D.nkv, nch, scale, kpw);
-      }
+      auto go = [&](auto kernel, int threads) {
+        (void)hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kFlashLds);
+        hipLaunchKernelGGL(kernel, grid, dim3(threads), kFlashLds, st, Q, Kb, Vb, (const bf16_t *)ck,
+                           (const bf16_t *)cv, ctx_lens, max_ctx, part, D.B, D.nq, D.nkv, nch, scale, ngrp, amask);
+      };
+      if (R == 64 && amask) go(attn_flash_kernel<4, 1, true>, 256);
+      else if (R == 64) go(attn_flash_kernel<4, 1, false>, 256);
+      else if (amask) go(attn_flash_kernel<8, 2, true>, 512);
+      else go(attn_flash_kernel<8, 2, false>, 512);
       const int items = D.bs * D.nq * D.B;
-      if (ngrp <= 8)
-        hipLaunchKernelGGL((attn_combine_kernel<128, 8>), dim3((items + 3) / 4), dim3(256), 0, st, part, ctx_lens,
-                           max_ctx, O, D.bs, D.B, D.nq, nch, kpw);
-      else if (ngrp <= 24)  // one batch row at a 1024-key context: 17 runs
-        hipLaunchKernelGGL((attn_combine_kernel<128, 24>), dim3((items + 3) / 4), dim3(256), 0, st, part, ctx_lens,
-                           max_ctx, O, D.bs, D.B, D.nq, nch, kpw);
-      else
-        hipLaunchKernelGGL((attn_combine_kernel<128, 40>), dim3((items + 3) / 4), dim3(256), 0, st, part, ctx_lens,
-                           max_ctx, O, D.bs, D.B, D.nq, nch, kpw);
+      auto merge = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((items + 3) / 4), dim3(256), 0, st, part, ctx_lens, max_ctx, O, D.bs, D.B,
+                           D.nq, nch, 0, ngrp, (uint16_t *)planes);
+      };
+      if (ngrp <= 2) merge(attn_combine_kernel<128, 2>);
+      else if (ngrp <= 8) merge(attn_combine_kernel<128, 8>);
+      else if (ngrp <= 24) merge(attn_combine_kernel<128, 24>);  // one batch row at a 1024-key context: 17 runs
+      else merge(attn_combine_kernel<128, 40>);
       return;
     }
   }
@@ -1221,10 +1313,10 @@ void launch_attention(const Dims &D, const float *Q, const float *Kb, const floa
   const int items = D.bs * D.nq * D.B;
   if (D.dh == 128)
     hipLaunchKernelGGL(attn_combine_kernel<128>, dim3((items + 3) / 4), dim3(256), 0, st, part, ctx_lens, max_ctx,
-                       O, D.bs, D.B, D.nq, nch, CH);
+                       O, D.bs, D.B, D.nq, nch, CH, 0, (uint16_t *)planes);
   else
     hipLaunchKernelGGL(attn_combine_kernel<64>, dim3((items + 3) / 4), dim3(256), 0, st, part, ctx_lens, max_ctx,
-                       O, D.bs, D.B, D.nq, nch, CH);
+                       O, D.bs, D.B, D.nq, nch, CH, 0, (uint16_t *)planes);
 }
 
 template <typename WT>

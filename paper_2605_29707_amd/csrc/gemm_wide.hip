@@ -4,8 +4,9 @@
 // with the packed weight tiles of the skinny kernel and the same hi + lo bf16
 // split of the activations, so both kernels compute to the same precision.
 //
-// The activations are split once per projection (split_frag_kernel) into two
-// bf16 planes, hi and lo, stored in MFMA fragment order: fragment (row block
+// The activations are split once per projection, by the kernel that produces
+// them (the RMSNorms, the attention merge, gate/up's own epilogue) or, where
+// that leaves fp32 rows, by split_frag_kernel, into two bf16 planes, hi and lo, stored in MFMA fragment order: fragment (row block
 // rb, k-step s) is 1 KB, lane l = 16 g + r holding the 8 k values
 // 32 s + 8 g .. + 7 of row 16 rb + r.  A fragment is then one coalesced 1 KB
 // wave load, exactly like a packed weight fragment, and no arithmetic is left
@@ -257,10 +258,26 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(1,
       for (int j = 0; j < TM; ++j) {
         const int m = ((mz * 4 + wave) * TM + j) * 16 + (lane & 15);
         if (m >= a.M) continue;
+        float o[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = silu_w(acc[c][j][e]) * acc[c + (c + 1 < CT ? 1 : 0)][j][e];
+        if (a.yf) {  // the next projection's fragment planes: 8 bytes of the lane's 16 (N is a multiple of 32)
+          const int KSo = a.N / 32;
+          const size_t at =
+              (((size_t)(m >> 4) * KSo + (col >> 5)) * 64 + 16 * ((col >> 3) & 3) + (m & 15)) * 2 + ((col >> 2) & 1);
+          const float o8[8] = {o[0], o[1], o[2], o[3], 0.f, 0.f, 0.f, 0.f};
+          bf16x8 hi, lo;
+          split8(o8, hi, lo);
+          const u32x4 hu = __builtin_bit_cast(u32x4, hi), lu = __builtin_bit_cast(u32x4, lo);
+          uint2 *pf = (uint2 *)a.yf;
+          pf[at] = make_uint2(hu[0], hu[1]);
+          pf[(size_t)nrb * KSo * 128 + at] = make_uint2(lu[0], lu[1]);
+          continue;
+        }
         float *y = Y + (size_t)m * a.ldy + col;
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          if (col + e < a.N) y[e] = silu_w(acc[c][j][e]) * acc[c + (c + 1 < CT ? 1 : 0)][j][e];
+          if (col + e < a.N) y[e] = o[e];
       }
     } else {
       if (tile >= a.ntiles) continue;
@@ -361,11 +378,13 @@ size_t gemm_wide_scratch_bytes(int M, int K) {
 bool launch_gemm_wide(int epi, const GemmArgs &a, const GemmPlan &p, hipStream_t st) {
   // the activation loads assume whole k-steps (K = 32 KS) and at least one row;
   // the model's config checks guarantee both for every projection
-  if (a.K != a.KS * 32 || a.M <= 0 || a.ldx < a.K || !a.xf) return false;
+  if (a.K != a.KS * 32 || a.M <= 0 || (a.X && a.ldx < a.K) || !a.xf) return false;
+  if (a.yf && (epi != EPI_SWIGLU || a.N % 32)) return false;
   const int nrb = (a.M + 15) / 16;
   const size_t items = (size_t)nrb * a.KS * 64;
-  hipLaunchKernelGGL(split_frag_kernel, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, st, a.X, a.ldx, a.M, a.KS,
-                     (u32x4 *)a.xf, nrb);
+  if (a.X)  // not split by its producer
+    hipLaunchKernelGGL(split_frag_kernel, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, st, a.X, a.ldx, a.M,
+                       a.KS, (u32x4 *)a.xf, nrb);
   switch (p.nw) {
     case 4: return launch_cols<4>(epi, a, p, nrb, st);
     case 6: return launch_cols<6>(epi, a, p, nrb, st);

@@ -26,8 +26,10 @@ struct GemmArgs {
   int ldy;
   size_t ysplit;
   int ksplit;
-  void *xf = nullptr;  // wide kernel: scratch for the activations' hi/lo fragment planes
-                       // (gemm_wide_scratch_bytes(M, K) bytes)
+  void *xf = nullptr;  // wide kernel: the activations' hi/lo fragment planes
+                       // (gemm_wide_scratch_bytes(M, K) bytes): written by the producer (X null)
+                       // or by the launch itself, from X
+  void *yf = nullptr;  // wide kernel, EPI_SWIGLU: output as fragment planes (N / 32 k-steps) instead of Y
   // Deferred RMSNorm of the activations (skinny kernel): X holds x * gain and
   // every output row m is scaled by rsqrt(sum_g rs_ssq[g][m] / rs_d + rs_eps),
   // the per-row sums of squares left by the producing projection's EPI_RESID.
@@ -97,11 +99,12 @@ void launch_embed_block(const Dims &D, const void *embed, const int32_t *anchor,
 // With `tokens` given (and `embed`), row i's token is tokens[i] instead.
 // With `hdr` given (and `embed`, no skip_anchor), the launch also zeroes
 // hdr[0 .. hdr_words) (the step's workspace header; hdr[0] is `err`) before
-// any error of its own is raised.
+// any error of its own is raised.  With `planes` (width a multiple of 32) the
+// rows are also written as the wide GEMM's fragment planes; y may then be null.
 void launch_add_norm(const Dims &D, const float *x, float *x_out, int ldx, const float *parts, int np, size_t pstride,
                      const void *gain, float *y, int ldy, int rows, int width, bool skip_anchor,
                      const void *embed, const int32_t *anchor, int32_t *err, hipStream_t st,
-                     const int32_t *tokens = nullptr, uint32_t *hdr = nullptr, int hdr_words = 0);
+                     const int32_t *tokens = nullptr, uint32_t *hdr = nullptr, int hdr_words = 0, void *planes = nullptr);
 // q/k RMSNorm + RoPE on the QKV projection (sum of np partials); writes
 // Q [M][nq][dh], Kb/Vb [M][nkv][dh].  The projection's rows M + b*n_new + i
 // (n_new appended context rows per batch row) have their K (k-norm, RoPE at
@@ -115,9 +118,11 @@ void launch_qk_norm_rope(const Dims &D, const float *qkv, int np, size_t pstride
 int attn_nchunks(int max_ctx, int B);
 // amask (optional, [bs][B][B] bytes, B a multiple of 4 and at most 64): block
 // query j sees block key k only where amask[b][j][k] is set.
+// planes (optional): the output goes there as the wide GEMM's fragment planes, not to O.
 void launch_attention(const Dims &D, const float *Q, const float *Kb, const float *Vb,
                       const void *ck, const void *cv, const int32_t *ctx_lens, int max_ctx,
-                      float *part, float *O, int32_t *err, hipStream_t st, const uint8_t *amask = nullptr);
+                      float *part, float *O, int32_t *err, hipStream_t st, const uint8_t *amask = nullptr,
+                      void *planes = nullptr);
 size_t attn_part_floats(const Dims &D, int max_ctx);
 bool attn_supported(int nq, int nkv, int B);
 
