@@ -759,7 +759,9 @@ __global__ __launch_bounds__(NW * 64) void attn_flash_kernel(const float *__rest
   floatx4 oacc[DH / 16];
 #pragma unroll
   for (int x = 0; x < DH / 16; ++x) oacc[x] = floatx4{0.f, 0.f, 0.f, 0.f};
-  float m_run = -INFINITY, l_run = 0.f;  // of query row cc (the same in every g)
+  // of query row cc: the running maximum (the same in every g) and this lane's
+  // share of the sum (its own keys)
+  float m_run = -INFINITY, l_run = 0.f;
   uint32_t mbits = 0;  // MASKED: bit 4 t + e: block key b0 + 16 t + 4 g + e is visible to query row cc
 
   // scores of one block against this wave's rows -> online softmax -> P V.
@@ -786,40 +788,49 @@ __global__ __launch_bounds__(NW * 64) void attn_flash_kernel(const float *__rest
         }
       }
     }
-    float mb = -INFINITY;
+    // Q carries scale * log2 e, so the scores are base-2 logarithms of the
+    // weights and a weight is one subtraction and one exp2 instruction.
+    // Invalid and hidden keys get -inf (a weight of zero).
+    if (nvalid < kFlashKB || (MASKED && hilo)) {  // workgroup-uniform
+#pragma unroll
+      for (int t = 0; t < kFlashKB / 16; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const bool vis = !MASKED || !hilo || ((mbits >> (4 * t + e)) & 1);
+          sacc[t][e] = 16 * t + 4 * g + e < nvalid && vis ? sacc[t][e] : -INFINITY;
+        }
+    }
+    float mb = sacc[0][0];
 #pragma unroll
     for (int t = 0; t < kFlashKB / 16; ++t)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const bool vis = !MASKED || !hilo || ((mbits >> (4 * t + e)) & 1);
-        const float v = 16 * t + 4 * g + e < nvalid && vis ? sacc[t][e] * scale : -INFINITY;
-        sacc[t][e] = v;
-        mb = fmaxf(mb, v);
-      }
+      for (int e = 0; e < 4; ++e) mb = fmaxf(mb, sacc[t][e]);
     mb = fmaxf(mb, __shfl_xor(mb, 16, 64));
     mb = fmaxf(mb, __shfl_xor(mb, 32, 64));
-    // finite unless MASKED hides every key so far from the row: its p and sums then stay 0
-    const float mn = fmaxf(m_run, mb);
-    const float alpha = m_run == -INFINITY ? 0.f : expf(m_run - mn);
-    m_run = mn;
+    if (__any(mb > m_run)) {  // some row of this wave has a new maximum: rescale
+      const float mn = fmaxf(m_run, mb);
+      const float alpha = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - mn);
+      m_run = mn;
+      l_run *= alpha;
+      // output rows are 4 g + e: their factors come from lanes 4 g + e
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float ae = __shfl(alpha, 4 * g + e, 64);
+#pragma unroll
+        for (int x = 0; x < DH / 16; ++x) oacc[x][e] *= ae;
+      }
+    }
+    // MASKED: a row that has seen no key yet has m_run = -inf; its weights stay 0
+    const float mref = MASKED && m_run == -INFINITY ? 0.f : m_run;
     float p[kFlashKB / 16][4], lb = 0.f;
 #pragma unroll
     for (int t = 0; t < kFlashKB / 16; ++t)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        p[t][e] = sacc[t][e] == -INFINITY ? 0.f : expf(sacc[t][e] - mn);
+        p[t][e] = __builtin_amdgcn_exp2f(sacc[t][e] - mref);
         lb += p[t][e];
       }
-    lb += __shfl_xor(lb, 16, 64);
-    lb += __shfl_xor(lb, 32, 64);
-    l_run = alpha * l_run + lb;
-    // output rows are 4 g + e: their factors come from lanes 4 g + e
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float ae = __shfl(alpha, 4 * g + e, 64);
-#pragma unroll
-      for (int x = 0; x < DH / 16; ++x) oacc[x][e] *= ae;
-    }
+    l_run += lb;  // of this lane's keys: the four g of a row are added at the end
 #pragma unroll
     for (int u = 0; u < kFlashKB / 32; ++u) {
       if (2 * u >= nkt) break;  // (keys past the valid tiles have p = 0)
@@ -921,7 +932,8 @@ __global__ __launch_bounds__(NW * 64) void attn_flash_kernel(const float *__rest
 #pragma unroll
     for (int s = 0; s < DH / 32; ++s) {
       const float4 a = *(const float4 *)(qrow + 32 * s + 8 * g), d = *(const float4 *)(qrow + 32 * s + 8 * g + 4);
-      const float f[8] = {a.x, a.y, a.z, a.w, d.x, d.y, d.z, d.w};
+      const float f[8] = {a.x * scale, a.y * scale, a.z * scale, a.w * scale,
+                          d.x * scale, d.y * scale, d.z * scale, d.w * scale};
       split8(f, qhf[s], qlf[s]);
     }
   }
@@ -990,10 +1002,12 @@ __global__ __launch_bounds__(NW * 64) void attn_flash_kernel(const float *__rest
 #pragma unroll
     for (int x = 0; x < DH / 16; ++x) dst[16 * x + cc] = oacc[x][e];
   }
+  l_run += __shfl_xor(l_run, 16, 64);
+  l_run += __shfl_xor(l_run, 32, 64);
   if (g == 0) {
     const int qi = 16 * wave + cc, qh = kvh * G + qi / B, j = qi % B;
     float *dst = part + ((((size_t)b * nq + qh) * B + j) * nch + c) * (DH + 2);
-    dst[DH] = m_run;
+    dst[DH] = m_run;  // base 2
     dst[DH + 1] = l_run;
   }
 }
@@ -1008,7 +1022,7 @@ __global__ __launch_bounds__(NW * 64) void attn_flash_kernel(const float *__rest
 // weighted and summed in chunk order.  `planes` (instead of O): the hi/lo bf16
 // fragment planes the wide GEMM reads; a lane's columns are neighbours, so four
 // rows of a workgroup fill 64 bytes of each line.
-template <int DH, int CB = 40>
+template <int DH, int CB = 40, bool BASE2 = false>
 __global__ __launch_bounds__(256) void attn_combine_kernel(const float *__restrict__ part,
                                                            const int32_t *__restrict__ ctx_lens,
                                                            int max_ctx, float *__restrict__ O, int bs,
@@ -1020,7 +1034,7 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float *__restri
   const int j = item % B, qh = (item / B) % nq, b = item / (B * nq);
   int n = ctx_lens[b];
   n = n < 0 ? 0 : (n > max_ctx ? max_ctx : n);
-  if (runs > 0) CH = flash_run(n + B, runs);  // the one-pass kernel's runs
+  if constexpr (BASE2) CH = flash_run(n + B, runs);  // the one-pass kernel's runs
   const int nc = (n + B + CH - 1) / CH;
   const float *base = part + (((size_t)b * nq + qh) * B + j) * nch * (DH + 2);
   constexpr int PER = DH / 64;  // this lane's columns: PER lane .. PER lane + PER - 1
@@ -1036,22 +1050,24 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float *__restri
   };
 #pragma unroll
   for (int u = 0; u < CB; ++u) load(u, min(u, nc - 1));  // (clamped, in flight together)
+  // weight of a maximum m against a larger one: the one-pass kernel's are in base 2
+  auto weight = [&](float d) { return BASE2 ? __builtin_amdgcn_exp2f(d) : expf(d); };
   float M = -INFINITY, den = 0.f;
   for (int c = lane; c < nc; c += 64) {
     const float m = base[c * (DH + 2) + DH], l = base[c * (DH + 2) + DH + 1];
     const float Mn = fmaxf(M, m);
-    den = (M == -INFINITY ? 0.f : den * expf(M - Mn)) + (m == -INFINITY ? 0.f : l * expf(m - Mn));
+    den = (M == -INFINITY ? 0.f : den * weight(M - Mn)) + (m == -INFINITY ? 0.f : l * weight(m - Mn));
     M = Mn;
   }
   const float Mw = wave_max(M);
-  den = wave_sum(M == -INFINITY ? 0.f : den * expf(M - Mw));
+  den = wave_sum(M == -INFINITY ? 0.f : den * weight(M - Mw));
   M = Mw;
   float acc[PER];
 #pragma unroll
   for (int q = 0; q < PER; ++q) acc[q] = 0.f;
 #pragma unroll
   for (int u = 0; u < CB; ++u) {
-    const float wu = u < nc ? expf(w[u] - M) : 0.f;
+    const float wu = u < nc ? weight(w[u] - M) : 0.f;
 #pragma unroll
     for (int q = 0; q < PER; ++q) acc[q] = fmaf(wu, v[u][q], acc[q]);
   }
@@ -1060,7 +1076,7 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float *__restri
     for (int u = 0; u < CB; ++u) load(u, min(c0 + u, nc - 1));
 #pragma unroll
     for (int u = 0; u < CB; ++u) {
-      const float wu = c0 + u < nc ? expf(w[u] - M) : 0.f;
+      const float wu = c0 + u < nc ? weight(w[u] - M) : 0.f;
 #pragma unroll
       for (int q = 0; q < PER; ++q) acc[q] = fmaf(wu, v[u][q], acc[q]);
     }
@@ -1276,7 +1292,7 @@ void launch_attention(const Dims &D, const float *Q, const float *Kb, const floa
       const long target = std::max(1L, (R == 64 ? 2L : 1L) * n_cu / pairs);
       const int ngrp = (int)std::min(target, (long)(nkeys + kFlashKB - 1) / kFlashKB);
       const int nch = attn_nchunks(max_ctx, D.B);
-      const float scale = 1.0f / sqrtf(128.f);
+      const float scale = 1.4426950408889634f / sqrtf(128.f);  // scores in base 2
       const dim3 grid(ngrp, D.nkv, D.bs);
       auto go = [&](auto kernel, int threads) {
         (void)hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kFlashLds);
@@ -1292,10 +1308,10 @@ void launch_attention(const Dims &D, const float *Q, const float *Kb, const floa
         hipLaunchKernelGGL(kernel, dim3((items + 3) / 4), dim3(256), 0, st, part, ctx_lens, max_ctx, O, D.bs, D.B,
                            D.nq, nch, 0, ngrp, (uint16_t *)planes);
       };
-      if (ngrp <= 2) merge(attn_combine_kernel<128, 2>);
-      else if (ngrp <= 8) merge(attn_combine_kernel<128, 8>);
-      else if (ngrp <= 24) merge(attn_combine_kernel<128, 24>);  // one batch row at a 1024-key context: 17 runs
-      else merge(attn_combine_kernel<128, 40>);
+      if (ngrp <= 2) merge(attn_combine_kernel<128, 2, true>);
+      else if (ngrp <= 8) merge(attn_combine_kernel<128, 8, true>);
+      else if (ngrp <= 24) merge(attn_combine_kernel<128, 24, true>);  // one batch row at a 1024-key context: 17 runs
+      else merge(attn_combine_kernel<128, 40, true>);
       return;
     }
   }
