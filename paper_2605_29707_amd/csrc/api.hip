@@ -139,7 +139,7 @@ Dims make_dims(const domino_model *m, int bs) {
 
 // ---- workspace layout of the draft step
 struct WsLayout {
-  size_t err, best, slots, hdr_words, X, X2, A, FC, HP, QKV, Q, Kb, Vb, attn, O, WOp, F, DNp, H, LP, hbuf, ghbuf, ubuf, pval, pid,
+  size_t err, best, slots, hdr_words, X, X2, A, FC, QKV, Q, Kb, Vb, attn, O, WOp, F, DNp, H, LP, hbuf, ghbuf, ubuf, pval, pid,
       praw, XF, total;
   // residual-epilogue tickets (in the cleared header) and row sums of squares
   // of the deferred RMSNorms; 0: this layout has none
@@ -235,7 +235,6 @@ bool layout(const domino_model *m, int bs, int max_ctx, int max_new, int beta, W
   };
   w.A = take(rows_bytes(Ma, D.d));
   w.FC = take((size_t)p.fc.ksplit * bs * max_new * D.d * 4);
-  w.HP = take(head_part_floats(D) * 4);  // state GEMM partials (batches above kHeadFusedBatch)
   w.QKV = take((size_t)p.qkv.ksplit * Ma * qkvw * 4);
   w.Q = take((size_t)M * D.nq * D.dh * 4);
   w.Kb = take((size_t)M * D.nkv * D.dh * 4);
@@ -867,8 +866,6 @@ HeadArgs head_args(domino_model_t m, int32_t batch, int32_t branch, char *ws, co
   h.whh_KS = m->whh.KS;
   h.w1s_NT = m->w1s.NT;
   h.w1s_KS = m->w1s.KS;
-  h.hpart = head_part_floats(D) ? F(w.HP) : nullptr;
-  h.n_cu = m->n_cu;
   return h;
 }
 
@@ -945,7 +942,7 @@ namespace {
 // the per-workgroup log-sum-exp pairs, the label logits and the per-row CEs
 struct TrainLayout {
   WsLayout w;
-  size_t S, Y, part, lab, ce, total;
+  size_t S, Y, U, part, lab, ce, total;
   int GCt;
 };
 void train_layout(const domino_model *m, int bs, int max_ctx, int max_new, TrainLayout &t) {
@@ -961,6 +958,7 @@ void train_layout(const domino_model *m, int bs, int max_ctx, int max_new, Train
   };
   t.S = take(Mr * D.ds * 4);
   t.Y = take(Mr * D.r * 4);
+  t.U = take(train_u_bytes((int)Mr, D.r));
   t.part = take(Mr * t.GCt * 16);
   t.lab = take(2 * Mr * 4);
   t.ce = take(2 * Mr * 4);
@@ -1046,6 +1044,7 @@ domino_status domino_train_forward(domino_model_t m, int32_t batch, const int32_
   t.P = (const float *)(ws + w.LP) + (w.ldl - D.r);
   t.ldp = w.ldl;
   t.Y = (const float *)(ws + tl.Y);
+  t.uf = ws + tl.U;
   t.Lbase = (const float *)(ws + w.LP);
   t.ldl = w.ldl;
   t.labels = labels;
@@ -1236,10 +1235,9 @@ domino_status domino_verify_accept_noalloc(int32_t batch, int32_t n_nodes, int32
   void *sp = nullptr;
   domino_status s = scratch_for_current_device(&sp);
   if (s != DOMINO_OK) return s;
-  float *pv = (float *)sp;
   launch_accept_parts(batch, n_nodes, vocab, block, node_token, node_parent, target_logits,
-                      logits_dtype == DOMINO_BF16, accept_len, accepted_nodes, out_tokens, pv,
-                      (int32_t *)(pv + ent), error_word, (hipStream_t)stream);
+                      logits_dtype == DOMINO_BF16, accept_len, accepted_nodes, out_tokens, sp, error_word,
+                      (hipStream_t)stream);
   hipError_t he = hipGetLastError();
   if (he != hipSuccess) return fail(DOMINO_ERR_HIP, "verify_accept_noalloc launch: %s", hipGetErrorString(he));
   return DOMINO_OK;
@@ -1266,7 +1264,6 @@ domino_status domino_verify_sample(int32_t batch, int32_t block, int32_t vocab, 
   const size_t need = vs_ws_bytes(batch, block, vocab);
   if (workspace_bytes < need) return fail(DOMINO_ERR_WORKSPACE, "workspace has %zu bytes, needs %zu", workspace_bytes, need);
   hipStream_t st = (hipStream_t)stream;
-  launch_fill_u32((uint32_t *)workspace, 1, 0u, st);
   launch_verify_sample(batch, block, vocab, node_token, target_logits, logits_dtype == DOMINO_BF16, draft_logits,
                        temperature, seed, accept_len, accepted_nodes, out_tokens, workspace, st);
   hipError_t he = hipGetLastError();

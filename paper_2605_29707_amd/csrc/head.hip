@@ -1,23 +1,26 @@
 // Domino-head rollout (Sec. 4.1.2 causal encoder and low-rank correction,
-// Fig. 3 sequential rollout), as three short kernels per draft position j:
+// Fig. 3 sequential rollout), as short kernels per draft position j:
 //
-//   gru    y_{j-1} = top-1 of position j-1 (merged from the logits kernel's
-//          per-workgroup lists; the anchor for j = 1; a forced token when
+//   gru    y_{j-1} = top-1 of position j-1 (the best of the logits kernel's
+//          keys; the anchor for j = 1; a forced token when
 //          teacher forcing), then S_{j-1} = GRU(E[y_{j-1}], S_{j-2}) for a
 //          slice of the d_s state indices per workgroup.  The input half of
 //          the gates, E[y] W_ih^T, is a row of the table G = E W_ih^T built at
 //          model creation, so a step gathers 3*d_s values instead of streaming
 //          W_ih.
 //   u      u = SiLU(W1[:, :d] H_j + W1[:, d:] S_{j-1}) (the H half comes from
-//          the LM-head GEMM).
-//   logits L_j = L_base_j + W2 u over a vocabulary slice per workgroup, the
-//          slice's top-beta under (value desc, id asc), and an atomic max of
-//          its top-1 into the position's key.
+//          the LM-head GEMM), and W_hh S_{j-1} for the next position's gates.
+//   logits L_j = L_base_j + W2 u over a vocabulary slice per workgroup, and an
+//          atomic max of its top-1 into the position's key.  With beta > 1 the
+//          corrected logits also replace L_base_j in memory: only the top-1 is
+//          on the chain from position to position, the other ranks are selected
+//          for all positions at once after the loop.
 // A kernel boundary is the cheapest grid-wide handshake on this device (about
 // 1.6 us against about 4 us for a 256-workgroup spin barrier), so the
-// rollout is 3(B-1)+1 launches rather than one persistent kernel; the top-1
+// rollout is 3(B-1) launches and the final selection rather than one persistent
+// kernel (which one or two batch rows and branch 1 still run, below); the top-1
 // of each position is a 64-bit atomic max, so no launch merges lists inside
-// the loop (the full top-beta lists are merged once at the end).
+// the loop.
 #include "common.h"
 #include "kernels.h"
 #include "mfma.h"
@@ -315,17 +318,21 @@ __global__ __launch_bounds__(kStateWaves * 64) void head_state_kernel(HeadArgs h
 }
 
 // ---------------------------------------------------------------------------
-// Batches above kFusedBatch: W_hh S_{j-1} and W1[:, d:] S_j run as K-split
-// GEMMs (the projections' weight-streaming kernel over packed copies of the
-// two matrices), which stage the states once per workgroup; these kernels add
-// the partials in split order and finish each step elementwise.
+// Batches above kFusedBatch: the elementwise GRU update and the state's two
+// products are a launch each.  (Two K-split GEMMs and two elementwise launches
+// to add their partials took 24 us a position at 32 rows, 20 at 16; the two
+// launches take 13 and 11.)
 // ---------------------------------------------------------------------------
 // S_j = GRU(G[y_{j-1}], S_{j-1}), one workgroup row per batch row
-__global__ __launch_bounds__(256) void head_gru_elem_kernel(HeadArgs h, int j, const float *__restrict__ gp, int np,
-                                                            size_t pstride) {
+__global__ __launch_bounds__(256) void head_gru_elem_kernel(HeadArgs h, int j) {
   const Dims &D = h.D;
   const int bs = D.bs, ds = D.ds, depth = D.B - 1, V = D.V;
-  const int b = blockIdx.y;
+  const int b = blockIdx.y, i = blockIdx.x * 256 + threadIdx.x;
+  // the hidden gates W_hh S_{j-1} + b_hh (S_0 = 0: b_hh alone at j = 1), loaded beside the keys
+  float gh[3];
+  const float *ghp = j > 1 ? h.ghbuf + ((size_t)((j - 1) & 1) * bs + b) * 3 * ds : h.bhh;
+#pragma unroll
+  for (int q = 0; q < 3; ++q) gh[q] = ghp[q * ds + min(i, ds - 1)];
   __shared__ int ysh;
   if (threadIdx.x == 0) {  // y_{j-1}: the anchor, a forced token, or the decoded best key of position j-1
     int y;
@@ -341,17 +348,9 @@ __global__ __launch_bounds__(256) void head_gru_elem_kernel(HeadArgs h, int j, c
     ysh = y;
   }
   __syncthreads();
-  const int i = blockIdx.x * 256 + threadIdx.x;
   if (i >= ds) return;
   const float *hprev = h.hbuf + (size_t)((j - 1) & 1) * bs * ds;
   float *hnext = h.hbuf + (size_t)(j & 1) * bs * ds;
-  float gh[3];
-#pragma unroll
-  for (int q = 0; q < 3; ++q) {
-    float acc = 0.f;  // W_hh S_{j-1} (S_0 = 0: no product at j = 1)
-    for (int p = 0; p < np; ++p) acc += gp[(size_t)p * pstride + (size_t)b * 3 * ds + q * ds + i];
-    gh[q] = acc + h.bhh[q * ds + i];
-  }
   const float *gy = h.gtab + (size_t)ysh * 3 * ds;  // b_ih is in G
   const float rg = sigm(gy[i] + gh[0]), zg = sigm(gy[ds + i] + gh[1]);
   const float ng = tanhf(fmaf(rg, gh[2], gy[2 * ds + i]));
@@ -361,172 +360,95 @@ __global__ __launch_bounds__(256) void head_gru_elem_kernel(HeadArgs h, int j, c
   if (h.states) h.states[((size_t)b * depth + (j - 1)) * ds + i] = hn;
 }
 
-// u_j = SiLU(W1[:, :d] H_j + W1[:, d:] S_j) from the summed partials
-__global__ __launch_bounds__(256) void head_u_elem_kernel(HeadArgs h, int j, const float *__restrict__ up, int np,
-                                                          size_t pstride) {
+// One 16-row tile of [W1[:, d:]; W_hh] times S_j for every batch row: the first
+// nu workgroups give u_j = SiLU(W1[:, :d] H_j + W1[:, d:] S_j), the others the
+// hidden gates W_hh S_j + b_hh of the next position.  Its 8 waves split K
+// (consecutive k-steps of the packed tiles); each loads its own states straight
+// into fragments, and the partial sums meet in LDS, added in wave order.
+// Latency-bound: every load of a wave is in flight at once.
+constexpr int kRowWaves = 8;
+template <typename WT, int MT>
+__global__ __launch_bounds__(kRowWaves * 64) void head_rows_kernel(HeadArgs h, int j, int nu) {
+  constexpr int EPL = Frag<WT>::EPL, KSTEP = Frag<WT>::KSTEP, XF = XStage<WT>::XF;
+  constexpr int kU = 4;  // k-steps in flight
   const Dims &D = h.D;
-  const int r = D.r, depth = D.B - 1;
-  const int e = blockIdx.x * 256 + threadIdx.x;
-  if (e >= D.bs * r) return;
-  const int b = e / r, k = e % r;
-  float acc = 0.f;
-  for (int p = 0; p < np; ++p) acc += up[(size_t)p * pstride + e];
-  const float x = h.P[((size_t)b * depth + (j - 1)) * h.ldp + k] + acc;
-  h.ubuf[(size_t)b * h.u_ld + (size_t)(j - 1) * h.u_pos + k] = x / (1.f + expf(-x));
+  const int bs = D.bs, ds = D.ds, r = D.r, depth = D.B - 1;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, cc = lane & 15;
+  const bool is_u = (int)blockIdx.x < nu;  // workgroup-uniform
+  const int tile = is_u ? blockIdx.x : blockIdx.x - nu;
+  const int KS = is_u ? h.w1s_KS : h.whh_KS;  // equal: both are over d_s
+  const u32x4 *P = (const u32x4 *)(is_u ? h.w1s_p : h.whh_p) + (size_t)tile * KS * 64 + lane;
+  const float *S = h.hbuf + (size_t)(j & 1) * bs * ds;
+  const int per = (KS + kRowWaves - 1) / kRowWaves, s0 = wave * per, s1 = min(KS, s0 + per);
+  floatx4 acc[MT];
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) acc[mt] = floatx4{0.f, 0.f, 0.f, 0.f};
+  for (int s = s0; s < s1; s += kU) {
+    u32x4 w[kU];
+    float4 x[kU][MT][EPL / 4];
+#pragma unroll
+    for (int q = 0; q < kU; ++q) {
+      const int sc = min(s + q, s1 - 1);
+      w[q] = P[(size_t)sc * 64];
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) {
+        const float *src = S + (size_t)min(mt * 16 + cc, bs - 1) * ds + sc * KSTEP + g * EPL;
+#pragma unroll
+        for (int e = 0; e < EPL / 4; ++e) x[q][mt][e] = *(const float4 *)(src + 4 * e);
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < kU; ++q)
+      if (s + q < s1) {
+        u32x4 xf[MT * XF];
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) XStage<WT>::put(xf + mt * XF, x[q][mt]);
+        Mac2<WT, MT>::step(w[q], xf, acc);
+      }
+  }
+  __shared__ floatx4 red[kRowWaves][MT][64];
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) red[wave][mt][lane] = acc[mt];
+  __syncthreads();
+  if (wave >= MT) return;
+  const int bb = wave * 16 + cc;  // wave mt finishes batch rows 16 mt ..
+  floatx4 t = red[0][wave][lane];
+#pragma unroll
+  for (int w = 1; w < kRowWaves; ++w) t += red[w][wave][lane];
+  if (bb >= bs) return;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int row = tile * 16 + 4 * g + e;
+    if (is_u) {
+      if (row >= r) continue;
+      const float x = h.P[((size_t)bb * depth + (j - 1)) * h.ldp + row] + t[e];
+      h.ubuf[(size_t)bb * h.u_ld + (size_t)(j - 1) * h.u_pos + row] = x / (1.f + expf(-x));
+    } else if (row < 3 * ds) {
+      h.ghbuf[((size_t)(j & 1) * bs + bb) * 3 * ds + row] = t[e] + h.bhh[row];
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------
 // logits: matrix-core W2 tiles times the staged u (batch rows as the 16
-// columns of the B operand, hi/lo split for bf16), plus L_base, then each
-// workgroup's top-beta per batch row.  A workgroup covers ROWS vocabulary
-// rows (8 waves x kTPW tiles of 16).
+// columns of the B operand, hi/lo split for bf16), added onto L_base, then each
+// workgroup's top-1 per batch row.  A workgroup covers ROWS vocabulary
+// rows (8 waves x kTPW tiles of 16).  (With the top-beta of beta > 1 selected
+// here, a position took 44 us at 32 rows and beta 4, half of it the selection;
+// now 31 us, and 92 once for the selection.)
 // ---------------------------------------------------------------------------
 constexpr int kLogitWaves = 8;
-// W2 tiles per wave: as many as fit the registers (all of a wave's loads are
-// issued at once, and the grid then fits the GPU in one round)
-constexpr int kTpwSmall = 5;
-constexpr int logit_tpw(int KS, int MT) { return KS * MT <= 8 ? kTpwSmall : (KS * MT <= 16 ? 3 : 1); }
+// W2 tiles per wave: five, so that the grid fits the GPU in one round at the
+// Qwen3 vocabulary (238 workgroups); one where the vocabulary is so small that
+// even then most CUs get no workgroup
+constexpr int logit_tpw(int KS, int MT) { return KS == 8 ? 5 : (MT == 1 ? 5 : (MT == 2 ? 3 : 1)); }
+constexpr int kSmallVocabTiles = 256 * kLogitWaves;
 
-// Compare-exchange under the selection order: (a, b) -> (better, worse).
-DEVI void sel_ce(float &va, int &ia, float &vb, int &ib) {
-  const bool t = better(vb, ib, va, ia);
-  const float v0 = t ? vb : va, v1 = t ? va : vb;
-  const int i0 = t ? ib : ia, i1 = t ? ia : ib;
-  va = v0;
-  ia = i0;
-  vb = v1;
-  ib = i1;
-}
-// a (sorted best first) <- the best L of a and b (both sorted): the pairwise
-// better of a[i] and b[L-1-i] is a bitonic sequence holding exactly those L,
-// which a bitonic merge network sorts.
-template <int L>
-DEVI void sel_merge(float (&av)[L], int (&ai)[L], const float (&bv)[L], const int (&bi)[L]) {
-#pragma unroll
-  for (int i = 0; i < L; ++i) {
-    const bool t = better(bv[L - 1 - i], bi[L - 1 - i], av[i], ai[i]);
-    av[i] = t ? bv[L - 1 - i] : av[i];
-    ai[i] = t ? bi[L - 1 - i] : ai[i];
-  }
-#pragma unroll
-  for (int st = L / 2; st >= 1; st >>= 1)
-#pragma unroll
-    for (int i = 0; i < L; ++i)
-      if ((i & st) == 0) sel_ce(av[i], ai[i], av[i + st], ai[i + st]);
-}
-
-// Top-beta (beta <= L) of a logits workgroup's rows for every batch row, in
-// registers: each lane sorts its own candidates of a batch row into an
-// L-entry list; within a wave the four lanes of a row (g) hand their lists to
-// lane g = 0 through LDS, which merges them; the waves' lists meet in LDS,
-// where one thread per batch row merges them and emits the first beta
-// entries (and the top-1 into the position's key).  (Merging by cross-lane
-// shuffles instead made the compiler take minutes per instantiation.)
-// LDS the lists need (after the u fragments): a wave's lane lists of one
-// m-tile, and each wave's list per batch row
-constexpr size_t topl_lds_bytes(int L, int MT) {
-  return (size_t)kLogitWaves * (4 * 16 + MT * 16) * L * (sizeof(float) + sizeof(int));
-}
-template <int L, int kTPW, int MT>
-DEVI void logits_topl(const HeadArgs &h, int j, const int (&tiles)[kTPW], const float4 (&lb)[kTPW][MT],
-                      const floatx4 (&acc)[kTPW][MT], unsigned char *sbuf) {
-  const Dims &D = h.D;
-  const int bs = D.bs, V = D.V, beta = h.beta;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, cc = lane & 15;
-  auto xg_v = (float(*)[4][16][L])sbuf;  // [kLogitWaves][4][16][L]
-  auto xg_i = (int(*)[4][16][L])(sbuf + sizeof(float) * kLogitWaves * 4 * 16 * L);
-  auto cand_v = (float(*)[MT * 16][L])(sbuf + (sizeof(float) + sizeof(int)) * kLogitWaves * 4 * 16 * L);
-  auto cand_i = (int(*)[MT * 16][L])(sbuf + (sizeof(float) + sizeof(int)) * kLogitWaves * 4 * 16 * L +
-                                     sizeof(float) * kLogitWaves * MT * 16 * L);
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt) {
-    float lv[L];
-    int li[L];
-#pragma unroll
-    for (int k = 0; k < L; ++k) {
-      lv[k] = -INFINITY;
-      li[k] = INT_MAX;
-    }
-#pragma unroll
-    for (int q = 0; q < kTPW; ++q)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int n = tiles[q] * 16 + 4 * g + e;
-        const float lbe = e == 0 ? lb[q][mt].x : (e == 1 ? lb[q][mt].y : (e == 2 ? lb[q][mt].z : lb[q][mt].w));
-        float v = n < V ? order_val(lbe + acc[q][mt][e]) : -INFINITY;
-        int id = n < V ? n : INT_MAX;
-#pragma unroll
-        for (int k = 0; k < L; ++k) sel_ce(lv[k], li[k], v, id);  // bubble (v, id) into place
-      }
-    // a wave's LDS accesses complete in order, so lane g = 0 reads the lists
-    // the other lanes of its wave wrote just before (and the next m-tile's
-    // writes follow its reads)
-    if (g > 0) {
-#pragma unroll
-      for (int k = 0; k < L; ++k) {
-        xg_v[wave][g][cc][k] = lv[k];
-        xg_i[wave][g][cc][k] = li[k];
-      }
-    }
-    __builtin_amdgcn_wave_barrier();
-    if (g == 0) {
-#pragma unroll
-      for (int o = 1; o < 4; ++o) {
-        float ov[L];
-        int oi[L];
-#pragma unroll
-        for (int k = 0; k < L; ++k) {
-          ov[k] = xg_v[wave][o][cc][k];
-          oi[k] = xg_i[wave][o][cc][k];
-        }
-        sel_merge<L>(lv, li, ov, oi);
-      }
-#pragma unroll
-      for (int k = 0; k < L; ++k) {
-        cand_v[wave][mt * 16 + cc][k] = lv[k];
-        cand_i[wave][mt * 16 + cc][k] = li[k];
-      }
-    }
-    __builtin_amdgcn_wave_barrier();
-  }
-  __syncthreads();
-  for (int bb = tid; bb < bs; bb += kLogitWaves * 64) {
-    float lv[L];
-    int li[L];
-#pragma unroll
-    for (int k = 0; k < L; ++k) {
-      lv[k] = cand_v[0][bb][k];
-      li[k] = cand_i[0][bb][k];
-    }
-    for (int w = 1; w < kLogitWaves; ++w) {
-      float ov[L];
-      int oi[L];
-#pragma unroll
-      for (int k = 0; k < L; ++k) {
-        ov[k] = cand_v[w][bb][k];
-        oi[k] = cand_i[w][bb][k];
-      }
-      sel_merge<L>(lv, li, ov, oi);
-    }
-    const size_t o = (((size_t)(j - 1) * bs + bb) * h.GC + blockIdx.x) * beta;
-#pragma unroll
-    for (int k = 0; k < L; ++k)
-      if (k < beta) {
-        h.pval[o + k] = lv[k];
-        h.pid[o + k] = li[k];
-      }
-    // top-1 of this workgroup into the position's best key (order-independent max)
-    if (li[0] != INT_MAX)
-      atomicMax(&h.best[((size_t)(j - 1) * bs + bb) * kBestSlots + (blockIdx.x % kBestSlots)], encode_best(lv[0], li[0]));
-  }
-}
-
-template <typename WT, int KS, int MT>
+template <typename WT, int KS, int MT, int kTPW>
 __global__ __launch_bounds__(kLogitWaves * 64) void head_logits_kernel(HeadArgs h, int j) {
   constexpr int EPL = Frag<WT>::EPL, KSTEP = Frag<WT>::KSTEP, XF = XStage<WT>::XF;
-  constexpr int kTPW = logit_tpw(KS, MT);
   const Dims &D = h.D;
-  const int bs = D.bs, r = D.r, V = D.V, depth = D.B - 1, beta = h.beta;
+  const int bs = D.bs, V = D.V, depth = D.B - 1;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int g = lane >> 4, cc = lane & 15;
   const int NT = (V + 15) / 16;
@@ -551,13 +473,13 @@ __global__ __launch_bounds__(kLogitWaves * 64) void head_logits_kernel(HeadArgs 
 #pragma unroll
     for (int e = 0; e < EPL / 4; ++e) uv[q][e] = *(const float4 *)(src + 4 * e);
   }
-  // then the L_base values this wave will add (rows are padded to whole tiles,
-  // ldl >= 16 * NT, so a tile's four values load as one float4; entries past V
-  // are masked below), then the W2 fragments of its tiles
+  // then the L_base values the products are added onto (rows are padded to whole
+  // tiles, ldl >= 16 * NT, so a tile's four values load as one float4, the layout
+  // of the sums; entries past V are masked below), then the W2 fragments of its tiles
   int tiles[kTPW];
 #pragma unroll
   for (int q = 0; q < kTPW; ++q) tiles[q] = (blockIdx.x * kLogitWaves + wave) * kTPW + q;
-  float4 lb[kTPW][MT];
+  floatx4 acc[kTPW][MT];
 #pragma unroll
   for (int q = 0; q < kTPW; ++q)
 #pragma unroll
@@ -565,16 +487,22 @@ __global__ __launch_bounds__(kLogitWaves * 64) void head_logits_kernel(HeadArgs 
       const int bb = mt * 16 + cc;
       const int t = tiles[q] < NT ? tiles[q] : NT - 1;
       // clamped row, unconditional (lanes of padding rows are never read)
-      lb[q][mt] = *(const float4 *)(h.Lbase + ((size_t)min(bb, bs - 1) * depth + (j - 1)) * h.ldl + t * 16 + 4 * g);
+      acc[q][mt] =
+          *(const floatx4 *)(h.Lbase + ((size_t)min(bb, bs - 1) * depth + (j - 1)) * h.ldl + t * 16 + 4 * g);
     }
+  // W2 fragments: kRing tiles in flight (8 waves then keep 192 KB or more per CU on
+  // the way, several times what the latency needs), later tiles into the
+  // registers of the finished ones
+  constexpr int kRing = KS == 8 ? (kTPW < 3 ? kTPW : 3) : (kTPW < 2 ? kTPW : 2);
   const u32x4 *w2p = (const u32x4 *)h.w2p;
-  u32x4 wf[kTPW][KS];
-#pragma unroll
-  for (int q = 0; q < kTPW; ++q) {
+  u32x4 wf[kRing][KS];
+  auto load_tile = [&](int q) {
     const int t = tiles[q] < NT ? tiles[q] : NT - 1;
 #pragma unroll
-    for (int s = 0; s < KS; ++s) wf[q][s] = w2p[((size_t)t * KS + s) * 64 + lane];
-  }
+    for (int s = 0; s < KS; ++s) wf[q % kRing][s] = w2p[((size_t)t * KS + s) * 64 + lane];
+  };
+#pragma unroll
+  for (int q = 0; q < kRing; ++q) load_tile(q);
   // u staged as matrix-core B fragments
 #pragma unroll
   for (int q = 0; q < kUIt; ++q) {
@@ -583,15 +511,10 @@ __global__ __launch_bounds__(kLogitWaves * 64) void head_logits_kernel(HeadArgs 
   }
   __syncthreads();
 
-  floatx4 acc[kTPW][MT];
-#pragma unroll
-  for (int q = 0; q < kTPW; ++q)
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) acc[q][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
   // tile-major, in the order the fragments were requested: tile q's products
   // start as soon as its fragments arrive, overlapping the rest of the stream
 #pragma unroll
-  for (int q = 0; q < kTPW; ++q)
+  for (int q = 0; q < kTPW; ++q) {
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       u32x4 xf[MT * XF];
@@ -599,14 +522,28 @@ __global__ __launch_bounds__(kLogitWaves * 64) void head_logits_kernel(HeadArgs 
       for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
         for (int f = 0; f < XF; ++f) xf[mt * XF + f] = us[((size_t)(s * MT + mt) * 64 + lane) * XF + f];
-      Mac2<WT, MT>::step(wf[q][s], xf, acc[q]);
+      Mac2<WT, MT>::step(wf[q % kRing][s], xf, acc[q]);
     }
+    __builtin_amdgcn_sched_barrier(0);
+    if (q + kRing < kTPW) load_tile(q + kRing);
+    __builtin_amdgcn_sched_barrier(0);
+  }
 
   // corrected logits of this workgroup's rows: lane (g, cc) holds rows
   // 16 t + 4 g + e of batch row mt * 16 + cc
-  if (beta == 1) {
+  if (h.lout) {  // beta > 1: for the selection after the loop (whole tiles: the padding keeps its zeros)
+#pragma unroll
+    for (int q = 0; q < kTPW; ++q)
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) {
+        const int bb = mt * 16 + cc;
+        if (bb < bs && tiles[q] < NT)
+          *(floatx4 *)(h.lout + ((size_t)bb * depth + (j - 1)) * h.ldl + tiles[q] * 16 + 4 * g) = acc[q][mt];
+      }
+  }
+  {
     // top-1 without staging: a running best per batch row in registers, the
-    // four lanes of a row combined by shuffles, then one entry per (wave, row)
+    // four lanes of a row combined by shuffles, then one entry per (wave, row).
     // With sampling the key is L / T + Gumbel noise of (row, position, id): the
     // maximum is a draw from softmax(L / T); raw carries the chosen L.
     __shared__ float best_v[kLogitWaves][64], best_r[kLogitWaves][64];
@@ -623,8 +560,7 @@ __global__ __launch_bounds__(kLogitWaves * 64) void head_logits_kernel(HeadArgs 
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const int n = tiles[q] * 16 + 4 * g + e;
-          const float lbe = e == 0 ? lb[q][mt].x : (e == 1 ? lb[q][mt].y : (e == 2 ? lb[q][mt].z : lb[q][mt].w));
-          const float val = lbe + acc[q][mt][e];
+          const float val = acc[q][mt][e];
           if (bb < bs && n < V) {
             if (h.final_logits) h.final_logits[((size_t)bb * depth + (j - 1)) * V + n] = val;
             const float key = h.sample ? val * h.inv_temp + rng_gumbel(noise.x[e]) : val;
@@ -665,45 +601,116 @@ __global__ __launch_bounds__(kLogitWaves * 64) void head_logits_kernel(HeadArgs 
           id = best_i[w][bb];
           raw = best_r[w][bb];
         }
-      const size_t o = ((size_t)(j - 1) * bs + bb) * h.GC + blockIdx.x;
-      h.pval[o] = v;
-      h.pid[o] = id;
-      if (h.sample) h.praw[o] = raw;
+      if (!h.lout) {  // branch 1: one entry a workgroup for the final merge
+        const size_t o = ((size_t)(j - 1) * bs + bb) * h.GC + blockIdx.x;
+        h.pval[o] = v;
+        h.pid[o] = id;
+        if (h.sample) h.praw[o] = raw;
+      }
       if (id != INT_MAX)
         atomicMax(&h.best[((size_t)(j - 1) * bs + bb) * kBestSlots + (blockIdx.x % kBestSlots)], encode_best(v, id));
     }
-    return;
   }
-  if (h.final_logits) {
-#pragma unroll
-    for (int q = 0; q < kTPW; ++q)
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
-        const int bb = mt * 16 + cc;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int n = tiles[q] * 16 + 4 * g + e;
-          const float lbe = e == 0 ? lb[q][mt].x : (e == 1 ? lb[q][mt].y : (e == 2 ? lb[q][mt].z : lb[q][mt].w));
-          if (bb < bs && n < V) h.final_logits[((size_t)bb * depth + (j - 1)) * V + n] = lbe + acc[q][mt][e];
-        }
-      }
-  }
-  unsigned char *sbuf = smem + sizeof(u32x4) * KS * MT * 64 * XF;
-  if (beta <= 4) logits_topl<4, kTPW, MT>(h, j, tiles, lb, acc, sbuf);
-  else logits_topl<8, kTPW, MT>(h, j, tiles, lb, acc, sbuf);
 }
 
-// Merge every workgroup's top-beta list of one (position, batch row) after the
-// rollout; one wave per (j, b).
-__global__ __launch_bounds__(64) void head_merge_kernel(HeadArgs h) {
+// The top-beta (beta > 1) of every position's corrected logits, after the
+// rollout: a wave per kTopWave values of one row, 64 a lane in registers.  The
+// beta-th largest of the 64 lane maxima bounds the wave's beta-th best from
+// below, so only the few values from there on (about beta of 4096) are
+// inserted, one by one, into a sorted list that every lane keeps alike; the bound
+// follows the list's last entry.  Bound by reading the logits (292 MB at 32
+// rows, 45 us; the whole selection 92).
+constexpr int kTopWave = 4096;
+__global__ __launch_bounds__(256) void head_topb_kernel(HeadArgs h, int nchunk) {
+  const int V = h.D.V, beta = h.beta, depth = h.D.B - 1, bs = h.D.bs;
+  const int lane = threadIdx.x & 63;
+  const int c = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int j = blockIdx.y, b = blockIdx.z;
+  if (c >= nchunk) return;  // (whole waves; no barrier below)
+  const float *row = h.Lbase + ((size_t)b * depth + j) * h.ldl;
+  constexpr int NQ = kTopWave / 256;
+  float4 x[NQ];
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {  // rows are padded to whole tiles of 16: a float4 that starts inside ends inside
+    const int id = c * kTopWave + q * 256 + 4 * lane;
+    x[q] = __builtin_bit_cast(float4, __builtin_nontemporal_load((const floatx4 *)(row + min(id, (V - 1) / 4 * 4))));
+  }
+  float m = -INFINITY;
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    const int id = c * kTopWave + q * 256 + 4 * lane;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      float &v = (&x[q].x)[e];
+      v = id + e < V ? order_val(v) : -INFINITY;
+      m = fmaxf(m, v);
+    }
+  }
+  float t = -INFINITY;
+  for (int k = 0; k < beta; ++k) {  // the beta-th largest lane maximum (equal ones leave together: the bound is only lower)
+    t = wave_max(m);
+    if (m == t) m = -INFINITY;
+  }
+  float lv[8];
+  int li[8];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    lv[k] = -INFINITY;
+    li[k] = INT_MAX;
+  }
+  float wv = t;  // what a value has to beat: the bound, then the list's entry of rank beta
+  int wi = INT_MAX;
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    const int id = c * kTopWave + q * 256 + 4 * lane;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float v = (&x[q].x)[e];
+      unsigned long long mk = __ballot(id + e < V && better(v, id + e, wv, wi));
+      while (mk) {  // wave-uniform
+        const int l = __ffsll(mk) - 1;
+        mk &= mk - 1;
+        const float cv = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+        const int ci = c * kTopWave + q * 256 + 4 * l + e;
+        if (!better(cv, ci, wv, wi)) continue;
+        list_insert(lv, li, cv, ci);
+        float ev = lv[0];
+        int ei = li[0];
+#pragma unroll
+        for (int k = 1; k < 8; ++k)
+          if (k < beta) {
+            ev = lv[k];
+            ei = li[k];
+          }
+        if (ei != INT_MAX) {  // the list has beta entries
+          wv = ev;
+          wi = ei;
+        }
+      }
+    }
+  }
+  if (lane == 0) {
+    const size_t o = (((size_t)j * bs + b) * nchunk + c) * beta;
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+      if (k < beta) {
+        h.pval[o + k] = lv[k];
+        h.pid[o + k] = li[k];
+      }
+  }
+}
+
+// Merge the nlist top-beta lists of one (position, batch row) after the
+// rollout (branch 1: a workgroup's top-1 each); one wave per (j, b).
+__global__ __launch_bounds__(64) void head_merge_kernel(HeadArgs h, int nlist) {
   const int j = blockIdx.x, b = blockIdx.y;
   const int bs = h.D.bs, depth = h.D.B - 1, beta = h.beta;
   const int lane = threadIdx.x;
-  const size_t base = ((size_t)j * bs + b) * h.GC * beta;
+  const size_t base = ((size_t)j * bs + b) * nlist * beta;
   if (h.sample) {  // branch 1: the largest key wins; its raw logit is the reported value
     float bv = -INFINITY, br = 0.f;
     int bi = INT_MAX;
-    for (int c = lane; c < h.GC; c += 64) {
+    for (int c = lane; c < nlist; c += 64) {
       const float v = order_val(h.pval[base + c]);
       const int id = h.pid[base + c];
       const float raw = h.praw[base + c];
@@ -732,7 +739,7 @@ __global__ __launch_bounds__(64) void head_merge_kernel(HeadArgs h) {
   }
   float mv;
   int mi;
-  wave_select_mem(h.pval + base, h.pid + base, h.GC * beta, beta, mv, mi);
+  wave_select_mem(h.pval + base, h.pid + base, nlist * beta, beta, mv, mi);
   if (lane < beta) {
     h.topk_ids[((size_t)b * depth + j) * beta + lane] = mi;
     h.topk_vals[((size_t)b * depth + j) * beta + lane] = mv;
@@ -1191,6 +1198,12 @@ __global__ __launch_bounds__(kPersWaves * 64) void head_persist_kernel(HeadArgs 
   }
 }
 
+// Its workgroups, and so best-key slots in use per batch row (never more than
+// the GC the workspace has, whose workgroups hold at most as many tiles)
+static int persist_groups(const Dims &D) {
+  return ((D.V + 15) / 16 + kPersWaves * kPersTiles - 1) / (kPersWaves * kPersTiles);
+}
+
 // The persistent kernel for one or two batch rows of `h` (D.bs <= 2): checks
 // the shapes and the device, and picks the instantiation and its LDS size.
 static bool persist_plan(const HeadArgs &h, int n_cu, const void **fn, size_t *lds_out, int *nr_out) {
@@ -1198,11 +1211,10 @@ static bool persist_plan(const HeadArgs &h, int n_cu, const void **fn, size_t *l
   if (!D.bf16 || D.r != kPersKS * 32 || D.bs < 1 || D.bs > 2 || h.beta != 1 || D.ds % 32 || D.ds > 256 * 8 ||
       D.V >= (1 << kKeyIdBits) || D.B > 64 || !h.uslot || !h.kslot || !h.abort_flag || (h.sample && !h.praw))
     return false;
-  const int NT = (D.V + 15) / 16;
-  const int G = (NT + kPersWaves * kPersTiles - 1) / (kPersWaves * kPersTiles);
+  const int G = persist_groups(D);
   // every workgroup must own a u row (its u slot doubles as its "gates stored" signal),
   // and the polls cover at most 4 * kFusedBatch slots per lane
-  if (G != h.GC || G > n_cu || G > D.r || G > 256) return false;  // polls: 4 slots per lane per batch row
+  if (G > h.GC || G > n_cu || G > D.r || G > 256) return false;  // polls: 4 slots per lane per batch row
   const int nr = (D.r + 3 * D.ds + G - 1) / G;
   const size_t lds = (size_t)nr * (D.ds / 8) * 16 + sizeof(float) * (size_t)D.bs * D.ds +
                      sizeof(u32x4) * kPersKS * 64 + sizeof(u32x4) * kPersWaves * kPersKS * 64 +
@@ -1282,7 +1294,7 @@ bool launch_head_persistent(const HeadArgs &h, int n_cu, hipStream_t st) {
     HeadArgs a = rows_of(h, 2 * p, nb);
     int nrv = nr[nb - 1];
     void *args[] = {&a, &nrv};
-    if (hipLaunchKernel(fn[nb - 1], dim3(a.GC), dim3(kPersWaves * 64), args, lds[nb - 1], st) != hipSuccess) {
+    if (hipLaunchKernel(fn[nb - 1], dim3(persist_groups(a.D)), dim3(kPersWaves * 64), args, lds[nb - 1], st) != hipSuccess) {
       // (a failure after the first pair leaves nothing wrong behind: the
       // launch-pair rollout that follows rewrites every row's outputs)
       (void)hipGetLastError();
@@ -1292,124 +1304,97 @@ bool launch_head_persistent(const HeadArgs &h, int n_cu, hipStream_t st) {
   return true;
 }
 
-static int logit_rows(const Dims &D) {
+static int logits_mt(const Dims &D) { return D.bs <= 16 ? 1 : (D.bs <= 32 ? 2 : 4); }
+static int logits_tiles(const Dims &D) {  // W2 tiles per wave
   const int KS = D.r / (D.bf16 ? 32 : 16);
-  const int MT = D.bs <= 16 ? 1 : (D.bs <= 32 ? 2 : 4);
-  return kLogitWaves * logit_tpw(KS, MT) * 16;
+  return (D.V + 15) / 16 <= kSmallVocabTiles ? 1 : logit_tpw(KS, logits_mt(D));
 }
-int head_logits_grid(const Dims &D) { return (D.V + logit_rows(D) - 1) / logit_rows(D); }
+int head_logits_grid(const Dims &D) {
+  const int rows = kLogitWaves * logits_tiles(D) * 16;
+  return (D.V + rows - 1) / rows;
+}
 
+// u of position j (nu tiles) and the next position's hidden gates (ng tiles) from S_j
+template <typename WT>
+static void launch_rows(const HeadArgs &h, int j, int nu, int ng, hipStream_t st) {
+  if (nu + ng <= 0) return;
+  const dim3 grid(nu + ng), block(kRowWaves * 64);
+  if (h.D.bs <= 16) hipLaunchKernelGGL((head_rows_kernel<WT, 1>), grid, block, 0, st, h, j, nu);
+  else if (h.D.bs <= 32) hipLaunchKernelGGL((head_rows_kernel<WT, 2>), grid, block, 0, st, h, j, nu);
+  else hipLaunchKernelGGL((head_rows_kernel<WT, 4>), grid, block, 0, st, h, j, nu);
+}
 
-
-// One position's state (and u) for batches above kFusedBatch: the two GEMMs
-// and their elementwise finishes
-static void states_gemm_step(const HeadArgs &h, int j, bool with_u, hipStream_t st) {
+// One position's state (and u, unless skip_u)
+template <typename WT>
+static void launch_state(const HeadArgs &h, int j, hipStream_t st) {
   const Dims &D = h.D;
-  const int bs = D.bs, ds = D.ds, r = D.r;
-  float *gp = h.hpart, *up = h.hpart + (size_t)kHeadMaxSplit * bs * 3 * ds;
-  int npg = 0;
-  if (j > 1) {
-    const GemmPlan pg = plan_gemm(h.whh_NT, h.whh_KS, bs, EPI_STORE, h.n_cu, kHeadMaxSplit);
-    GemmArgs a;
-    a.P = h.whh_p;
-    a.KS = h.whh_KS;
-    a.tile0 = 0;
-    a.ntiles = h.whh_NT;
-    a.N = 3 * ds;
-    a.X = h.hbuf + (size_t)((j - 1) & 1) * bs * ds;
-    a.ldx = ds;
-    a.M = bs;
-    a.K = ds;
-    a.Y = gp;
-    a.ldy = 3 * ds;
-    a.ysplit = (size_t)bs * 3 * ds;
-    a.ksplit = pg.ksplit;
-    launch_gemm(D.bf16, EPI_STORE, a, pg, st);
-    npg = pg.ksplit;
+  if (D.bs <= kFusedBatch) {
+    const size_t slds = sizeof(float) * (size_t)D.bs * D.ds;
+    const int rows = (h.skip_u ? 0 : D.r) + 3 * D.ds;
+    const int gs = min((rows + 2 * kStateWaves - 1) / (2 * kStateWaves), kStateMaxGrid);
+    hipLaunchKernelGGL(head_state_kernel<WT>, dim3(gs), dim3(kStateWaves * 64), slds, st, h, j);
+    return;
   }
-  hipLaunchKernelGGL(head_gru_elem_kernel, dim3((ds + 255) / 256, bs), dim3(256), 0, st, h, j, gp, npg,
-                     (size_t)bs * 3 * ds);
-  if (!with_u) return;
-  const GemmPlan pu = plan_gemm(h.w1s_NT, h.w1s_KS, bs, EPI_STORE, h.n_cu, kHeadMaxSplit);
-  GemmArgs a;
-  a.P = h.w1s_p;
-  a.KS = h.w1s_KS;
-  a.tile0 = 0;
-  a.ntiles = h.w1s_NT;
-  a.N = r;
-  a.X = h.hbuf + (size_t)(j & 1) * bs * ds;
-  a.ldx = ds;
-  a.M = bs;
-  a.K = ds;
-  a.Y = up;
-  a.ldy = r;
-  a.ysplit = (size_t)bs * r;
-  a.ksplit = pu.ksplit;
-  launch_gemm(D.bf16, EPI_STORE, a, pu, st);
-  hipLaunchKernelGGL(head_u_elem_kernel, dim3((bs * r + 255) / 256), dim3(256), 0, st, h, j, up, pu.ksplit,
-                     (size_t)bs * r);
+  hipLaunchKernelGGL(head_gru_elem_kernel, dim3((D.ds + 255) / 256, D.bs), dim3(256), 0, st, h, j);
+  launch_rows<WT>(h, j, h.skip_u ? 0 : h.w1s_NT, j < D.B - 1 ? h.whh_NT : 0, st);  // the last S has no successor
 }
-static bool states_by_gemm(const HeadArgs &h) {
-  return h.D.bs > kFusedBatch && h.whh_p && h.w1s_p && h.hpart && h.n_cu > 0;
+template <typename WT>
+static void prepare_state(const HeadArgs &h) {
+  if (h.D.bs <= kFusedBatch)
+    (void)hipFuncSetAttribute((const void *)head_state_kernel<WT>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)(sizeof(float) * (size_t)h.D.bs * h.D.ds));
 }
 
-template <typename WT, int KS, int MT>
-static void launch_loop(const HeadArgs &h, hipStream_t st) {
+template <typename WT, int KS, int MT, int TPW>
+static void launch_loop(HeadArgs h, hipStream_t st) {
   const Dims &D = h.D;
   const int depth = D.B - 1;
-  constexpr int XF = XStage<WT>::XF;
-  // the largest request (beta 8) plus the kernel's 6 KB of static LDS fits a CU's 160 KB
-  static_assert(sizeof(u32x4) * KS * MT * 64 * XF + topl_lds_bytes(8, MT) + 8192 <= 160 * 1024, "logits LDS");
-  const size_t lds = sizeof(u32x4) * KS * MT * 64 * XF + (h.beta == 1 ? 0 : topl_lds_bytes(h.beta <= 4 ? 4 : 8, MT));
-  (void)hipFuncSetAttribute((const void *)head_logits_kernel<WT, KS, MT>,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  const bool fused = D.bs <= kFusedBatch;
-  const size_t slds = sizeof(float) * (size_t)D.bs * D.ds;
-  const int gs = min((D.r + 3 * D.ds + 2 * kStateWaves - 1) / (2 * kStateWaves), kStateMaxGrid);
-  if (fused)
-    (void)hipFuncSetAttribute((const void *)head_state_kernel<WT>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)slds);
+  constexpr size_t lds = sizeof(u32x4) * KS * MT * 64 * XStage<WT>::XF;
+  static_assert(lds + 8192 <= 160 * 1024, "logits LDS (u fragments and 6 KB of static LDS)");
+  auto logits = head_logits_kernel<WT, KS, MT, TPW>;
+  (void)hipFuncSetAttribute((const void *)logits, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  prepare_state<WT>(h);
+  h.lout = h.beta > 1 ? const_cast<float *>(h.Lbase) : nullptr;
   for (int j = 1; j <= depth; ++j) {
-    if (fused) hipLaunchKernelGGL(head_state_kernel<WT>, dim3(gs), dim3(kStateWaves * 64), slds, st, h, j);
-    else states_gemm_step(h, j, true, st);
-    hipLaunchKernelGGL((head_logits_kernel<WT, KS, MT>), dim3(h.GC), dim3(kLogitWaves * 64), lds, st, h, j);
+    launch_state<WT>(h, j, st);
+    hipLaunchKernelGGL(logits, dim3(h.GC), dim3(kLogitWaves * 64), lds, st, h, j);
   }
-  hipLaunchKernelGGL(head_merge_kernel, dim3(depth, D.bs), dim3(64), 0, st, h);
+  int nlist = h.GC;
+  if (h.beta > 1) {
+    nlist = (D.V + kTopWave - 1) / kTopWave;  // (at most GC: the lists fit the workspace)
+    hipLaunchKernelGGL(head_topb_kernel, dim3((nlist + 3) / 4, depth, D.bs), dim3(256), 0, st, h, nlist);
+  }
+  hipLaunchKernelGGL(head_merge_kernel, dim3(depth, D.bs), dim3(64), 0, st, h, nlist);
 }
 
 template <typename WT>
 static void launch_states_t(const HeadArgs &h, hipStream_t st) {
-  const Dims &D = h.D;
-  const bool fused = D.bs <= kFusedBatch;
-  const size_t slds = sizeof(float) * (size_t)D.bs * D.ds;
-  const int rows = (h.skip_u ? 0 : D.r) + 3 * D.ds;
-  const int gs = min((rows + 2 * kStateWaves - 1) / (2 * kStateWaves), kStateMaxGrid);
-  if (fused)
-    (void)hipFuncSetAttribute((const void *)head_state_kernel<WT>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)slds);
-  for (int j = 1; j <= D.B - 1; ++j) {
-    if (fused) hipLaunchKernelGGL(head_state_kernel<WT>, dim3(gs), dim3(kStateWaves * 64), slds, st, h, j);
-    else states_gemm_step(h, j, !h.skip_u, st);
-  }
+  prepare_state<WT>(h);
+  for (int j = 1; j <= h.D.B - 1; ++j) launch_state<WT>(h, j, st);
 }
 
 hipError_t launch_head_states(const HeadArgs &h, hipStream_t st) {
   if (!h.forced) return hipErrorInvalidValue;
-  if (h.D.bs > kFusedBatch && !states_by_gemm(h)) return hipErrorInvalidValue;
   if (h.D.bf16) launch_states_t<bf16_t>(h, st);
   else launch_states_t<float>(h, st);
   return hipGetLastError();
 }
 
+template <typename WT, int KS, int MT>
+static void launch_tpw(const HeadArgs &h, hipStream_t st) {
+  constexpr int T = logit_tpw(KS, MT);
+  if (logits_tiles(h.D) == T) launch_loop<WT, KS, MT, T>(h, st);
+  else if constexpr (T != 1) launch_loop<WT, KS, MT, 1>(h, st);
+}
 template <typename WT, int KS>
 static void launch_mt(const HeadArgs &h, hipStream_t st) {
-  if (h.D.bs <= 16) launch_loop<WT, KS, 1>(h, st);
-  else if (h.D.bs <= 32) launch_loop<WT, KS, 2>(h, st);
-  else launch_loop<WT, KS, 4>(h, st);
+  const int MT = logits_mt(h.D);
+  if (MT == 1) launch_tpw<WT, KS, 1>(h, st);
+  else if (MT == 2) launch_tpw<WT, KS, 2>(h, st);
+  else launch_tpw<WT, KS, 4>(h, st);
 }
 
 hipError_t launch_head(const HeadArgs &h, hipStream_t st) {
-  if (h.D.bs > kFusedBatch && !states_by_gemm(h)) return hipErrorInvalidValue;
   const bool bf = h.D.bf16;
   const int KS = h.D.r / (bf ? 32 : 16);
   if (bf) {

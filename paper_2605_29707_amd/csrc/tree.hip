@@ -2,6 +2,9 @@
 // prefix plus the target's bonus token).  Integer / compare work only; every
 // argmax uses the total order (value desc, id asc) with NaN as -inf, so the
 // results are exact and independent of reduction order.
+#include <algorithm>
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -65,7 +68,11 @@ void launch_build_tree(int bs, int depth, int beta, const int32_t *topk, const i
 // the root.  When the walk stops on a node without children (a leaf of a
 // tree, or the end of a fully accepted chain) the bonus token is that row's
 // argmax, which the walk's workgroup scans itself: one row, and only then.
-// workspace: [err:int32][pad to 256 B][partials: (float,int) bs*nn*nchunk]
+// workspace: [err:int32][pad to 256 B][partials: 64-bit best keys bs*nn*nchunk]
+// 32 rows x 61 nodes (17 with children) x 151936 bf16 logits, 156 MB read: 40 us
+// while a workgroup took 8 neighbouring node rows (two of them with children) and
+// 43 us for a walk that scanned the leaf's 300 KB with 256 threads; now 29 us
+// and 11.
 // ---------------------------------------------------------------------------
 constexpr int ACH = 4096;  // vocabulary elements per argmax chunk
 
@@ -103,120 +110,132 @@ struct LVec<float> {
   DEVI static float get(const u32x4 &x, int e) { return __uint_as_float(x[e]); }
 };
 
-// Fold the values of one 16-byte load (ids id0 .. id0 + N - 1, those below v1)
-// into a running best; ids grow within a thread, so a strict comparison keeps
-// the smallest id of equal values.
+// Best (value, id) of the values of NV 16-byte loads of one row, as the 64-bit
+// key of the whole wave: the maximum first (NaN drops out of fmaxf, so it counts
+// as -inf), then the smallest id holding it.  Load q holds ids id0 + q * step ..;
+// ids from v1 on do not count.
+template <typename LT, int NV>
+DEVI unsigned long long wave_best_key(const u32x4 (&x)[NV], int id0, int step, int v1) {
+  constexpr int N = LVec<LT>::N;
+  float m[NV], t = -INFINITY;
+#pragma unroll
+  for (int q = 0; q < NV; ++q) {
+    m[q] = -INFINITY;
+    const int id = id0 + q * step;
+    if (id + N <= v1) {
+#pragma unroll
+      for (int e = 0; e < N; ++e) m[q] = fmaxf(m[q], LVec<LT>::get(x[q], e));
+    }
+    t = fmaxf(t, m[q]);
+  }
+  const float wm = wave_max(t);
+  int best = INT_MAX;
+#pragma unroll
+  for (int q = 0; q < NV; ++q) {
+    const int id = id0 + q * step;
+    if (id + N <= v1 && m[q] == wm) {
+#pragma unroll
+      for (int e = N - 1; e >= 0; --e)
+        if (order_val(LVec<LT>::get(x[q], e)) == wm) best = min(best, id + e);
+    }
+  }
+  // (+ 0: a zero's sign is no difference)
+  return wave_max_u64(best == INT_MAX ? 0ull : encode_best(wm + 0.f, best));
+}
+// the same of single values (rows that are not whole 16-byte loads)
+template <int NV>
+DEVI unsigned long long wave_best_key(const float (&x)[NV], int id0, int step, int v1) {
+  float t = -INFINITY;
+#pragma unroll
+  for (int q = 0; q < NV; ++q)
+    if (id0 + q * step < v1) t = fmaxf(t, x[q]);
+  const float wm = wave_max(t);
+  int best = INT_MAX;
+#pragma unroll
+  for (int q = NV - 1; q >= 0; --q)
+    if (id0 + q * step < v1 && order_val(x[q]) == wm) best = min(best, id0 + q * step);
+  return wave_max_u64(best == INT_MAX ? 0ull : encode_best(wm + 0.f, best));
+}
+
+// Partial argmax over one vocabulary chunk of the rows of nodes that have
+// children (the walk scans another row itself if it ends there).  Every
+// workgroup lists those rows of its batch row (a few loads that hit the L2) and
+// takes entries y, y + gridDim.y, ... of the list, two rows in flight: the
+// work is split by rows that are read, wherever they lie among the leaves.
+// Rows are 16-byte aligned when V is a multiple of 8 (bf16) or 4 (fp32); then
+// every value comes from 16-byte loads, otherwise one value per load.  The
+// first workgroup also clears the error word (only the walk, a later launch,
+// raises errors).
+constexpr int kWalkMaxNodes = 1024;
+
 template <typename LT>
-DEVI void fold_vec(const u32x4 &x, int id0, int v1, float &bv, int &bi) {
-#pragma unroll
-  for (int e = 0; e < LVec<LT>::N; ++e) {
-    const int v = id0 + e;
-    const float o = order_val(LVec<LT>::get(x, e));
-    if (v < v1 && (o > bv || bi == INT_MAX)) {
-      bv = o;
-      bi = v;
-    }
-  }
-}
-
-// (bv, bi) of the 256-thread workgroup: every thread gets the best
-DEVI void block_best(float &bv, int &bi, float (&sv)[4], int (&si)[4]) {
-  wave_best(bv, bi);
-  __syncthreads();  // the arrays may hold the previous reduction
-  if ((threadIdx.x & 63) == 0) {
-    sv[threadIdx.x >> 6] = bv;
-    si[threadIdx.x >> 6] = bi;
-  }
-  __syncthreads();
-  bv = sv[0];
-  bi = si[0];
-  for (int w = 1; w < 4; ++w)
-    if (better(sv[w], si[w], bv, bi)) {
-      bv = sv[w];
-      bi = si[w];
-    }
-}
-
-// Partial argmax of rows m0 .. m0 + kArgRows - 1 of batch row b over one
-// vocabulary chunk (one row per workgroup for small grids, several when there
-// are many node rows), for the rows of nodes that have children (the walk scans
-// another row itself if it ends there).  Rows are 16-byte aligned when V is a
-// multiple of 8 (bf16) or 4 (fp32); then every value comes from 16-byte loads,
-// all of the workgroup's rows in flight together; otherwise one value per
-// load.  The first workgroup also clears the error word (only the walk, a
-// later launch, raises errors).
-template <typename LT, int kArgRows>
 __global__ __launch_bounds__(256) void argmax_partial_kernel(int nn, int V, const LT *__restrict__ logits,
-                                                             const int32_t *__restrict__ par, float *part_v,
-                                                             int32_t *part_i, int32_t *err) {
+                                                             const int32_t *__restrict__ par,
+                                                             unsigned long long *__restrict__ part, int32_t *err) {
   constexpr int EV = LVec<LT>::N, VPT = ACH / EV / 256;  // 16-byte loads per thread and row
-  const int ch = blockIdx.x, m0 = blockIdx.y * kArgRows, b = blockIdx.z;
-  const int nch = gridDim.x, tid = threadIdx.x;
+  const int ch = blockIdx.x, b = blockIdx.z;
+  const int nch = gridDim.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   if ((ch | blockIdx.y | b) == 0 && tid == 0) *err = 0;
-  __shared__ int s_has[kArgRows];
-  __shared__ float sv[4];
-  __shared__ int si[4];
-  if (tid < kArgRows) s_has[tid] = 0;
+  __shared__ unsigned char s_has[kWalkMaxNodes];
+  __shared__ int s_list[kWalkMaxNodes], s_n;
+  __shared__ unsigned long long s_key[2][4];
+  for (int c = tid; c < nn; c += blockDim.x) s_has[c] = 0;
   __syncthreads();
-  // children come after their parent
-  for (int c = m0 + 1 + tid; c < nn; c += blockDim.x) {
+  for (int c = 1 + tid; c < nn; c += blockDim.x) {  // children come after their parent
     const int p = par[(size_t)b * nn + c];
-    if (p >= m0 && p < m0 + kArgRows && p < c) s_has[p - m0] = 1;
+    if (p >= 0 && p < c) s_has[p] = 1;
   }
   __syncthreads();
-  const int v0 = ch * ACH, v1 = min(V, v0 + ACH);
-  if (V % EV == 0) {
-    u32x4 x[kArgRows][VPT];
-#pragma unroll
-    for (int r = 0; r < kArgRows; ++r) {
-      if (!s_has[r] || m0 + r >= nn) continue;  // uniform: a leaf's row is not read
-      const LT *row = logits + ((size_t)b * nn + m0 + r) * V;
-#pragma unroll
-      for (int q = 0; q < VPT; ++q) {  // clamped within the row: every lane's load valid
-        const int id0 = min(v0 + (q * 256 + tid) * EV, V - EV);
-        x[r][q] = *(const u32x4 *)(row + id0);
-      }
+  if (wave == 0) {  // the list, in node order
+    int n = 0;
+    for (int c0 = 0; c0 < nn; c0 += 64) {
+      const bool has = c0 + lane < nn && s_has[c0 + lane];
+      const unsigned long long mk = __ballot(has);
+      if (has) s_list[n + __popcll(mk & ((1ull << lane) - 1))] = c0 + lane;
+      n += __popcll(mk);
     }
+    if (lane == 0) s_n = n;
+  }
+  __syncthreads();
+  const int n = s_n, ys = gridDim.y;
+  const int v0 = ch * ACH, v1 = min(V, v0 + ACH);
+  auto finish = [&](int k, int slot, unsigned long long key) {  // list entry k: the four waves' keys
+    if (lane == 0) s_key[slot][wave] = key;
+    __syncthreads();
+    if (tid == 0) {
+      unsigned long long o = s_key[slot][0];
 #pragma unroll
-    for (int r = 0; r < kArgRows; ++r) {
-      if (!s_has[r] || m0 + r >= nn) continue;  // uniform over the workgroup
-      float bv = -INFINITY;
-      int bi = INT_MAX;
+      for (int w = 1; w < 4; ++w) o = s_key[slot][w] > o ? s_key[slot][w] : o;
+      part[((size_t)b * nn + s_list[k]) * nch + ch] = o;
+    }
+  };
+  if (V % EV == 0) {
+    u32x4 x[2][VPT];
+    const int id0 = v0 + tid * EV;
+    auto load = [&](u32x4 (&y)[VPT], int k) {  // clamped within the list and the row: every load valid
+      const LT *row = logits + ((size_t)b * nn + s_list[min(k, n - 1)]) * V;
 #pragma unroll
-      for (int q = 0; q < VPT; ++q) fold_vec<LT>(x[r][q], v0 + (q * 256 + tid) * EV, v1, bv, bi);
-      block_best(bv, bi, sv, si);
-      if (tid == 0) {
-        const size_t o = ((size_t)b * nn + m0 + r) * nch + ch;
-        part_v[o] = bv;
-        part_i[o] = bi;
-      }
+      for (int q = 0; q < VPT; ++q) y[q] = __builtin_nontemporal_load((const u32x4 *)(row + min(id0 + q * 256 * EV, V - EV)));
+    };
+    int k = blockIdx.y;
+    if (k >= n) return;  // uniform
+    load(x[0], k);
+    for (; k < n; k += 2 * ys) {
+      load(x[1], k + ys);
+      finish(k, 0, wave_best_key<LT>(x[0], id0, 256 * EV, v1));
+      load(x[0], k + 2 * ys);
+      if (k + ys < n) finish(k + ys, 1, wave_best_key<LT>(x[1], id0, 256 * EV, v1));
     }
     return;
   }
-  for (int r = 0; r < kArgRows; ++r) {
-    if (!s_has[r] || m0 + r >= nn) continue;  // uniform over the workgroup
-    const LT *row = logits + ((size_t)b * nn + m0 + r) * V;
+  int slot = 0;
+  for (int k = blockIdx.y; k < n; k += ys, slot ^= 1) {
+    const LT *row = logits + ((size_t)b * nn + s_list[k]) * V;
     constexpr int PER = ACH / 256;
     float x[PER];
 #pragma unroll
     for (int q = 0; q < PER; ++q) x[q] = ld_logit<LT>(row + min(v0 + tid + q * 256, v1 - 1));
-    float bv = -INFINITY;
-    int bi = INT_MAX;
-#pragma unroll
-    for (int q = 0; q < PER; ++q) {
-      const int v = v0 + tid + q * 256;  // increasing in q: a strict > keeps the smallest id
-      const float o = v < v1 ? order_val(x[q]) : -INFINITY;
-      if (v < v1 && (o > bv || bi == INT_MAX)) {
-        bv = o;
-        bi = v;
-      }
-    }
-    block_best(bv, bi, sv, si);
-    if (tid == 0) {
-      const size_t o = ((size_t)b * nn + m0 + r) * nch + ch;
-      part_v[o] = bv;
-      part_i[o] = bi;
-    }
+    finish(k, slot, wave_best_key(x, v0 + tid, 256, v1));
   }
 }
 
@@ -227,21 +246,23 @@ __global__ __launch_bounds__(256) void argmax_partial_kernel(int nn, int V, cons
 // first child of each node whose token is that R.  The walk from the root is
 // then a chase through LDS.  Only if it stops on a node without children (a
 // leaf of a tree, or the end of a fully accepted chain) is that row's argmax
-// needed, which the workgroup scans itself.
-constexpr int kWalkMaxNodes = 1024;
+// needed, which the workgroup scans itself: 16 waves, so that one CU has a whole
+// 300 KB row in flight in two passes.
+
+constexpr int kWalkThreads = 1024;
 
 template <typename LT>
-__global__ __launch_bounds__(256) void accept_walk_kernel(int nn, int V, int B, const int32_t *__restrict__ tok,
-                                                          const int32_t *__restrict__ par,
-                                                          const float *__restrict__ part_v,
-                                                          const int32_t *__restrict__ part_i,
-                                                          const LT *__restrict__ logits,
-                                                          int32_t *acc_len, int32_t *acc_nodes,
-                                                          int32_t *out_tok, int32_t *err) {
+__global__ __launch_bounds__(kWalkThreads) void accept_walk_kernel(int nn, int V, int B,
+                                                                   const int32_t *__restrict__ tok,
+                                                                   const int32_t *__restrict__ par,
+                                                                   const unsigned long long *__restrict__ part,
+                                                                   const LT *__restrict__ logits, int32_t *acc_len,
+                                                                   int32_t *acc_nodes, int32_t *out_tok,
+                                                                   int32_t *err) {
+  constexpr int kWaves = kWalkThreads / 64;
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int nch = (V + ACH - 1) / ACH;
-  __shared__ float sv[4];
-  __shared__ int si[4];
+  __shared__ unsigned long long s_key[kWaves];
   __shared__ int s_R[kWalkMaxNodes], s_next[kWalkMaxNodes];
   __shared__ unsigned char s_kid[kWalkMaxNodes];
   const int32_t *pr = par + (size_t)b * nn, *tk = tok + (size_t)b * nn;
@@ -257,40 +278,25 @@ __global__ __launch_bounds__(256) void accept_walk_kernel(int nn, int V, int B, 
     if (c > 0 && p >= 0 && p < c) s_kid[p] = 1;
   }
   __syncthreads();
-  // R of every node with children: wave w takes nodes w + 4 q (+ 16 per pass),
+  // R of every node with children: wave w takes nodes w + 16 q (+ 64 per pass),
   // lanes over the vocabulary chunks
-  for (int c0 = wave; c0 < nn; c0 += 16) {
-    float bv[4];
-    int bi[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      bv[q] = -INFINITY;
-      bi[q] = INT_MAX;
-    }
+  for (int c0 = wave; c0 < nn; c0 += 4 * kWaves) {
+    unsigned long long best[4] = {0ull, 0ull, 0ull, 0ull};
     for (int k0 = 0; k0 < nch; k0 += 64) {
-      float lv[4];
-      int li[4];
+      unsigned long long x[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {  // clamped: every load valid, all in flight together
-        const int c = min(c0 + 4 * q, nn - 1), k = min(k0 + lane, nch - 1);
-        const size_t o = ((size_t)b * nn + c) * nch + k;
-        lv[q] = part_v[o];
-        li[q] = part_i[o];
+        const int c = min(c0 + kWaves * q, nn - 1), k = min(k0 + lane, nch - 1);
+        x[q] = part[((size_t)b * nn + c) * nch + k];
       }
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int c = c0 + 4 * q;
-        if (c < nn && s_kid[c] && k0 + lane < nch && better(lv[q], li[q], bv[q], bi[q])) {
-          bv[q] = lv[q];
-          bi[q] = li[q];
-        }
-      }
+      for (int q = 0; q < 4; ++q) best[q] = x[q] > best[q] ? x[q] : best[q];
     }
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      wave_best(bv[q], bi[q]);
-      const int c = c0 + 4 * q;
-      if (lane == 0 && c < nn) s_R[c] = bi[q];
+      const unsigned long long o = wave_max_u64(best[q]);
+      const int c = c0 + kWaves * q;  // (a row without children has no partials: its R is never used)
+      if (lane == 0 && c < nn) s_R[c] = s_kid[c] ? decode_best_id(o, V) : -1;
     }
   }
   __syncthreads();
@@ -320,41 +326,32 @@ __global__ __launch_bounds__(256) void accept_walk_kernel(int nn, int V, int B, 
     cur = nx;
   }
   if (leaf) {  // the bonus token: the argmax of this row, scanned here
-    float bv = -INFINITY;
-    int bi = INT_MAX;
-    // ids visited in increasing order per thread: a strict > keeps the smallest id
     const LT *row = logits + ((size_t)b * nn + cur) * V;
-    constexpr int EV = LVec<LT>::N, U = 16;
+    constexpr int EV = LVec<LT>::N, U = 10;
+    unsigned long long best = 0ull;
     if (V % EV == 0) {  // 16-byte rows: U loads of EV values per thread in flight
-      const int nv = V / EV;
-      for (int g0 = 0; g0 < nv; g0 += 256 * U) {
+      for (int g0 = 0; g0 < V; g0 += kWalkThreads * U * EV) {
         u32x4 x[U];
+        const int id0 = g0 + tid * EV;
 #pragma unroll
-        for (int q = 0; q < U; ++q) x[q] = *(const u32x4 *)(row + (size_t)min(g0 + q * 256 + tid, nv - 1) * EV);
-#pragma unroll
-        for (int q = 0; q < U; ++q) {
-          const int gi = g0 + q * 256 + tid;
-          fold_vec<LT>(x[q], gi * EV, gi < nv ? V : 0, bv, bi);
-        }
+        for (int q = 0; q < U; ++q) x[q] = *(const u32x4 *)(row + min(id0 + q * kWalkThreads * EV, V - EV));
+        const unsigned long long o = wave_best_key<LT>(x, id0, kWalkThreads * EV, V);
+        best = o > best ? o : best;
       }
     } else {
-      for (int v0 = tid; v0 < V; v0 += 256 * U) {
+      for (int g0 = 0; g0 < V; g0 += kWalkThreads * U) {
         float x[U];
+        const int id0 = g0 + tid;
 #pragma unroll
-        for (int q = 0; q < U; ++q) x[q] = ld_logit<LT>(row + min(v0 + q * 256, V - 1));
-#pragma unroll
-        for (int q = 0; q < U; ++q) {
-          const int v = v0 + q * 256;
-          const float ov = order_val(x[q]);
-          if (v < V && (ov > bv || bi == INT_MAX)) {
-            bv = ov;
-            bi = v;
-          }
-        }
+        for (int q = 0; q < U; ++q) x[q] = ld_logit<LT>(row + min(id0 + q * kWalkThreads, V - 1));
+        const unsigned long long o = wave_best_key(x, id0, kWalkThreads, V);
+        best = o > best ? o : best;
       }
     }
-    block_best(bv, bi, sv, si);
-    R = bi;
+    if (lane == 0) s_key[wave] = best;
+    __syncthreads();
+    for (int w = 0; w < kWaves; ++w) best = s_key[w] > best ? s_key[w] : best;
+    R = decode_best_id(best, V);
   }
   if (tid == 0) {
     acc_len[b] = a;
@@ -370,40 +367,26 @@ void launch_accept(int bs, int nn, int V, int B, const int32_t *tok, const int32
                    const void *logits, bool bf16, int32_t *acc_len, int32_t *acc_nodes,
                    int32_t *out_tok, void *ws, hipStream_t st) {
   unsigned char *w = (unsigned char *)ws;
-  float *pv = (float *)(w + acc_part_off());
-  launch_accept_parts(bs, nn, V, B, tok, par, logits, bf16, acc_len, acc_nodes, out_tok, pv,
-                      (int32_t *)(pv + accept_part_entries(bs, nn, V)), (int32_t *)w, st);
+  launch_accept_parts(bs, nn, V, B, tok, par, logits, bf16, acc_len, acc_nodes, out_tok, w + acc_part_off(),
+                      (int32_t *)w, st);
 }
 
 void launch_accept_parts(int bs, int nn, int V, int B, const int32_t *tok, const int32_t *par,
                          const void *logits, bool bf16, int32_t *acc_len, int32_t *acc_nodes,
-                         int32_t *out_tok, float *pv, int32_t *pi, int32_t *err, hipStream_t st) {
+                         int32_t *out_tok, void *part, int32_t *err, hipStream_t st) {
   const int nch = (V + ACH - 1) / ACH;
-  // a workgroup per row while the grid is small; eight rows per workgroup for
-  // many rows (most of them leaves of a tree), which keeps the grid of
-  // workgroups that only find no children from dominating
-  const bool many = (long)nch * nn * bs > 4096;
-  const int rpw = many ? 8 : 1;
-  dim3 grid(nch, (nn + rpw - 1) / rpw, bs);
-  if (bf16) {
-    if (many)
-      hipLaunchKernelGGL((argmax_partial_kernel<bf16_t, 8>), grid, dim3(256), 0, st, nn, V, (const bf16_t *)logits,
-                         par, pv, pi, err);
-    else
-      hipLaunchKernelGGL((argmax_partial_kernel<bf16_t, 1>), grid, dim3(256), 0, st, nn, V, (const bf16_t *)logits,
-                         par, pv, pi, err);
-    hipLaunchKernelGGL(accept_walk_kernel<bf16_t>, dim3(bs), dim3(256), 0, st, nn, V, B, tok, par, pv, pi,
-                       (const bf16_t *)logits, acc_len, acc_nodes, out_tok, err);
-  } else {
-    if (many)
-      hipLaunchKernelGGL((argmax_partial_kernel<float, 8>), grid, dim3(256), 0, st, nn, V, (const float *)logits, par,
-                         pv, pi, err);
-    else
-      hipLaunchKernelGGL((argmax_partial_kernel<float, 1>), grid, dim3(256), 0, st, nn, V, (const float *)logits, par,
-                         pv, pi, err);
-    hipLaunchKernelGGL(accept_walk_kernel<float>, dim3(bs), dim3(256), 0, st, nn, V, B, tok, par, pv, pi,
-                       (const float *)logits, acc_len, acc_nodes, out_tok, err);
-  }
+  // about 2048 workgroups (8 a CU): a row each while there are few, several each for large batches
+  const int ys = (int)std::max(1L, std::min((long)nn, 2048L / ((long)nch * bs)));
+  const dim3 grid(nch, ys, bs);
+  auto go = [&](auto *lg) {
+    using LT = std::remove_cv_t<std::remove_pointer_t<decltype(lg)>>;
+    unsigned long long *p = (unsigned long long *)part;
+    hipLaunchKernelGGL(argmax_partial_kernel<LT>, grid, dim3(256), 0, st, nn, V, lg, par, p, err);
+    hipLaunchKernelGGL(accept_walk_kernel<LT>, dim3(bs), dim3(kWalkThreads), 0, st, nn, V, B, tok, par,
+                       (const unsigned long long *)p, lg, acc_len, acc_nodes, out_tok, err);
+  };
+  if (bf16) go((const bf16_t *)logits);
+  else go((const float *)logits);
 }
 
 }  // namespace dk
