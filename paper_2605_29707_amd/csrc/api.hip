@@ -139,11 +139,9 @@ Dims make_dims(const domino_model *m, int bs) {
 
 // ---- workspace layout of the draft step
 struct WsLayout {
-  size_t err, best, slots, hdr_words, X, X2, A, FC, QKV, Q, Kb, Vb, attn, O, WOp, F, DNp, H, LP, hbuf, ghbuf, ubuf, pval, pid,
+  size_t err, best, slots, hdr_words, X, X2, A, A2, FC, QKV, Q, Kb, Vb, attn, O, WOp, F, DNp, H, LP, hbuf, ghbuf, ubuf, pval, pid,
       praw, XF, total;
-  // residual-epilogue tickets (in the cleared header) and row sums of squares
-  // of the deferred RMSNorms; 0: this layout has none
-  size_t tickets = 0, SSQ = 0;
+  size_t SSQ = 0;  // row sums of squares of the deferred RMSNorms
   int GC, ldl;
 };
 
@@ -155,27 +153,32 @@ struct Plans {
 
 constexpr int kMaxSplit = 16;
 
-// bf16 projections of more than kSkinnyMaxRows rows (K a multiple of 32, as
-// the config checks make every K here) run the wide-activation kernel;
-// everything else the skinny weight-streaming kernel
+// A layer's projection: fragment-plane kernels for bf16 weights (K a multiple of
+// 32, as the config checks make every K here), the skinny one for fp32
+GemmPlan plan_layer(const domino_model *m, const Packed &pk, int M, int epi, int max_split) {
+  if (!m->bf16) return plan_gemm(pk.NT, pk.KS, M, epi, m->n_cu, max_split);
+  if (M <= kRowsMax) return plan_gemm_rows(pk.NT, pk.KS, M, epi, m->n_cu, max_split);
+  return plan_gemm_wide(pk.NT, pk.KS, M, epi, m->n_cu, max_split);
+}
+// The other GEMMs, whose input is fp32 rows
 GemmPlan plan_proj(const domino_model *m, const Packed &pk, int M, int epi, int max_split) {
   if (m->bf16 && M > kSkinnyMaxRows) return plan_gemm_wide(pk.NT, pk.KS, M, epi, m->n_cu, max_split);
   return plan_gemm(pk.NT, pk.KS, M, epi, m->n_cu, max_split);
 }
-// false when a wide plan's arguments were refused (nothing launched)
+// false when a plan's arguments were refused (nothing launched)
 bool launch_proj(const domino_model *m, int epi, const GemmArgs &a, const GemmPlan &p, hipStream_t st) {
+  if (p.rows) return launch_gemm_rows(epi, a, p, st);
   if (p.wide) return launch_gemm_wide(epi, a, p, st);  // a.K == a.KS * 32, a.xf set
   launch_gemm(m->bf16, epi, a, p, st);
   return true;
 }
 
-// Fragment scratch of the wide projections of a layout: the most rows any of
-// them has times the widest K among them (0 when every plan is skinny)
+// Scratch for the fragment planes of wide GEMMs over fp32 rows: the context fusion
+// of `rows` appended rows, the training forward's state projection
 size_t wide_scratch(const domino_model *m, const Plans &p, int rows, int train_rows) {
   const Dims &D = m->D;
-  const bool wide = p.qkv.wide || p.wo.wide || p.gateup.wide || p.down.wide || p.lm.wide || p.fc.wide;
-  const int kmax = std::max({D.d, D.nq * D.dh, D.ffn, std::max(m->fuse_k, 1) * D.d, D.ds});
-  size_t b = wide ? gemm_wide_scratch_bytes(rows, kmax) : 0;
+  // (the layers' and the LM head's inputs are planes already)
+  size_t b = p.fc.wide ? gemm_wide_scratch_bytes(rows, m->fuse_k * D.d) : 0;
   if (train_rows > 0 && m->bf16 && train_rows > kSkinnyMaxRows)
     b = std::max(b, gemm_wide_scratch_bytes(train_rows, D.ds));
   return b;
@@ -186,10 +189,11 @@ size_t wide_scratch(const domino_model *m, const Plans &p, int rows, int train_r
 Plans make_plans_rows(const domino_model *m, int M, int Mlm, int Ma) {
   Plans p;
   // projections whose consumer is elementwise write K-split partial outputs
-  p.qkv = plan_proj(m, m->qkv[0], Ma, EPI_STORE, kMaxSplit);
-  p.wo = plan_proj(m, m->wo[0], M, EPI_STORE, kMaxSplit);
-  p.gateup = plan_proj(m, m->gateup[0], M, EPI_SWIGLU, 1);
-  p.down = plan_proj(m, m->down[0], M, EPI_STORE, kMaxSplit);
+  // (the rows kernel's O ends with the residual update)
+  p.qkv = plan_layer(m, m->qkv[0], Ma, EPI_STORE, kMaxSplit);
+  p.wo = plan_layer(m, m->wo[0], M, m->bf16 && M <= kRowsMax ? EPI_RESID : EPI_STORE, kMaxSplit);
+  p.gateup = plan_layer(m, m->gateup[0], M, EPI_SWIGLU, 1);
+  p.down = plan_layer(m, m->down[0], M, EPI_STORE, kMaxSplit);
   p.lm = plan_proj(m, m->lm, Mlm, EPI_STORE, 1);
   if (p.lm.wide && Mlm <= kStreamMaxRows) {
     const GemmPlan s = plan_gemm(m->lm.NT, m->lm.KS, Mlm, EPI_STORE, m->n_cu, 1);
@@ -223,17 +227,17 @@ bool layout(const domino_model *m, int bs, int max_ctx, int max_new, int beta, W
   w.err = take(256);
   w.best = take((size_t)(D.B - 1) * bs * head_best_slots() * 8);
   w.slots = take((size_t)bs * (D.r + w.GC) * 8 * kSlotStride);  // persistent rollout: u and key slots
-  w.tickets = take((size_t)2 * m->cfg.n_layers * kNormGroups * 4);
-  w.hdr_words = o / 4;  // error word (+ rollout abort flag), best keys, slots, tickets: cleared at every step
+  w.hdr_words = o / 4;  // error word (+ rollout abort flag), best keys, slots: cleared at every step
   const int qkvw = (D.nq + 2 * D.nkv) * D.dh;
   w.X = take((size_t)M * D.d * 4);
   w.X2 = take((size_t)M * D.d * 4);
   const int Ma = M + bs * max_new;  // block rows, then the appended context rows
-  // a wide projection's input may be fragment planes (whole row blocks) in the place of fp32 rows
+  // a projection's input may be fragment planes (whole row blocks) in the place of fp32 rows
   auto rows_bytes = [](int rows, int width) {
     return std::max((size_t)rows * width * 4, gemm_wide_scratch_bytes(rows, width));
   };
   w.A = take(rows_bytes(Ma, D.d));
+  w.A2 = m->bf16 ? take(rows_bytes(M, D.d)) : w.A;  // the FFN's input: A's planes keep the appended rows
   w.FC = take((size_t)p.fc.ksplit * bs * max_new * D.d * 4);
   w.QKV = take((size_t)p.qkv.ksplit * Ma * qkvw * 4);
   w.Q = take((size_t)M * D.nq * D.dh * 4);
@@ -244,7 +248,7 @@ bool layout(const domino_model *m, int bs, int max_ctx, int max_new, int beta, W
   w.WOp = take((size_t)p.wo.ksplit * M * D.d * 4);
   w.F = take(rows_bytes(M, D.ffn));
   w.DNp = take((size_t)p.down.ksplit * M * D.d * 4);
-  w.SSQ = take((size_t)kNormGroups * M * 4);
+  w.SSQ = take((size_t)p.wo.groups * M * 4);
   w.H = take(rows_bytes(Mh, D.d));
   w.ldl = m->lm.NT * 16;
   w.LP = take((size_t)Mh * w.ldl * 4);  // [L_base | pad | P] per draft row
@@ -254,7 +258,7 @@ bool layout(const domino_model *m, int bs, int max_ctx, int max_new, int beta, W
   w.pval = take((size_t)(D.B - 1) * bs * w.GC * beta * 4);
   w.pid = take((size_t)(D.B - 1) * bs * w.GC * beta * 4);
   w.praw = take((size_t)(D.B - 1) * bs * w.GC * 4);
-  w.XF = take(wide_scratch(m, p, Ma, bs * (D.B - 1)));  // also the training forward's W1 S-half rows
+  w.XF = take(wide_scratch(m, p, bs * max_new, bs * (D.B - 1)));  // also the training forward's W1 S-half rows
   w.total = o;
   return true;
 }
@@ -302,6 +306,7 @@ bool target_layout(const domino_model *m, int bs, int nn, int max_ctx, TargetLay
     return std::max((size_t)rows * width * 4, gemm_wide_scratch_bytes(rows, width));
   };
   w.A = take(rows_bytes(M, D.d));
+  w.A2 = m->bf16 ? take(rows_bytes(M, D.d)) : w.A;
   w.QKV = take((size_t)p.qkv.ksplit * M * qkvw * 4);
   w.Q = take((size_t)M * D.nq * D.dh * 4);
   w.Kb = take((size_t)M * D.nkv * D.dh * 4);
@@ -311,10 +316,10 @@ bool target_layout(const domino_model *m, int bs, int nn, int max_ctx, TargetLay
   w.WOp = take((size_t)p.wo.ksplit * M * D.d * 4);
   w.F = take(rows_bytes(M, D.ffn));
   w.DNp = take((size_t)p.down.ksplit * M * D.d * 4);
+  w.SSQ = take((size_t)p.wo.groups * M * 4);
   w.H = take(rows_bytes(M, D.d));
   w.ldl = m->lm.NT * 16;
   w.LP = take((size_t)M * w.ldl * 4);
-  w.XF = take(wide_scratch(m, p, M, 0));
   t.tok = take((size_t)M * 4);
   t.pos = take((size_t)M * 4);
   t.mask = take((size_t)bs * t.Bp * t.Bp);
@@ -661,8 +666,13 @@ domino_status run_layers(domino_model_t m, const Dims &D, const Plans &p, const 
                            F(w.FC), D.d, p.fc);
     a.xf = ws + w.XF;
     if (!launch_proj(m, EPI_STORE, a, p.fc, st)) return fail(DOMINO_ERR_UNSUPPORTED, "context fusion projection refused");
-    launch_sum_parts(F(w.FC), p.fc.ksplit, (size_t)rows * D.d, rows, D.d, F(w.A) + (size_t)M * D.d, D.d, st);
+    if (p.qkv.planes())
+      launch_sum_parts_planes(F(w.FC), p.fc.ksplit, (size_t)rows * D.d, rows, D.d, F(w.A), M, (Ma + 15) / 16, st);
+    else
+      launch_sum_parts(F(w.FC), p.fc.ksplit, (size_t)rows * D.d, rows, D.d, F(w.A) + (size_t)M * D.d, D.d, st);
     prof_end(m, DOMINO_KC_CTXPROJ, st);
+  } else if (n_new > 0 && p.qkv.planes()) {
+    launch_sum_parts_planes((const float *)ctx_hidden_new, 1, 0, batch * n_new, D.d, F(w.A), M, (Ma + 15) / 16, st);
   } else if (n_new > 0) {
     hipError_t ce = hipMemcpyAsync(F(w.A) + (size_t)M * D.d, ctx_hidden_new, (size_t)batch * n_new * D.d * 4,
                                    hipMemcpyDeviceToDevice, st);
@@ -670,69 +680,41 @@ domino_status run_layers(domino_model_t m, const Dims &D, const Plans &p, const 
   }
 
   const size_t rstride = (size_t)M * D.d;  // partial-output stride of the residual projections
-  // Every projection of the step.  A wide projection reads fragment planes: its
-  // producer writes them in the place of the fp32 rows (the GEMM then gets no X),
-  // except that QKV's input with appended context rows, which other launches
-  // write, stays fp32 and is split by the projection.
-  const bool fa = p.qkv.wide && n_new == 0, fo = p.wo.wide, fg = p.gateup.wide, ff = p.gateup.wide && p.down.wide,
-             fh = p.lm.wide;
-  auto proj = [&](int epi, GemmArgs a, const GemmPlan &pl, bool planes) {
-    a.xf = planes ? (void *)a.X : (void *)(ws + w.XF);
-    if (planes) a.X = nullptr;
-    return launch_proj(m, epi, a, pl, st);
+  // Every projection of the step.  With bf16 weights its input is fragment
+  // planes, written by its producer in the place of the fp32 rows (the GEMM then
+  // gets no X).  fh: the LM head's, which reads fp32 rows on the skinny kernel.
+  const bool pl = p.qkv.planes(), fh = p.lm.wide;
+  auto proj = [&](int epi, GemmArgs a, const GemmPlan &gp, bool planes) {
+    if (planes) {
+      a.xf = (void *)a.X;
+      a.X = nullptr;
+    }
+    return launch_proj(m, epi, a, gp, st);
   };
   // the residual stream ping-pongs between two buffers: every RMSNorm launch
-  // reads one and writes the updated residual to the other
+  // (and every residual epilogue) reads one and writes the updated residual to the other
   float *xc = F(w.X), *xn = F(w.X2);
-  // Fused norms (one batch row's block on the skinny kernel): the O and down
-  // projections end with the residual update (EPI_RESID), which also leaves the
-  // next RMSNorm's input times its gain in A and the row sums of squares in SSQ;
-  // the gate/up and next QKV projections then scale their output rows by the
-  // norm factor.  Only layer 0's RMSNorm (of the embedding rows) and the final
-  // one remain launches of their own.  The tickets start at zero: layer 0's
-  // RMSNorm clears the header (clear_header), or the caller cleared it before
-  // (the training forward); a layout without tickets never fuses.
-  auto fusable = [](const GemmPlan &pl) { return !pl.wide && pl.pgrid == 0 && pl.WPT == 1 && pl.mgroups == 1; };
-  const bool fuse = w.tickets && w.SSQ && n_new == 0 && m->bf16 && fusable(p.qkv) && fusable(p.wo) &&
-                    fusable(p.gateup) && fusable(p.down) && p.wo.groups <= kNormGroups &&
-                    p.down.groups <= kNormGroups && D.d % 4 == 0;
-  unsigned *tickets = fuse ? (unsigned *)(ws + w.tickets) : nullptr;
-  float *SSQ = fuse ? F(w.SSQ) : nullptr;
-  auto resid = [&](GemmArgs &a, const void *gain, int slot) {
-    a.res_in = xc;
-    a.res_out = xn;
-    a.res_xg = F(w.A);
-    a.res_ssq = SSQ;
-    a.res_gain = gain;
-    a.res_tickets = tickets + (size_t)slot * kNormGroups;
-  };
-  auto deferred = [&](GemmArgs &a, int ng) {
-    a.rs_ssq = SSQ;
-    a.rs_ng = ng;
-    a.rs_d = D.d;
-    a.rs_eps = m->cfg.rms_eps;
-  };
+  // The rows kernel's O ends with the residual update and the FFN RMSNorm's
+  // statistics: gate/up scales its sums by the norm factor, and that RMSNorm is
+  // no launch of its own.
+  const bool fuse = p.wo.rows;
   for (int l = 0; l < m->cfg.n_layers; ++l) {
     const char *ck = (const char *)ctx_k + l * layer_elems * m->esz;
     const char *cv = (const char *)ctx_v + l * layer_elems * m->esz;
     // residual += previous layer's down projection, then the attention RMSNorm
-    // (fused: done by that down projection, except at layer 0)
-    if (l == 0 || !fuse) {
-      prof_begin(m, DOMINO_KC_NORM, st);
-      // (layer 0: the residual starts as the embedding of [anchor, MASK, ...])
-      launch_add_norm(D, xc, xn, D.d, F(w.DNp), l > 0 ? p.down.ksplit : 0, rstride, m->attn_norm[l],
-                      fa ? nullptr : F(w.A), D.d,
-                      M, D.d, false, l == 0 ? m->embed : nullptr, anchor_ids, err, st, spec.tokens,
-                      l == 0 && clear_header ? (uint32_t *)ws : nullptr, (int)w.hdr_words, fa ? F(w.A) : nullptr);
-      std::swap(xc, xn);
-      prof_end(m, DOMINO_KC_NORM, st);
-    }
+    prof_begin(m, DOMINO_KC_NORM, st);
+    // (layer 0: the residual starts as the embedding of [anchor, MASK, ...])
+    launch_add_norm(D, xc, xn, D.d, F(w.DNp), l > 0 ? p.down.ksplit : 0, rstride, m->attn_norm[l],
+                    pl ? nullptr : F(w.A), D.d, M, D.d, false, l == 0 ? m->embed : nullptr, anchor_ids, err, st,
+                    spec.tokens, l == 0 && clear_header ? (uint32_t *)ws : nullptr, (int)w.hdr_words,
+                    pl ? F(w.A) : nullptr, (Ma + 15) / 16);
+    std::swap(xc, xn);
+    prof_end(m, DOMINO_KC_NORM, st);
 
     prof_begin(m, DOMINO_KC_QKV, st);
     GemmArgs a = gemm_args(base + m->qkv[l].off, m->qkv[l], 0, m->qkv[l].NT, qkvw, F(w.A), D.d, Ma, D.d, F(w.QKV),
                            qkvw, p.qkv);
-    if (fuse && l > 0) deferred(a, p.down.groups);
-    if (!proj(EPI_STORE, a, p.qkv, fa)) return fail(DOMINO_ERR_UNSUPPORTED, "qkv projection refused");
+    if (!proj(EPI_STORE, a, p.qkv, pl)) return fail(DOMINO_ERR_UNSUPPORTED, "qkv projection refused");
     prof_end(m, DOMINO_KC_QKV, st);
 
     prof_begin(m, DOMINO_KC_ROPE, st);
@@ -742,46 +724,49 @@ domino_status run_layers(domino_model_t m, const Dims &D, const Plans &p, const 
 
     prof_begin(m, DOMINO_KC_ATTN, st);
     launch_attention(D, F(w.Q), F(w.Kb), F(w.Vb), ck, cv, ctx_lens, max_ctx, F(w.attn), F(w.O), err, st, spec.amask,
-                     fo ? F(w.O) : nullptr);
+                     pl ? F(w.O) : nullptr);
     prof_end(m, DOMINO_KC_ATTN, st);
 
     prof_begin(m, DOMINO_KC_WO, st);
     a = gemm_args(base + m->wo[l].off, m->wo[l], 0, m->wo[l].NT, D.d, F(w.O), qd, M, qd, F(w.WOp), D.d, p.wo);
     if (fuse) {  // residual += attention output, and the FFN RMSNorm's statistics
-      resid(a, m->ffn_norm[l], 2 * l);
-      if (!proj(EPI_RESID, a, p.wo, fo)) return fail(DOMINO_ERR_UNSUPPORTED, "wo projection refused");
+      a.res_in = xc;
+      a.res_out = xn;
+      a.res_ssq = F(w.SSQ);
+      a.res_gain = m->ffn_norm[l];
+      a.yf = F(w.A2);
+      if (!proj(EPI_RESID, a, p.wo, pl)) return fail(DOMINO_ERR_UNSUPPORTED, "wo projection refused");
       std::swap(xc, xn);
-    } else if (!proj(EPI_STORE, a, p.wo, fo)) {
+    } else if (!proj(EPI_STORE, a, p.wo, pl)) {
       return fail(DOMINO_ERR_UNSUPPORTED, "wo projection refused");
     }
     prof_end(m, DOMINO_KC_WO, st);
 
     if (!fuse) {  // residual += attention output, then the FFN RMSNorm
       prof_begin(m, DOMINO_KC_NORM, st);
-      launch_add_norm(D, xc, xn, D.d, F(w.WOp), p.wo.ksplit, rstride, m->ffn_norm[l], fg ? nullptr : F(w.A), D.d, M,
-                      D.d, false, nullptr, nullptr, err, st, nullptr, nullptr, 0, fg ? F(w.A) : nullptr);
+      launch_add_norm(D, xc, xn, D.d, F(w.WOp), p.wo.ksplit, rstride, m->ffn_norm[l], pl ? nullptr : F(w.A2), D.d, M,
+                      D.d, false, nullptr, nullptr, err, st, nullptr, nullptr, 0, pl ? F(w.A2) : nullptr);
       std::swap(xc, xn);
       prof_end(m, DOMINO_KC_NORM, st);
     }
 
     prof_begin(m, DOMINO_KC_GATEUP, st);
-    a = gemm_args(base + m->gateup[l].off, m->gateup[l], 0, m->gateup[l].NT, D.ffn, F(w.A), D.d, M, D.d, F(w.F),
+    a = gemm_args(base + m->gateup[l].off, m->gateup[l], 0, m->gateup[l].NT, D.ffn, F(w.A2), D.d, M, D.d, F(w.F),
                   D.ffn, p.gateup);
-    if (fuse) deferred(a, p.wo.groups);
-    if (ff) a.yf = F(w.F);
-    if (!proj(EPI_SWIGLU, a, p.gateup, fg)) return fail(DOMINO_ERR_UNSUPPORTED, "gateup projection refused");
+    if (fuse) {
+      a.rs_ssq = F(w.SSQ);
+      a.rs_ng = p.wo.groups;
+      a.rs_d = D.d;
+      a.rs_eps = m->cfg.rms_eps;
+    }
+    if (pl) a.yf = F(w.F);
+    if (!proj(EPI_SWIGLU, a, p.gateup, pl)) return fail(DOMINO_ERR_UNSUPPORTED, "gateup projection refused");
     prof_end(m, DOMINO_KC_GATEUP, st);
 
     prof_begin(m, DOMINO_KC_DOWN, st);
     a = gemm_args(base + m->down[l].off, m->down[l], 0, m->down[l].NT, D.d, F(w.F), D.ffn, M, D.ffn, F(w.DNp), D.d,
                   p.down);
-    if (fuse && l + 1 < m->cfg.n_layers) {  // residual += FFN output, and the next attention RMSNorm's statistics
-      resid(a, m->attn_norm[l + 1], 2 * l + 1);
-      if (!proj(EPI_RESID, a, p.down, ff)) return fail(DOMINO_ERR_UNSUPPORTED, "down projection refused");
-      std::swap(xc, xn);
-    } else if (!proj(EPI_STORE, a, p.down, ff)) {
-      return fail(DOMINO_ERR_UNSUPPORTED, "down projection refused");
-    }
+    if (!proj(EPI_STORE, a, p.down, pl)) return fail(DOMINO_ERR_UNSUPPORTED, "down projection refused");
     prof_end(m, DOMINO_KC_DOWN, st);
   }
 

@@ -58,7 +58,7 @@ __global__ __launch_bounds__(512) void add_norm_kernel(const float *__restrict__
                                                        const int32_t *__restrict__ anchor, int mask_id, int V,
                                                        int32_t *err, const int32_t *__restrict__ tokens,
                                                        int nsplit, uint32_t *hdr, int hdr_words, int rows,
-                                                       u32x4 *__restrict__ planes) {
+                                                       u32x4 *__restrict__ planes, int nrb) {
   // nsplit workgroups per row: each forms the whole row's sum of squares but
   // writes only its slice of the columns
   int i = blockIdx.x / nsplit;
@@ -179,7 +179,7 @@ __global__ __launch_bounds__(512) void add_norm_kernel(const float *__restrict__
     if (planes) {
       bf16x8 hi, lo;
       split8(o, hi, lo);
-      const int KS = width / 32, nrb = (rows + 15) / 16;
+      const int KS = width / 32;
       const size_t at = ((size_t)(i >> 4) * KS + (c0 >> 5)) * 64 + 16 * ((c0 >> 3) & 3) + (i & 15);
       planes[at] = __builtin_bit_cast(u32x4, hi);
       planes[(size_t)nrb * KS * 64 + at] = __builtin_bit_cast(u32x4, lo);
@@ -1128,23 +1128,23 @@ template <typename WT, int MAXP>
 static void add_norm_t(const Dims &D, const float *x, float *x_out, int ldx, const float *parts, int np, size_t pstride,
                        const void *gain, float *y, int ldy, int rows, int width, bool skip_anchor,
                        const void *embed, const int32_t *anchor, int32_t *err, hipStream_t st,
-                       const int32_t *tokens, uint32_t *hdr, int hdr_words, void *planes) {
+                       const int32_t *tokens, uint32_t *hdr, int hdr_words, void *planes, int nrb) {
   // a few workgroups per row when there are few rows: a GEMM that reads rows
   // written by one workgroup each was measured ~5 us slower (QKV after the
   // attention RMSNorm at 16 rows), with two or more per row it is not
   int split = 1;
   while (split < 4 && rows * split < 64 && width % (2 * split * 8) == 0) split *= 2;
-  const int per = 8 / split, nrb = (rows + 15) / 16;  // with planes: groups of 8 / split row blocks
-  const int grid = planes ? (nrb + per - 1) / per * per * 16 * split : rows * split;
+  const int per = 8 / split, rb = (rows + 15) / 16;  // with planes: groups of 8 / split row blocks
+  const int grid = planes ? (rb + per - 1) / per * per * 16 * split : rows * split;
   hipLaunchKernelGGL((add_norm_kernel<WT, MAXP>), dim3(grid), dim3(512), 0, st, x, x_out, ldx, parts, np, pstride,
                      (const WT *)gain, y, ldy, width, D.eps, (int)skip_anchor, D.B - 1, (const WT *)embed, anchor,
-                     D.mask_id, D.V, err, tokens, split, hdr, hdr_words, rows, (u32x4 *)planes);
+                     D.mask_id, D.V, err, tokens, split, hdr, hdr_words, rows, (u32x4 *)planes, nrb > 0 ? nrb : rb);
 }
 
 void launch_add_norm(const Dims &D, const float *x, float *x_out, int ldx, const float *parts, int np, size_t pstride,
                      const void *gain, float *y, int ldy, int rows, int width, bool skip_anchor,
                      const void *embed, const int32_t *anchor, int32_t *err, hipStream_t st,
-                     const int32_t *tokens, uint32_t *hdr, int hdr_words, void *planes) {
+                     const int32_t *tokens, uint32_t *hdr, int hdr_words, void *planes, int nrb) {
   if (rows <= 0) return;
   if (np < 0 || np > 16) return;  // partial counts come from the GEMM planner (<= 16)
   // the least instance that holds every partial: slots past np are loaded all the same
@@ -1152,10 +1152,10 @@ void launch_add_norm(const Dims &D, const float *x, float *x_out, int ldx, const
     constexpr int P = decltype(slots)::value;
     if (D.bf16)
       add_norm_t<bf16_t, P>(D, x, x_out, ldx, parts, np, pstride, gain, y, ldy, rows, width, skip_anchor, embed,
-                            anchor, err, st, tokens, hdr, hdr_words, planes);
+                            anchor, err, st, tokens, hdr, hdr_words, planes, nrb);
     else
       add_norm_t<float, P>(D, x, x_out, ldx, parts, np, pstride, gain, y, ldy, rows, width, skip_anchor, embed,
-                           anchor, err, st, tokens, hdr, hdr_words, planes);
+                           anchor, err, st, tokens, hdr, hdr_words, planes, nrb);
   };
   if (np <= 2) go(std::integral_constant<int, 2>{});
   else if (np <= 4) go(std::integral_constant<int, 4>{});
@@ -1385,6 +1385,34 @@ void launch_sum_parts(const float *parts, int np, size_t pstride, int rows, int 
   if (n == 0) return;
   const unsigned blocks = (unsigned)std::min<size_t>((n + 255) / 256, 4096);
   hipLaunchKernelGGL(sum_parts_kernel, dim3(blocks), dim3(256), 0, st, parts, np, pstride, rows, width, y, ldy);
+}
+
+// one thread per 8 columns: a lane's 16 bytes of a fragment in each plane
+__global__ __launch_bounds__(256) void sum_parts_planes_kernel(const float *__restrict__ parts, int np,
+                                                               size_t pstride, int rows, int width,
+                                                               u32x4 *__restrict__ planes, int row0, int nrb) {
+  const int KS = width / 32, idx = blockIdx.x * 256 + threadIdx.x;
+  if (idx >= rows * KS * 4) return;
+  const int k = idx % (KS * 4) * 8, r = idx / (KS * 4), m = row0 + r;
+  float f[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+  for (int p = 0; p < np; ++p) {
+    const float4 *s = (const float4 *)(parts + p * pstride + (size_t)r * width + k);
+    const float4 a = s[0], b = s[1];
+    f[0] += a.x; f[1] += a.y; f[2] += a.z; f[3] += a.w;
+    f[4] += b.x; f[5] += b.y; f[6] += b.z; f[7] += b.w;
+  }
+  bf16x8 hi, lo;
+  split8(f, hi, lo);
+  const size_t at = ((size_t)(m >> 4) * KS + (k >> 5)) * 64 + 16 * ((k >> 3) & 3) + (m & 15);
+  planes[at] = __builtin_bit_cast(u32x4, hi);
+  planes[(size_t)nrb * KS * 64 + at] = __builtin_bit_cast(u32x4, lo);
+}
+void launch_sum_parts_planes(const float *parts, int np, size_t pstride, int rows, int width, void *planes, int row0,
+                             int nrb, hipStream_t st) {
+  const int items = rows * width / 8;
+  hipLaunchKernelGGL(sum_parts_planes_kernel, dim3((items + 255) / 256), dim3(256), 0, st, parts, np, pstride, rows,
+                     width, (u32x4 *)planes, row0, nrb);
 }
 
 __global__ void fill_u32_kernel(uint32_t *p, size_t n, uint32_t v) {

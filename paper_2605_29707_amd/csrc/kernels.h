@@ -6,12 +6,9 @@
 
 namespace dk {
 
-// Most column groups a residual epilogue (and so a deferred RMSNorm) covers.
-constexpr int kNormGroups = 64;
-
 // EPI_STORE: outputs (or K-split partials) stored; EPI_SWIGLU: silu(gate) * up
-// of interleaved (gate, up) tile pairs; EPI_RESID: K-split partials, then the
-// residual update with the next RMSNorm's statistics (GemmArgs res_*)
+// of interleaved (gate, up) tile pairs; EPI_RESID: the residual update with the
+// next RMSNorm's statistics (GemmArgs res_*)
 enum { EPI_STORE = 0, EPI_SWIGLU = 2, EPI_RESID = 3 };
 
 struct GemmArgs {
@@ -29,22 +26,19 @@ struct GemmArgs {
   void *xf = nullptr;  // wide kernel: the activations' hi/lo fragment planes
                        // (gemm_wide_scratch_bytes(M, K) bytes): written by the producer (X null)
                        // or by the launch itself, from X
-  void *yf = nullptr;  // wide kernel, EPI_SWIGLU: output as fragment planes (N / 32 k-steps) instead of Y
-  // Deferred RMSNorm of the activations (skinny kernel): X holds x * gain and
-  // every output row m is scaled by rsqrt(sum_g rs_ssq[g][m] / rs_d + rs_eps),
-  // the per-row sums of squares left by the producing projection's EPI_RESID.
+  void *yf = nullptr;  // rows and wide kernels: output as fragment planes (N / 32 k-steps):
+                       // of SwiGLU instead of Y, of the residual times the gain
+  // Deferred RMSNorm of the activations (rows kernel, EPI_SWIGLU): the planes hold
+  // x * gain and every output row m is scaled by rsqrt(sum_g rs_ssq[g][m] / rs_d +
+  // rs_eps), the per-row sums of squares left by the producing EPI_RESID.
   const float *rs_ssq = nullptr;
   int rs_ng = 0, rs_d = 0;
   float rs_eps = 0.f;
-  // EPI_RESID (skinny kernel, K split over workgroups): each split's partial
-  // goes out to the device coherence point and the last split of a column group
-  // to arrive (res_tickets[group], zero at launch) adds the partials in split
-  // order to res_in, writes the sum to res_out and, times res_gain, to res_xg,
-  // and the sum's squares over the group's columns to res_ssq[group][m].
+  // EPI_RESID (rows kernel): res_in + the product goes to res_out and, times
+  // res_gain, to yf, its squares' sums over tile g's columns to res_ssq[g][m].
   const float *res_in = nullptr;
-  float *res_out = nullptr, *res_xg = nullptr, *res_ssq = nullptr;
+  float *res_out = nullptr, *res_ssq = nullptr;
   const void *res_gain = nullptr;
-  unsigned *res_tickets = nullptr;
 };
 
 struct GemmPlan {
@@ -53,6 +47,8 @@ struct GemmPlan {
   int nw;   // weight tiles per workgroup (skinny: a wave each, 8 or 6)
   int pgrid;  // > 0: that many workgroups loop over the groups (one pipeline across groups)
   int wide = 0;  // 1: the wide-activation kernel (gemm_wide.hip) runs this plan
+  int rows = 0;  // 1: the kernel for one or two row blocks (gemm_rows.hip) runs this plan
+  bool planes() const { return wide || rows; }  // its input is fragment planes
 };
 
 // max_split = 1: one workgroup covers all of K (direct output); otherwise K
@@ -67,11 +63,15 @@ GemmPlan plan_gemm_wide(int ntiles, int KS, int M, int epi, int n_cu, int max_sp
 // (K not 32 KS, no rows, no fragment scratch)
 bool launch_gemm_wide(int epi, const GemmArgs &a, const GemmPlan &p, hipStream_t st);
 size_t gemm_wide_scratch_bytes(int M, int K);
-// Above this many rows a bf16 GEMM whose K is a multiple of 32 runs the wide
-// kernel.  At 64 rows it takes 43 us against the skinny kernel's 64 on gate/up of
-// the 8B shape, 14 against 19 on QKV, 24 against 32 on down; at 32 rows 38 against
-// 43, but there the skinny kernel's projections also end with the residual update
-// and the next norm's statistics, which saves two launches a layer.
+// One or two row blocks (up to kRowsMax rows), bf16 weights: planes in a.xf (X null)
+GemmPlan plan_gemm_rows(int ntiles, int KS, int M, int epi, int n_cu, int max_split);
+bool launch_gemm_rows(int epi, const GemmArgs &a, const GemmPlan &p, hipStream_t st);
+// Layer projections with bf16 weights: up to this many rows the rows kernel,
+// above it the wide kernel (64 rows of the 8B shape: 43 us on gate/up, 14 on QKV,
+// 24 on down; the rows kernel at 32 rows 34, 12, 25 and nearly twice that per
+// further pair of row blocks).
+constexpr int kRowsMax = 32;
+// Other bf16 GEMMs (context fusion, LM head): up to this many rows the skinny kernel
 constexpr int kSkinnyMaxRows = 32;
 // Up to this many rows the LM head stays on the skinny kernel where that runs as
 // one persistent launch (226 against 239 us at 64 rows, 196 against 227 at 32).
@@ -100,11 +100,12 @@ void launch_embed_block(const Dims &D, const void *embed, const int32_t *anchor,
 // With `hdr` given (and `embed`, no skip_anchor), the launch also zeroes
 // hdr[0 .. hdr_words) (the step's workspace header; hdr[0] is `err`) before
 // any error of its own is raised.  With `planes` (width a multiple of 32) the
-// rows are also written as the wide GEMM's fragment planes; y may then be null.
+// rows are also written as fragment planes of nrb row blocks (0: of these rows);
+// y may then be null.
 void launch_add_norm(const Dims &D, const float *x, float *x_out, int ldx, const float *parts, int np, size_t pstride,
                      const void *gain, float *y, int ldy, int rows, int width, bool skip_anchor,
                      const void *embed, const int32_t *anchor, int32_t *err, hipStream_t st,
-                     const int32_t *tokens = nullptr, uint32_t *hdr = nullptr, int hdr_words = 0, void *planes = nullptr);
+                     const int32_t *tokens = nullptr, uint32_t *hdr = nullptr, int hdr_words = 0, void *planes = nullptr, int nrb = 0);
 // q/k RMSNorm + RoPE on the QKV projection (sum of np partials); writes
 // Q [M][nq][dh], Kb/Vb [M][nkv][dh].  The projection's rows M + b*n_new + i
 // (n_new appended context rows per batch row) have their K (k-norm, RoPE at
@@ -261,5 +262,9 @@ void launch_fill_u32(uint32_t *p, size_t n, uint32_t v, hipStream_t st);
 // (width, pstride and ldy multiples of 4; y must not alias parts)
 void launch_sum_parts(const float *parts, int np, size_t pstride, int rows, int width, float *y, int ldy,
                       hipStream_t st);
+// the same sum (np = 1: a copy) written as rows row0 .. of fragment planes of nrb
+// row blocks (width a multiple of 32)
+void launch_sum_parts_planes(const float *parts, int np, size_t pstride, int rows, int width, void *planes, int row0,
+                             int nrb, hipStream_t st);
 
 }  // namespace dk
