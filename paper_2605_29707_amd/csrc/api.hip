@@ -928,13 +928,11 @@ namespace {
 struct TrainLayout {
   WsLayout w;
   size_t S, Y, U, part, lab, ce, total;
-  int GCt;
 };
 void train_layout(const domino_model *m, int bs, int max_ctx, int max_new, TrainLayout &t) {
   layout(m, bs, max_ctx, max_new, 1, t.w);
   const Dims &D = m->D;
   const size_t Mr = (size_t)bs * (D.B - 1);
-  t.GCt = train_ce_grid(D.V, D.r, m->bf16);
   size_t o = t.w.total;
   auto take = [&](size_t bytes) {
     size_t at = o;
@@ -944,7 +942,7 @@ void train_layout(const domino_model *m, int bs, int max_ctx, int max_new, Train
   t.S = take(Mr * D.ds * 4);
   t.Y = take(Mr * D.r * 4);
   t.U = take(train_u_bytes((int)Mr, D.r));
-  t.part = take(Mr * t.GCt * 16);
+  t.part = take(train_part_bytes((int)Mr, D.V, D.r, m->bf16));
   t.lab = take(2 * Mr * 4);
   t.ce = take(2 * Mr * 4);
   t.total = o;

@@ -254,7 +254,9 @@ bool launch_mt(int epi, const GemmArgs &a, const GemmPlan &p, int nrb, hipStream
 
 // Tiles per workgroup (nw) and K split: the least traffic of the busiest CU,
 // its workgroups' weights and activations (every k-step 1 KB a tile and 2 KB a
-// row block) and the split's partial outputs, written and read back.  On the
+// row block) and the split's partial outputs, written and read back, which count
+// sixteenfold (they come after the last product, and a consumer waits for them:
+// QKV 3 tiles x 2 splits 9.6 us, 6 x 4 11.4; down 4 x 4 17.3, 8 x 8 19.4).  On the
 // 8B shape at 16 rows it takes 6 tiles for gate/up, 3 x 2 splits for QKV and 4 x
 // 4 for down, each the fastest of those measured.  EPI_RESID: one tile, no split.
 GemmPlan plan_gemm_rows(int ntiles, int KS, int M, int epi, int n_cu, int max_split) {
@@ -277,7 +279,7 @@ GemmPlan plan_gemm_rows(int ntiles, int KS, int M, int epi, int n_cu, int max_sp
       const int spw = (KS + ks - 1) / ks;
       if (ks > 1 && ((ks - 1) * spw >= KS || spw < 16)) continue;  // an empty or a very short split
       const long wgs = (long)groups * ks;
-      const double part = ks > 1 ? 4.0 * ks * (double)M * ntiles * 16 * 4 / 1024.0 / n_cu : 0.0;
+      const double part = ks > 1 ? 16 * 2.0 * ks * (double)M * ntiles * 16 * 4 / 1024.0 / n_cu : 0.0;
       const double cost = (double)((wgs + n_cu - 1) / n_cu) * spw * (ct + 2 * p.MT) + part;
       if (cost < best * 0.999) {
         best = cost;

@@ -28,10 +28,11 @@
 
 namespace dk {
 
-// Insert (v, id) into a sorted 8-entry list (best first) by bubbling.
-DEVI void list_insert(float (&lv)[8], int (&li)[8], float v, int id) {
+// Insert (v, id) into a sorted list (best first) by bubbling.
+template <int L>
+DEVI void list_insert(float (&lv)[L], int (&li)[L], float v, int id) {
 #pragma unroll
-  for (int q = 0; q < 8; ++q) {
+  for (int q = 0; q < L; ++q) {
     if (better(v, id, lv[q], li[q])) {
       const float tv = lv[q];
       const int ti = li[q];
@@ -435,7 +436,7 @@ __global__ __launch_bounds__(kRowWaves * 64) void head_rows_kernel(HeadArgs h, i
 // workgroup's top-1 per batch row.  A workgroup covers ROWS vocabulary
 // rows (8 waves x kTPW tiles of 16).  (With the top-beta of beta > 1 selected
 // here, a position took 44 us at 32 rows and beta 4, half of it the selection;
-// now 31 us, and 92 once for the selection.)
+// now 31 us, and 47 once for the selection.)
 // ---------------------------------------------------------------------------
 constexpr int kLogitWaves = 8;
 // W2 tiles per wave: five, so that the grid fits the GPU in one round at the
@@ -613,14 +614,28 @@ __global__ __launch_bounds__(kLogitWaves * 64) void head_logits_kernel(HeadArgs 
   }
 }
 
-// The top-beta (beta > 1) of every position's corrected logits, after the
+// Maximum over the wave by lane rotations within rows and four lane reads
+DEVI float wave_max_dpp(float v) {
+  v = fmaxf(v, row_ror<8>(v));
+  v = fmaxf(v, row_ror<4>(v));
+  v = fmaxf(v, row_ror<2>(v));
+  v = fmaxf(v, row_ror<1>(v));
+  float r = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 0));
+#pragma unroll
+  for (int k = 1; k < 4; ++k) r = fmaxf(r, __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 16 * k)));
+  return r;
+}
+
+// The top-beta (1 < beta <= L) of every position's corrected logits, after the
 // rollout: a wave per kTopWave values of one row, 64 a lane in registers.  The
 // beta-th largest of the 64 lane maxima bounds the wave's beta-th best from
 // below, so only the few values from there on (about beta of 4096) are
 // inserted, one by one, into a sorted list that every lane keeps alike; the bound
-// follows the list's last entry.  Bound by reading the logits (292 MB at 32
-// rows, 45 us; the whole selection 92).
+// follows the list's last entry.  Four values share a test.  Bound by reading
+// the logits (292 MB at 32 rows, 45 us; the whole selection 47, 92 with a
+// test and eight list entries for each value).
 constexpr int kTopWave = 4096;
+template <int L>
 __global__ __launch_bounds__(256) void head_topb_kernel(HeadArgs h, int nchunk) {
   const int V = h.D.V, beta = h.beta, depth = h.D.B - 1, bs = h.D.bs;
   const int lane = threadIdx.x & 63;
@@ -635,37 +650,42 @@ __global__ __launch_bounds__(256) void head_topb_kernel(HeadArgs h, int nchunk) 
     const int id = c * kTopWave + q * 256 + 4 * lane;
     x[q] = __builtin_bit_cast(float4, __builtin_nontemporal_load((const floatx4 *)(row + min(id, (V - 1) / 4 * 4))));
   }
-  float m = -INFINITY;
+  if ((c + 1) * kTopWave > V) {  // wave-uniform: ids past V become NaN, which nothing below takes
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (c * kTopWave + q * 256 + 4 * lane + e >= V) (&x[q].x)[e] = NAN;
+  }
+  float m4[NQ], m = -INFINITY;
 #pragma unroll
   for (int q = 0; q < NQ; ++q) {
-    const int id = c * kTopWave + q * 256 + 4 * lane;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      float &v = (&x[q].x)[e];
-      v = id + e < V ? order_val(v) : -INFINITY;
-      m = fmaxf(m, v);
-    }
+    m4[q] = fmaxf(fmaxf(x[q].x, x[q].y), fmaxf(x[q].z, x[q].w));  // a NaN drops out
+    m = fmaxf(m, m4[q]);
   }
   float t = -INFINITY;
   for (int k = 0; k < beta; ++k) {  // the beta-th largest lane maximum (equal ones leave together: the bound is only lower)
-    t = wave_max(m);
+    t = wave_max_dpp(m);
     if (m == t) m = -INFINITY;
   }
-  float lv[8];
-  int li[8];
+  float lv[L];
+  int li[L];
 #pragma unroll
-  for (int k = 0; k < 8; ++k) {
+  for (int k = 0; k < L; ++k) {
     lv[k] = -INFINITY;
     li[k] = INT_MAX;
   }
   float wv = t;  // what a value has to beat: the bound, then the list's entry of rank beta
   int wi = INT_MAX;
+  // A bound of -inf admits every value: NaN (as -inf) too, below V
+  const bool low = t == -INFINITY;
 #pragma unroll
   for (int q = 0; q < NQ; ++q) {
+    if (!low && !__any(m4[q] >= wv)) continue;
     const int id = c * kTopWave + q * 256 + 4 * lane;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const float v = (&x[q].x)[e];
+      const float v = order_val((&x[q].x)[e]);
       unsigned long long mk = __ballot(id + e < V && better(v, id + e, wv, wi));
       while (mk) {  // wave-uniform
         const int l = __ffsll(mk) - 1;
@@ -673,11 +693,11 @@ __global__ __launch_bounds__(256) void head_topb_kernel(HeadArgs h, int nchunk) 
         const float cv = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
         const int ci = c * kTopWave + q * 256 + 4 * l + e;
         if (!better(cv, ci, wv, wi)) continue;
-        list_insert(lv, li, cv, ci);
+        list_insert<L>(lv, li, cv, ci);
         float ev = lv[0];
         int ei = li[0];
 #pragma unroll
-        for (int k = 1; k < 8; ++k)
+        for (int k = 1; k < L; ++k)
           if (k < beta) {
             ev = lv[k];
             ei = li[k];
@@ -692,7 +712,7 @@ __global__ __launch_bounds__(256) void head_topb_kernel(HeadArgs h, int nchunk) 
   if (lane == 0) {
     const size_t o = (((size_t)j * bs + b) * nchunk + c) * beta;
 #pragma unroll
-    for (int k = 0; k < 8; ++k)
+    for (int k = 0; k < L; ++k)
       if (k < beta) {
         h.pval[o + k] = lv[k];
         h.pid[o + k] = li[k];
@@ -1362,7 +1382,10 @@ static void launch_loop(HeadArgs h, hipStream_t st) {
   int nlist = h.GC;
   if (h.beta > 1) {
     nlist = (D.V + kTopWave - 1) / kTopWave;  // (at most GC: the lists fit the workspace)
-    hipLaunchKernelGGL(head_topb_kernel, dim3((nlist + 3) / 4, depth, D.bs), dim3(256), 0, st, h, nlist);
+    const dim3 grid((nlist + 3) / 4, depth, D.bs);
+    if (h.beta <= 2) hipLaunchKernelGGL(head_topb_kernel<2>, grid, dim3(256), 0, st, h, nlist);
+    else if (h.beta <= 4) hipLaunchKernelGGL(head_topb_kernel<4>, grid, dim3(256), 0, st, h, nlist);
+    else hipLaunchKernelGGL(head_topb_kernel<8>, grid, dim3(256), 0, st, h, nlist);
   }
   hipLaunchKernelGGL(head_merge_kernel, dim3(depth, D.bs), dim3(64), 0, st, h, nlist);
 }

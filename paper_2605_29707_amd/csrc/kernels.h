@@ -210,7 +210,7 @@ struct TrainArgs {
   const float *Lbase;     // [Mr] rows of stride ldl
   int ldl;
   const int32_t *labels;  // [Mr]
-  float *part;            // [Mr][GC][4] per-workgroup (max, sum exp) of base and final logits
+  float *part;            // [Mr][GC][8 waves][4]: (max, sum exp) of base and final logits (train_part_bytes)
   float *lab;             // [2][Mr] label logits (base, final)
   float *ce;              // [2][Mr] cross-entropies (base, final)
   float *loss;            // [3] total, base, final
@@ -219,6 +219,7 @@ struct TrainArgs {
   int32_t *err;
 };
 int train_ce_grid(int V, int r, bool bf16);
+size_t train_part_bytes(int Mr, int V, int r, bool bf16);
 inline size_t train_u_bytes(int Mr, int r) { return (size_t)((Mr + 15) / 16) * 16 * r * 4; }
 hipError_t launch_train_loss(const TrainArgs &t, bool bf16, hipStream_t st);
 

@@ -8,20 +8,24 @@
 //          as matrix-core fragments (hi/lo split as in the rollout);
 //   ce     L_final = L_base + W2 u for all bs*(B-1) rows at once: W2 streams
 //          from HBM once (tile-packed, kept in registers), L_base once, and the
-//          corrected logits never leave the chip.  Each workgroup leaves, per
+//          corrected logits never leave the chip.  Each wave leaves, per
 //          row, the (max, sum exp) pair of its vocabulary slice for the base and
-//          the final logits, and the workgroup holding the label writes the
+//          the final logits, and the wave holding the label writes the
 //          label's two logits.  A workgroup walks the rows 16 at a time with the
 //          next 16's operands in flight and one barrier each.  240 rows of
 //          151936 logits: 165 us while every workgroup formed every u itself,
-//          loaded after each barrier and used expf; now 153, against 35 us for
-//          the bytes (W2 and L_base) and 17 for the products.
-//   ce_row a wave per row merges the pairs (CE = log-sum-exp - label logit);
+//          loaded after each barrier and used expf, 120 while the waves' pairs
+//          were merged through LDS; now 108, against 35 us for the bytes (W2
+//          and L_base) and 17 for the products: two waves a SIMD, which spend
+//          most of it on the exponentials between the barriers.
+//   ce_row a workgroup per row merges the pairs (CE = log-sum-exp - label logit);
 //   loss   one wave: the position-weighted means (weights exp(-k / gamma), k = 0
 //          for the first draft position) and the curriculum mix
 //          (1 - lambda) L_final + lambda L_base, in a fixed order
 //          (deterministic).  As one workgroup for all rows the two took 80 us
-//          at 240 rows, now 7 and 5.
+//          at 240 rows, now 8 and 5.
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
 #include "mfma.h"
@@ -69,7 +73,8 @@ __global__ __launch_bounds__(256) void train_u_kernel(TrainArgs t) {
 
 constexpr float kLog2e = 1.4426950408889634f;
 
-template <typename WT, int KS>
+// FINAL: the corrected logits are also written out
+template <typename WT, int KS, bool FINAL>
 __global__ __launch_bounds__(kCeWaves * 64) void train_ce_kernel(TrainArgs t) {
   constexpr int XF = XStage<WT>::XF;
   constexpr int kTPW = ce_tpw(KS);
@@ -81,7 +86,6 @@ __global__ __launch_bounds__(kCeWaves * 64) void train_ce_kernel(TrainArgs t) {
   const int g = lane >> 4, cc = lane & 15;
   const int NT = (V + 15) / 16, nrt = (Mr + 15) / 16;
   __shared__ u32x4 us[2][KS * 64 * XF];        // U tile as B fragments
-  __shared__ float4 red[2][kCeWaves][16];      // per-wave (mb, sb, mf, sf) of each row
   // L_base of the tile in work, a lane's own values: parked here because the
   // registers hold this wave's W2 fragments and the next tile's loads
   __shared__ float4 lbs[kCeWaves][kTPW][64];
@@ -89,14 +93,24 @@ __global__ __launch_bounds__(kCeWaves * 64) void train_ce_kernel(TrainArgs t) {
   int tiles[kTPW];
 #pragma unroll
   for (int q = 0; q < kTPW; ++q) tiles[q] = (blockIdx.x * kCeWaves + wave) * kTPW + q;
-  // this wave's W2 fragments, loaded once and reused for every row tile
+  // this wave's W2 fragments, loaded once and reused for every row tile: the
+  // last of five tiles in LDS, because with all of them in registers some value
+  // spills, and a spill's reload waits for every load issued before it, the next
+  // rows' operands included (153 us instead of 120)
+  constexpr int kReg = kTPW > 4 ? 4 : kTPW;
+  extern __shared__ __align__(16) unsigned char smem[];
+  u32x4 *w2s = (u32x4 *)smem + (size_t)wave * KS * 64 + lane;  // [s * 64], kTPW > kReg
   const u32x4 *w2p = (const u32x4 *)t.w2p;
-  u32x4 wf[kTPW][KS];
+  u32x4 wf[kReg][KS];
 #pragma unroll
   for (int q = 0; q < kTPW; ++q) {
     const int tc = min(tiles[q], NT - 1);
 #pragma unroll
-    for (int s = 0; s < KS; ++s) wf[q][s] = w2p[((size_t)tc * KS + s) * 64 + lane];
+    for (int s = 0; s < KS; ++s) {
+      const u32x4 w = w2p[((size_t)tc * KS + s) * 64 + lane];
+      if (q < kReg) wf[q < kReg ? q : 0][s] = w;
+      else w2s[s * 64] = w;
+    }
   }
   // The next row tile's operands: its U fragments (element tid + 512 q of the
   // tile) and L_base of this lane's row and the four vocabulary ids of each
@@ -115,22 +129,6 @@ __global__ __launch_bounds__(kCeWaves * 64) void train_ce_kernel(TrainArgs t) {
       lb[q] = *(const float4 *)(t.Lbase + (size_t)rowc * t.ldl + min(tiles[q], NT - 1) * 16 + 4 * g);
     label = t.labels[rowc];
   };
-  // merge of the waves' pairs of row tile rt: eight lanes a row
-  auto merge = [&](int rt) {
-    if (wave >= 2) return;
-    const int m = tid >> 3;
-    float4 p = red[rt & 1][tid & 7][m];
-#pragma unroll
-    for (int o = 1; o <= 4; o <<= 1) {
-      const float x = __shfl_xor(p.x, o, 64), y = __shfl_xor(p.y, o, 64);
-      const float z = __shfl_xor(p.z, o, 64), w = __shfl_xor(p.w, o, 64);
-      lse_merge(p.x, p.y, x, y);
-      lse_merge(p.z, p.w, z, w);
-    }
-    if ((tid & 7) == 0 && 16 * rt + m < Mr)
-      *(float4 *)(t.part + ((size_t)(16 * rt + m) * gridDim.x + blockIdx.x) * 4) = p;
-  };
-
   load(0);
   for (int rt = 0; rt < nrt; ++rt) {
     u32x4 *ub = us[rt & 1];
@@ -139,12 +137,10 @@ __global__ __launch_bounds__(kCeWaves * 64) void train_ce_kernel(TrainArgs t) {
 #pragma unroll
     for (int q = 0; q < kTPW; ++q) lbs[wave][q][lane] = lb[q];
     const int row = 16 * rt + cc, lab = label;
-    // one barrier a tile: U of this one is staged, every wave has left the
-    // products of the last one (whose buffer the next one takes) and its pairs
-    // are in red
+    // one barrier a tile: U of this one is staged, and every wave has left the
+    // products of the last one, whose buffer the next one takes
     __syncthreads();
     load(rt + 1);
-    if (rt > 0) merge(rt - 1);
 
     // k-step major: each staged U fragment is read from LDS once for all tiles
     floatx4 acc[kTPW][1];
@@ -156,75 +152,96 @@ __global__ __launch_bounds__(kCeWaves * 64) void train_ce_kernel(TrainArgs t) {
 #pragma unroll
       for (int f = 0; f < XF; ++f) xf[f] = ub[((size_t)s * 64 + lane) * XF + f];
 #pragma unroll
-      for (int q = 0; q < kTPW; ++q) Mac2<WT, 1>::step(wf[q][s], xf, acc[q]);
+      for (int q = 0; q < kTPW; ++q) {
+        const u32x4 w = q < kReg ? wf[q < kReg ? q : 0][s] : w2s[s * 64];
+        Mac2<WT, 1>::step(w, xf, acc[q]);
+      }
     }
 
-    // lane (g, cc) holds vocabulary ids 16 tile + 4 g + e of row m0 + cc:
-    // stores, the label's logits and the maximum first, then the sums (of
-    // 2^(x log2 e - m log2 e): one multiply-add and one instruction a term)
-    float mb = -INFINITY, mf = -INFINITY;
+    // lane (g, cc) holds vocabulary ids 16 tile + 4 g + e of row 16 rt + cc: the
+    // label's logits (by selection, one branch at the end) and the maximum first,
+    // then the sums (the difference first, so that the largest term is 1 exactly
+    // and a row of the type's lowest value stays finite).  Ids past V are tested only in a wave that has some;
+    // rows past the end only feed pairs that are never stored.
+    float mb = -INFINITY, mf = -INFINITY, sb = 0.f, sf = 0.f;
+    float lab_b = 0.f, lab_f = 0.f;
+    auto reduce = [&](auto masked) {
+      constexpr bool kMasked = decltype(masked)::value;
 #pragma unroll
-    for (int q = 0; q < kTPW; ++q)
+      for (int q = 0; q < kTPW; ++q) {
+        const float4 l4 = lbs[wave][q][lane];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int n = tiles[q] * 16 + 4 * g + e;
-        const bool ok = row < Mr && n < V;
-        const float base = (&lbs[wave][q][lane].x)[e];
-        const float fin = base + acc[q][0][e];
-        if (t.final_logits && ok) t.final_logits[(size_t)row * V + n] = fin;
-        if (ok && n == lab) {
-          t.lab[row] = base;
-          t.lab[Mr + row] = fin;
+        for (int e = 0; e < 4; ++e) {
+          const int n = tiles[q] * 16 + 4 * g + e;
+          const bool ok = !kMasked || n < V;
+          const float base = e == 0 ? l4.x : (e == 1 ? l4.y : (e == 2 ? l4.z : l4.w));
+          const float fin = base + acc[q][0][e];
+          if (FINAL && ok && row < Mr) t.final_logits[(size_t)row * V + n] = fin;
+          lab_b = n == lab ? base : lab_b;
+          lab_f = n == lab ? fin : lab_f;
+          mb = fmaxf(mb, ok ? base : -INFINITY);  // (a NaN drops out: it counts as -inf)
+          acc[q][0][e] = ok ? order_val(fin) : -INFINITY;
+          mf = fmaxf(mf, acc[q][0][e]);
         }
-        mb = fmaxf(mb, ok ? order_val(base) : -INFINITY);
-        acc[q][0][e] = ok ? order_val(fin) : -INFINITY;
-        mf = fmaxf(mf, acc[q][0][e]);
       }
-    // a slice with no finite value (maximum -inf) keeps its sum at 0; one of +inf is NaN, as inf - inf
-    const float rb = mb == -INFINITY ? 0.f : mb * kLog2e, rf = mf == -INFINITY ? 0.f : mf * kLog2e;
-    float sb = 0.f, sf = 0.f;
+      // the row's maximum over its four lanes, so that their sums add
 #pragma unroll
-    for (int q = 0; q < kTPW; ++q)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const bool ok = row < Mr && tiles[q] * 16 + 4 * g + e < V;
-        const float base = ok ? order_val((&lbs[wave][q][lane].x)[e]) : -INFINITY;
-        sb += __builtin_amdgcn_exp2f(fmaf(base, kLog2e, -rb));
-        sf += __builtin_amdgcn_exp2f(fmaf(acc[q][0][e], kLog2e, -rf));
+      for (int o = 16; o <= 32; o <<= 1) {
+        mb = fmaxf(mb, __shfl_xor(mb, o, 64));
+        mf = fmaxf(mf, __shfl_xor(mf, o, 64));
       }
-    // the four lanes of a row; the waves one tile later
+      // a slice with no finite value (maximum -inf) keeps its sum at 0; one of +inf is NaN, as inf - inf
+      const float rb = mb == -INFINITY ? 0.f : mb, rf = mf == -INFINITY ? 0.f : mf;
+#pragma unroll
+      for (int q = 0; q < kTPW; ++q) {
+        const float4 l4 = lbs[wave][q][lane];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const bool ok = !kMasked || tiles[q] * 16 + 4 * g + e < V;
+          const float base = ok ? order_val(e == 0 ? l4.x : (e == 1 ? l4.y : (e == 2 ? l4.z : l4.w))) : -INFINITY;
+          sb += __builtin_amdgcn_exp2f((base - rb) * kLog2e);
+          sf += __builtin_amdgcn_exp2f((acc[q][0][e] - rf) * kLog2e);
+        }
+      }
+    };
+    if ((tiles[kTPW - 1] + 1) * 16 <= V) reduce(std::false_type{});  // wave-uniform
+    else reduce(std::true_type{});
+    const int lt = lab - tiles[0] * 16;  // (the tiles are consecutive)
+    if (row < Mr && lab < V && lt >= 0 && lt < kTPW * 16 && ((lt >> 2) & 3) == g) {
+      t.lab[row] = lab_b;
+      t.lab[Mr + row] = lab_f;
+    }
 #pragma unroll
     for (int o = 16; o <= 32; o <<= 1) {
-      const float mb2 = __shfl_xor(mb, o, 64), sb2 = __shfl_xor(sb, o, 64);
-      const float mf2 = __shfl_xor(mf, o, 64), sf2 = __shfl_xor(sf, o, 64);
-      lse_merge(mb, sb, mb2, sb2);
-      lse_merge(mf, sf, mf2, sf2);
+      sb += __shfl_xor(sb, o, 64);
+      sf += __shfl_xor(sf, o, 64);
     }
-    if (g == 0) red[rt & 1][wave][cc] = make_float4(mb, sb, mf, sf);
+    if (g == 0 && row < Mr)
+      *(float4 *)(t.part + (((size_t)row * gridDim.x + blockIdx.x) * kCeWaves + wave) * 4) =
+          make_float4(mb, sb, mf, sf);
   }
-  __syncthreads();
-  merge(nrt - 1);
 }
 
-// A wave per row merges the workgroups' pairs (CE = log-sum-exp - label logit).
-constexpr int kLoadsPerLane = 8;
-__global__ __launch_bounds__(256) void train_ce_row_kernel(TrainArgs t, int GC) {
-  const int lane = threadIdx.x & 63, row = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= t.Mr) return;
+// A workgroup per row merges the waves' pairs (CE = log-sum-exp - label logit):
+// 1904 of them at 151936 logits and 238 workgroups, two rounds of loads a lane.
+constexpr int kLoadsPerLane = 4;
+__global__ __launch_bounds__(256) void train_ce_row_kernel(TrainArgs t, int npair) {
+  __shared__ float4 red[4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, row = blockIdx.x;
   // the label and its two logits first, so their round trip overlaps the pairs'
   const int label = t.labels[row];
   const float lb = order_val(t.lab[row]), lf = order_val(t.lab[t.Mr + row]);
   float mb = -INFINITY, s_b = 0.f, mf = -INFINITY, s_f = 0.f;
   // kLoadsPerLane pairs per lane in flight together (clamped index, masked
   // after): a load per merge would pay one memory round trip each
-  const float4 *pr = (const float4 *)t.part + (size_t)row * GC;
-  for (int c0 = 0; c0 < GC; c0 += 64 * kLoadsPerLane) {
+  const float4 *pr = (const float4 *)t.part + (size_t)row * npair;
+  for (int c0 = wave * 64 + lane; c0 < npair; c0 += 256 * kLoadsPerLane) {
     float4 p[kLoadsPerLane];
 #pragma unroll
-    for (int q = 0; q < kLoadsPerLane; ++q) p[q] = pr[min(c0 + q * 64 + lane, GC - 1)];
+    for (int q = 0; q < kLoadsPerLane; ++q) p[q] = pr[min(c0 + q * 256, npair - 1)];
 #pragma unroll
     for (int q = 0; q < kLoadsPerLane; ++q)
-      if (c0 + q * 64 + lane < GC) {
+      if (c0 + q * 256 < npair) {
         lse_merge(mb, s_b, p[q].x, p[q].y);
         lse_merge(mf, s_f, p[q].z, p[q].w);
       }
@@ -236,7 +253,13 @@ __global__ __launch_bounds__(256) void train_ce_row_kernel(TrainArgs t, int GC) 
     lse_merge(mb, s_b, mb2, sb2);
     lse_merge(mf, s_f, mf2, sf2);
   }
-  if (lane == 0) {
+  if (lane == 0) red[wave] = make_float4(mb, s_b, mf, s_f);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < 4; ++w) {
+      lse_merge(mb, s_b, red[w].x, red[w].y);
+      lse_merge(mf, s_f, red[w].z, red[w].w);
+    }
     const bool ok = label >= 0 && label < t.V;
     if (!ok) raise_error(t.err, DEV_BAD_TOKEN);
     t.ce[row] = ok ? mb + logf(s_b) - lb : NAN;
@@ -275,7 +298,17 @@ template <typename WT, int KS>
 static void launch_ce_t(const TrainArgs &t, int GC, hipStream_t st) {
   const int items = (t.Mr + 15) / 16 * KS * 64;
   hipLaunchKernelGGL((train_u_kernel<WT, KS>), dim3((items + 255) / 256), dim3(256), 0, st, t);
-  hipLaunchKernelGGL((train_ce_kernel<WT, KS>), dim3(GC), dim3(kCeWaves * 64), 0, st, t);
+  constexpr size_t lds = ce_tpw(KS) > 4 ? (size_t)kCeWaves * KS * 1024 : 0;  // the fifth tiles
+  auto go = [&](auto kernel) {
+    (void)hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipLaunchKernelGGL(kernel, dim3(GC), dim3(kCeWaves * 64), lds, st, t);
+  };
+  if (t.final_logits) go(train_ce_kernel<WT, KS, true>);
+  else go(train_ce_kernel<WT, KS, false>);
+}
+
+size_t train_part_bytes(int Mr, int V, int r, bool bf16) {
+  return (size_t)Mr * train_ce_grid(V, r, bf16) * kCeWaves * 16;
 }
 
 int train_ce_grid(int V, int r, bool bf16) {
@@ -295,7 +328,7 @@ hipError_t launch_train_loss(const TrainArgs &t, bool bf16, hipStream_t st) {
     else if (KS == 8) launch_ce_t<float, 8>(t, GC, st);
     else return hipErrorInvalidValue;
   }
-  hipLaunchKernelGGL(train_ce_row_kernel, dim3((t.Mr + 3) / 4), dim3(256), 0, st, t, GC);
+  hipLaunchKernelGGL(train_ce_row_kernel, dim3(t.Mr), dim3(256), 0, st, t, GC * kCeWaves);
   hipLaunchKernelGGL(train_loss_kernel, dim3(1), dim3(64), 0, st, t);
   return hipGetLastError();
 }
