@@ -115,9 +115,10 @@ DEVI void load_chunk(const LT *row, int c, int V, float (&z)[kVsPer]) {
 }
 
 // (1) max and sum of exp over one vocabulary chunk of one row (NaN as -inf).
-// Bound by the logits' bytes: 16-byte loads, one multiply-add and one exp2
-// instruction a value.  The first workgroup clears the error word (the next
-// launch raises errors).
+// Bound by the logits' bytes: 16-byte loads and one exp2 instruction a value,
+// of the difference to the maximum first, since a chunk may hold nothing but a
+// mask of the type's lowest value, whose multiple is infinite.  The first
+// workgroup clears the error word (the next launch raises errors).
 template <typename LT, bool WIDE>
 __global__ __launch_bounds__(kVsThreads) void vs_lse_partial_kernel(const LT *__restrict__ target,
                                                                     const float *__restrict__ draft, int B, int V,
@@ -136,10 +137,10 @@ __global__ __launch_bounds__(kVsThreads) void vs_lse_partial_kernel(const LT *__
     m = fmaxf(m, z[q]);
   }
   m = block_max(m, red);
-  const float ref = m == -INFINITY ? 0.f : m * kVsLog2e;  // (every term is then 0)
+  const float ref = m == -INFINITY ? 0.f : m;  // (every term is then 0)
   float s = 0.f;
 #pragma unroll
-  for (int q = 0; q < kVsPer; ++q) s += __builtin_amdgcn_exp2f(fmaf(z[q], kVsLog2e, -ref));
+  for (int q = 0; q < kVsPer; ++q) s += __builtin_amdgcn_exp2f((z[q] - ref) * kVsLog2e);
   s = block_sum(s, red);
   if (threadIdx.x == 0) part[((size_t)b * (2 * B - 1) + r) * nch + c] = make_float2(m, s);
 }

@@ -1,0 +1,77 @@
+"""The rollout's selection where its row tiles and the bounded top-beta can go
+wrong: batches around 16 and 32 rows, vocabularies that end inside a load, a tile
+and a 4096-value list, exact ties and NaN logits.  The selected ids and values are
+compared bit by bit with the selection from the logits that the step reports, and
+those with the fp64 oracle.
+
+Tolerance: 3e-4, as for the projections of this shape (test_gpu_wide_gemm states
+why; the rollout adds a rank-256 product of the same kind)."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from gpu_helpers import GpuRun, check_against_oracle, log
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+
+@pytest.mark.parametrize("batch,beta,V,dtype", [(1, 8, 130, "bf16"), (2, 2, 4099, "bf16"), (3, 1, 4113, "bf16"),
+                                                (16, 3, 8196, "bf16"), (17, 8, 4097, "bf16"), (33, 2, 4099, "bf16"),
+                                                (17, 4, 4099, "f32"), (1, 1, 33, "f32")])
+def test_rollout_selection_edges(batch, beta, V, dtype):
+    cfg = synth.get_config("tiny").with_(dtype=dtype, vocab=V, batch=batch, branch=beta, ctx=16, ctx_from_hidden=False)
+    w = synth.make_weights(cfg, seed=41, gain_std=0.1)
+    # every third id is a copy of the one before it (exact ties), five ids and the tail past 4096 are NaN
+    nan_ids = np.r_[np.arange(5) * (V // 5), np.arange(4096, V)]
+    for name in ("lm_head", "w2"):
+        w[name][2::3][: len(w[name][1::3])] = w[name][1::3][: len(w[name][2::3])]
+    w["lm_head"][nan_ids] = np.nan
+    inp = synth.make_inputs(cfg, seed=41)
+    run = GpuRun(cfg, w, inp["max_ctx"], beta=beta)
+    gpu = run.step(inp)
+    assert gpu["err"] == 0
+    run.close()
+    fin = gpu["final_logits"]
+    nan = np.zeros(V, bool)
+    nan[nan_ids] = True
+    assert np.array_equal(np.isnan(fin), np.broadcast_to(nan, fin.shape))
+    for b in range(batch):
+        for j in range(cfg.depth):
+            ids, vals = oracle.top_beta(fin[b, j], beta)
+            np.testing.assert_array_equal(gpu["topk_ids"][b, j], ids, err_msg=f"row {b} depth {j + 1}")
+            np.testing.assert_array_equal(gpu["topk_vals"][b, j], vals.astype(np.float32))
+    rows = np.unique([0, batch // 2, batch - 1])
+    w["lm_head"][nan_ids] = 0.0
+    ref = oracle.draft_step(cfg, oracle.as_f64_weights(w), inp["anchor"][rows], inp["ctx_lens"][rows],
+                            inp["ctx_k"][:, rows], inp["ctx_v"][:, rows], beta, forced=gpu["topk_ids"][rows, :, 0])
+    sub = {k: gpu[k][rows] for k in ("topk_ids", "topk_vals", "hidden", "base_logits", "final_logits", "states")}
+    for d in (sub, ref):
+        for k in ("base_logits", "final_logits"):
+            d[k] = d[k].copy()
+            d[k][..., nan] = -1e9
+    log(f"batch {batch} beta {beta} V {V} {dtype}")
+    check_against_oracle(cfg, sub, ref, 3e-4, beta)
+
+
+@pytest.mark.parametrize("batch,V,dtype", [(1, 4099, "bf16"), (3, 4097, "bf16"), (17, 10242, "bf16"), (2, 4099, "f32")])
+def test_training_cross_entropy_edges(batch, V, dtype):
+    """Labels at the edges of waves' and workgroups' vocabulary slices, row counts that are not whole tiles."""
+    from oracle import train_oracle as to
+    from test_gpu_train import GAMMA, _check, _train
+    cfg = synth.get_config("tiny").with_(dtype=dtype, vocab=V, batch=batch, ctx=16, ctx_from_hidden=False)
+    w = synth.make_weights(cfg, seed=43, gain_std=0.1)
+    inp = synth.make_inputs(cfg, seed=43)
+    edges = np.array([0, V - 1, 15, 16, 79, 80, 255, 256, 639, 640, 1279, 1280, 4095, 4096, 31, 32], np.int32)
+    labels = np.resize(edges, (batch, cfg.depth)).astype(np.int32)
+    run = GpuRun(cfg, w, inp["max_ctx"], beta=1)
+    gpu = _train(run, inp, labels, 0.4)
+    run.close()
+    assert gpu["err"] == 0
+    ref = to.train_forward(cfg, oracle.as_f64_weights(w), inp["anchor"], inp["ctx_lens"], inp["ctx_k"], inp["ctx_v"],
+                           labels, 0.4, GAMMA)
+    _check(gpu, ref, 3e-4)
