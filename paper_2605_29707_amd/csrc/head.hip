@@ -18,7 +18,7 @@
 // A kernel boundary is the cheapest grid-wide handshake on this device (about
 // 1.6 us against about 4 us for a 256-workgroup spin barrier), so the
 // rollout is 3(B-1) launches and the final selection rather than one persistent
-// kernel (which one or two batch rows and branch 1 still run, below); the top-1
+// kernel (which up to eight batch rows and branch 1 run, below); the top-1
 // of each position is a 64-bit atomic max, so no launch merges lists inside
 // the loop.
 #include "common.h"
@@ -767,24 +767,29 @@ __global__ __launch_bounds__(64) void head_merge_kernel(HeadArgs h, int nlist) {
 }
 
 // ---------------------------------------------------------------------------
-// Persistent rollout (bf16 weights, r = 256, one or two batch rows, greedy or
-// sampled; three or four rows as one launch per pair): one
-// launch of at most one workgroup per CU runs all B-1 positions.  Each workgroup keeps its slice
-// of W2 resident for the whole rollout (kPersTiles tiles per wave, the last
-// one in LDS, the rest in registers: 77.8 MB over 238 workgroups at the Qwen3
-// vocabulary) and its rows of [W1[:, d:]; W_hh] in LDS, so W2 leaves HBM once
-// per step instead of once per position.
+// Persistent rollout (bf16 weights, r = 256, up to eight batch rows, greedy or
+// sampled): one launch of at most one workgroup per CU runs all B-1 positions
+// (137 us at one row of the Qwen3 vocabulary, 302 at four, which took 412 as two
+// launches of two rows).  Each workgroup keeps its slice of W2 for the whole rollout (kPersTiles tiles per wave, the last one in
+// LDS, the rest in registers: 77.8 MB over 238 workgroups) and its rows of [W1[:, d:]; W_hh] in LDS, so W2 leaves HBM once
+// per step instead of once per position.  Bound by the serial chain of a
+// position: the state's update, two exchanges between all workgroups and the
+// logits.  The rows of a batch are columns of the same products (u's high and
+// low parts, 2 x 8 of the tile's 16) and words of the same 64-byte exchange line,
+// polled by as many waves, so that eight rows cost one row's traffic; what grows
+// with the rows (about 4 us a position and row) is the state's update, which every
+// workgroup makes for itself rather than pay a third exchange.
 //
 // Workgroups exchange data through tagged 64-bit slots in the workspace
 // header (zeroed at every step), written with device-scope atomic stores and
-// polled with device-scope atomic loads by one wave; a slot is ready when its
+// polled with device-scope atomic loads by a wave per batch row; a slot is ready when its
 // top bits carry the position's tag, so a poll both waits and delivers:
-//   u slot [b][k]   (j << 32) | bits of u_j[k], written by the owner of row k
-//   key slot [b][g] (j << 50) | value(32) << 18 | (2^18 - 1 - id): workgroup
+//   u slot [k][b]   (j << 32) | bits of u_j[k], written by the owner of row k
+//   key slot [g][b] (j << 50) | value(32) << 18 | (2^18 - 1 - id): workgroup
 //                   g's top-1 for position j; the maximum over g is the argmax
 //                   under (value desc, id asc)
 // The hidden gates W_hh S for the next position go out as plain device-scope
-// stores while one wave waits for u; each thread waits for its own stores
+// stores while other waves wait for u; each thread waits for its own stores
 // before its workgroup publishes its key, so "all key slots ready" also means
 // "all gates stored".
 // Waits are bounded: a timeout sets DEV_BARRIER_TIMEOUT and the abort flag,
@@ -792,8 +797,11 @@ __global__ __launch_bounds__(64) void head_merge_kernel(HeadArgs h, int nlist) {
 // drafted token and its value of every position (no merge kernel).
 // ---------------------------------------------------------------------------
 constexpr int kPersWaves = 8, kPersTiles = 5, kPersKS = 8, kPersRegTiles = kPersTiles - 1;
-constexpr int kPersMaxBatch = 4;  // batch rows the persistent rollout takes (in launches of two)
+constexpr int kPersMaxBatch = kSlotStride;  // batch rows: a word of an exchange line each
+static_assert(kPersMaxBatch <= kPersWaves && 2 * kPersMaxBatch <= 16, "a polling wave and two tile columns per row");
 constexpr int kKeyIdBits = 18;
+// 64-lane loads of 16 bytes that bring a wave's tiles of L_base for BS rows
+constexpr int pers_lb_loads(int BS) { return (kPersTiles * BS * 4 + 63) / 64; }
 
 DEVI unsigned long long ld_slot(const unsigned long long *p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -808,13 +816,14 @@ DEVI unsigned long long pack_key50(float v, int id) {
 }
 DEVI int key50_id(unsigned long long k) { return (1 << kKeyIdBits) - 1 - (int)(k & ((1ull << kKeyIdBits) - 1)); }
 
-// Wave 0 polls `n` slots (kSlotStride words apart) until each carries `tag`
-// (top bits from `shift`); lane l holds slots l, l+64, ... in w[].  Returns
-// false on timeout (`limit` polls made, none complete) or when another
-// workgroup has aborted.
-template <int MAXQ>
-DEVI bool poll_tagged(const unsigned long long *slots, int n, unsigned long long tag, int shift,
-                      unsigned *abort_flag, int32_t *err, unsigned limit, unsigned long long (&w)[MAXQ]) {
+// The first BS waves poll `n` <= 256 lines (kSlotStride words apart, word b batch
+// row b's) until each word carries `tag` (top bits from `shift`): lane l of wave
+// w holds units e = (4 w + q) 64 + l in x[q], line e / BS, word e % BS (past the
+// last line or row: a copy).  Returns false on timeout (`limit` polls made, none
+// complete) or when another workgroup has aborted.
+template <int BS>
+DEVI bool poll_tagged(const unsigned long long *slots, int n, int bs, int wave, unsigned long long tag, int shift,
+                      unsigned *abort_flag, int32_t *err, unsigned limit, unsigned long long (&x)[4]) {
   const int lane = threadIdx.x & 63;
   unsigned polls = 0;
   while (true) {
@@ -826,16 +835,19 @@ DEVI bool poll_tagged(const unsigned long long *slots, int n, unsigned long long
       return false;
     }
 #pragma unroll
-    for (int q = 0; q < MAXQ; ++q) w[q] = ld_slot(slots + (size_t)min(lane + 64 * q, n - 1) * kSlotStride);
+    for (int q = 0; q < 4; ++q) {
+      const int e = (4 * wave + q) * 64 + lane;
+      x[q] = ld_slot(slots + (size_t)min(e / BS, n - 1) * kSlotStride + (BS == 1 ? 0 : min(e % BS, bs - 1)));
+    }
     bool ready = true;
 #pragma unroll
-    for (int q = 0; q < MAXQ; ++q) ready = ready && (w[q] >> shift) == tag;
+    for (int q = 0; q < 4; ++q) ready = ready && (x[q] >> shift) == tag;
     if (__all(ready)) return true;
     if ((polls & 63) == 0 && __hip_atomic_load(abort_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return false;
   }
 }
 
-// BS: the largest batch the instantiation serves (1 or 2; arrays sized by it);
+// BS: the largest batch the instantiation serves (1, 2, 4 or 8; arrays sized by it);
 // DBG: the final logits are also written out (h.final_logits);
 // SAMPLE: temperature sampling, the selection key is L / T + Gumbel noise
 // (Philox stream RNG_DRAFT, as in the launch-pair rollout) and the reported
@@ -859,15 +871,27 @@ __global__ __launch_bounds__(kPersWaves * 64) void head_persist_kernel(HeadArgs 
   float *S = (float *)(rows + (size_t)nr * nchunk);     // [bs][ds] the state
   u32x4 *us = (u32x4 *)(S + (size_t)bs * ds);           // [KS][64] u as B fragments
   u32x4 *w2s = us + kPersKS * 64;                       // [waves][KS][64] each wave's last W2 tile
-  float4 *lbs = (float4 *)(w2s + kPersWaves * kPersKS * 64);  // [waves][tiles][64] this lane's L_base values
+  constexpr int NI = pers_lb_loads(BS);
+  float4 *lbs = (float4 *)(w2s + kPersWaves * kPersKS * 64);  // [waves][NI * 64] L_base, see below
   const int nu = (r + G - 1) / G;                              // u rows per workgroup: k < nu (R < r)
-  float *P_s = (float *)(lbs + kPersWaves * kPersTiles * 64);  // [depth][bs][nu] W1[:, :d] H at the u rows
-  // each lane's best of its tiles: [wave][row group g][column]
-  __shared__ float best_v[kPersWaves][4][16], best_r[SAMPLE ? kPersWaves : 1][4][16];
-  __shared__ int best_i[kPersWaves][4][16];
-  __shared__ int win_id[SAMPLE ? 64 : 1][BS];  // workgroup 0: each position's drafted token
-  __shared__ int ys[kFusedBatch];
-  __shared__ int s_ok;
+  float *P_s = (float *)(lbs + kPersWaves * NI * 64);  // [depth][bs][nu] W1[:, :d] H at the u rows
+  // each lane's best of its tiles, value, id and raw logit by [row group g][batch
+  // row]: over the wave's own part of lbs, once its values are used
+  auto best_at = [&](int w, int field, int gg, int b) { return (float *)(lbs + w * NI * 64) + (field * 4 + gg) * BS + b; };
+  __shared__ unsigned long long s_key[BS][BS];  // polling wave's best key of each batch row
+  __shared__ int ys[BS], s_ok[BS];
+  auto all_ok = [&] {
+    int ok = 1;
+#pragma unroll
+    for (int w = 0; w < BS; ++w) ok &= s_ok[w];
+    return ok != 0;
+  };
+  auto key_of = [&](int b) {
+    unsigned long long k = s_key[0][b];
+#pragma unroll
+    for (int w = 1; w < BS; ++w) k = s_key[w][b] > k ? s_key[w][b] : k;
+    return k;
+  };
   const WT *w1 = (const WT *)h.w1, *whh = (const WT *)h.w_hh;
   const int tile0 = (blockIdx.x * kPersWaves + wave) * kPersTiles;  // this wave's tiles tile0 + q
 
@@ -893,7 +917,7 @@ __global__ __launch_bounds__(kPersWaves * 64) void head_persist_kernel(HeadArgs 
     rows[e] = *(const u32x4 *)(src + (size_t)ch * EPL);
   }
   for (int e = tid; e < bs * ds; e += kPersWaves * 64) S[e] = 0.f;
-  // the u fragments' unused columns (2 bs and up) stay zero for the whole launch
+  // the u fragments' unused columns stay zero for the whole launch
   for (int e = tid; e < kPersKS * 64; e += kPersWaves * 64) us[e] = u32x4{0u, 0u, 0u, 0u};
   for (int e = tid; e < depth * bs * nu; e += kPersWaves * 64) {
     const int k = e % nu, b = (e / nu) % bs, jj = e / (nu * bs);
@@ -905,7 +929,7 @@ __global__ __launch_bounds__(kPersWaves * 64) void head_persist_kernel(HeadArgs 
   // state items: two indices of one batch row each, so that all eight waves
   // share the GRU's transcendental arithmetic (one item per thread at one
   // batch row and d_s = 1024)
-  constexpr int GE = 2;
+  constexpr int GE = 2, GU = BS < 2 ? BS : 2;
   const int nit = bs * ds / GE;
   for (int j = 1; j <= depth; ++j) {
     // the thread index, opaque to the compiler once per position: addresses
@@ -920,54 +944,62 @@ __global__ __launch_bounds__(kPersWaves * 64) void head_persist_kernel(HeadArgs 
       int y;
       if (j == 1) y = clamp_token(h.anchor[tj], V, h.err);
       else if (h.forced) y = clamp_token(h.forced[(size_t)tj * depth + (j - 2)], V, h.err);
-      else y = ys[tj];
+      else y = min(max(key50_id(key_of(tj)), 0), V - 1);
       ys[tj] = y;
     }
     __syncthreads();
-    // L_base of this lane's row and tiles, straight from memory into LDS (no
-    // registers held).  Issued after the barrier above, whose wait would
-    // otherwise take in its whole latency, and alongside the GRU's loads: the
-    // barrier after the GRU finds both complete.
-    {
-      const int bb = min(cc, bs - 1);
+    // L_base of this wave's tiles, straight from memory into LDS (no registers
+    // held): 16 bytes for (tile q, row b, group g) at (q BS + b) 4 + g.
+    // Issued after the barrier above, whose wait would otherwise take in its whole
+    // latency, and alongside the GRU's loads: the barrier after the GRU finds
+    // both complete.
 #pragma unroll
-      for (int q = 0; q < kPersTiles; ++q) {
-        const int t = min(tile0 + q, NT - 1);
-        __builtin_amdgcn_global_load_lds(
-            (const void *)(h.Lbase + ((size_t)bb * depth + (j - 1)) * h.ldl + t * 16 + 4 * g),
-            (void __attribute__((address_space(3))) *)(lbs + ((size_t)wave * kPersTiles + q) * 64), 16, 0, 0);
-      }
+    for (int i = 0; i < NI; ++i) {
+      const int e = i * 64 + lane_j;
+      const int t = min(tile0 + min(e / (4 * BS), kPersTiles - 1), NT - 1), bb = min((e >> 2) % BS, bs - 1);
+      __builtin_amdgcn_global_load_lds(
+          (const void *)(h.Lbase + ((size_t)bb * depth + (j - 1)) * h.ldl + t * 16 + 4 * (e & 3)),
+          (void __attribute__((address_space(3))) *)(lbs + ((size_t)wave * NI + i) * 64), 16, 0, 0);
     }
     // ---- S_{j-1} = GRU(E[y_{j-1}], S_{j-2}) in place
-    for (int it = tid; it < nit; it += kPersWaves * 64) {
-      const int b = it / (ds / GE), i = (it % (ds / GE)) * GE;
-      // W_hh S_{j-2} + b_hh (stored by the previous position's row owners) and the G row, loaded together
-      float ghv[3][GE];
-      {
+    for (int it0 = tid; it0 < nit; it0 += kPersWaves * 64 * GU) {
+      // W_hh S_{j-2} + b_hh (stored by the previous position's row owners) and
+      // the G rows of GU items, loaded together (past the last one: a copy)
+      float2 gh[GU][3], gi[GU][3];
+#pragma unroll
+      for (int u = 0; u < GU; ++u) {
+        const int it = min(it0 + u * kPersWaves * 64, nit - 1);
+        const int b = it / (ds / GE), i = (it % (ds / GE)) * GE;
         const float *gb = h.ghbuf + (size_t)((j - 1) & 1) * bs * 3 * ds + (size_t)b * 3 * ds + i;
+        const float *gy = h.gtab + (size_t)ys[b] * 3 * ds + i;
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
+          // (8-byte aligned: i and d_s are even)
           const float2 c0 = *(const float2 *)(h.bhh + q * ds + i);  // the gates at j = 1 (S = 0)
-          const float v0 = ld_coherent(gb + q * ds), v1 = ld_coherent(gb + q * ds + 1);
-          ghv[q][0] = j > 1 ? v0 : c0.x;
-          ghv[q][1] = j > 1 ? v1 : c0.y;
+          const float2 v = __builtin_bit_cast(float2, ld_slot((const unsigned long long *)(gb + q * ds)));
+          gh[u][q] = j > 1 ? v : c0;
+          gi[u][q] = *(const float2 *)(gy + q * ds);
         }
       }
-      const float *gy = h.gtab + (size_t)ys[b] * 3 * ds + i;
-      const float2 g0 = *(const float2 *)gy, g1 = *(const float2 *)(gy + ds), g2 = *(const float2 *)(gy + 2 * ds);
-      const float gi[3][GE] = {{g0.x, g0.y}, {g1.x, g1.y}, {g2.x, g2.y}};
-      float2 s2 = *(const float2 *)(S + (size_t)b * ds + i);
-      const float hold[GE] = {s2.x, s2.y};
-      float out[GE];
 #pragma unroll
-      for (int e = 0; e < GE; ++e) {
-        const float rg = sigm(gi[0][e] + ghv[0][e]), zg = sigm(gi[1][e] + ghv[1][e]);
-        const float ng = tanhf(fmaf(rg, ghv[2][e], gi[2][e]));
-        out[e] = gru_mix(zg, ng, hold[e]);
+      for (int u = 0; u < GU; ++u) {
+        const int it = it0 + u * kPersWaves * 64;
+        if (GU > 1 && it >= nit) break;
+        const int b = it / (ds / GE), i = (it % (ds / GE)) * GE;
+        float2 s2 = *(const float2 *)(S + (size_t)b * ds + i);
+        const float hold[GE] = {s2.x, s2.y};
+        float out[GE];
+#pragma unroll
+        for (int e = 0; e < GE; ++e) {
+          auto at = [&](const float2 &v) { return e == 0 ? v.x : v.y; };
+          const float rg = sigm(at(gi[u][0]) + at(gh[u][0])), zg = sigm(at(gi[u][1]) + at(gh[u][1]));
+          const float ng = tanhf(fmaf(rg, at(gh[u][2]), at(gi[u][2])));
+          out[e] = gru_mix(zg, ng, hold[e]);
+        }
+        s2 = make_float2(out[0], out[1]);
+        *(float2 *)(S + (size_t)b * ds + i) = s2;
+        if (blockIdx.x == 0 && h.states) *(float2 *)(h.states + ((size_t)b * depth + (j - 1)) * ds + i) = s2;
       }
-      s2 = make_float2(out[0], out[1]);
-      *(float2 *)(S + (size_t)b * ds + i) = s2;
-      if (blockIdx.x == 0 && h.states) *(float2 *)(h.states + ((size_t)b * depth + (j - 1)) * ds + i) = s2;
     }
     __syncthreads();
     // ---- this workgroup's u rows against S_{j-1} into the tagged u slots
@@ -996,16 +1028,17 @@ __global__ __launch_bounds__(kPersWaves * 64) void head_persist_kernel(HeadArgs 
       if (lane == 0) {
         const float x = P_s[((size_t)(j - 1) * bs + b) * nu + k] + acc;
         const float u = x / (1.f + expf(-x));
-        st_slot(h.uslot + ((size_t)b * r + R) * kSlotStride, ((unsigned long long)j << 32) | __float_as_uint(u));
+        st_slot(h.uslot + (size_t)R * kSlotStride + b, ((unsigned long long)j << 32) | __float_as_uint(u));
       }
     }
     // ---- gates of the next position, W_hh S_{j-1} + b_hh (plain device-scope
-    // stores), by waves 1.. while wave 0 waits for u; the stores are waited for
-    // before this workgroup publishes its top-1, so "every key slot of position
+    // stores), by the waves that do not wait for u (all of them first where
+    // every wave will); the stores are waited for before this workgroup publishes its top-1, so "every key slot of position
     // j ready" also means "every gate of position j + 1 stored"
-    if (wave > 0 && j < depth) {
+    constexpr int W0 = BS < kPersWaves ? BS : 0;
+    if (wave >= W0 && j < depth) {
       float *gh_out = h.ghbuf + (size_t)(j & 1) * bs * 3 * ds;
-      for (int k = wave - 1; k < nr; k += kPersWaves - 1) {
+      for (int k = wave - W0; k < nr; k += kPersWaves - W0) {
         const int R = blockIdx.x + k * G;
         if (R < r || R >= nrows_all) continue;  // wave-uniform
         float accb[BS];
@@ -1040,32 +1073,31 @@ __global__ __launch_bounds__(kPersWaves * 64) void head_persist_kernel(HeadArgs 
         }
       }
     }
-    // ---- wait for u (wave 0 polls all u slots; the slots deliver the values)
-    if (wave == 0) {
-      unsigned long long w[4 * BS];
-      const bool ok = poll_tagged<4 * BS>(h.uslot, bs * r, (unsigned long long)j, 32, h.abort_flag, h.err, h.poll_limit, w);
+    // ---- wait for u (the slots deliver the values)
+    if (wave < BS) {
+      unsigned long long w[4];
+      const bool ok = poll_tagged<BS>(h.uslot, r, bs, wave, (unsigned long long)j, 32, h.abort_flag, h.err, h.poll_limit, w);
       // u goes straight into the B fragments of the logits product: element
       // (b, k) sits at k-step k / 32, lane 16 ((k / 8) mod 4) + column, slot k mod 8,
       // where column b holds the bf16 high part of batch row b's u and column
-      // bs + b its low part (u - hi).  One product per tile and k-step then
+      // BS + b its low part (u - hi).  One product per tile and k-step then
       // carries both; the two columns are summed after the k loop.
       unsigned short *us16 = (unsigned short *)us;
 #pragma unroll
-      for (int q = 0; q < 4 * BS; ++q) {
-        const int e = lane_j + 64 * q;  // slot b * r + k (r = 256)
-        if (BS == 1 || e < bs * r) {
+      for (int q = 0; q < 4; ++q) {
+        const int e = (4 * wave + q) * 64 + lane_j, k = e / BS, b = e % BS;  // r = 256 lines: 4 units a lane
+        if (BS <= 2 || b < bs) {
           const float u = __uint_as_float((uint32_t)(w[q] & 0xffffffffu));
           const __bf16 hi = (__bf16)u, lo = (__bf16)(u - (float)hi);
-          const int b = e >> 8, k = e & 255;
           const int at = ((k >> 5) * 64 + ((k >> 3) & 3) * 16 + b) * 8 + (k & 7);
           us16[at] = __builtin_bit_cast(unsigned short, hi);
-          us16[at + bs * 8] = __builtin_bit_cast(unsigned short, lo);
+          us16[at + BS * 8] = __builtin_bit_cast(unsigned short, lo);
         }
       }
-      if (lane == 0) s_ok = ok;
+      if (lane == 0) s_ok[wave] = ok;
     }
     __syncthreads();
-    if (!s_ok) return;
+    if (!all_ok()) return;
     // ---- logits: u as B fragments against the resident W2
     floatx4 acc[kPersTiles];
 #pragma unroll
@@ -1080,7 +1112,7 @@ __global__ __launch_bounds__(kPersWaves * 64) void head_persist_kernel(HeadArgs 
           __builtin_bit_cast(bf16x8, w2s[((size_t)wave * kPersKS + s) * 64 + lane]), xb, acc[kPersRegTiles], 0, 0, 0);
     }
     // lane (g, cc) holds vocabulary ids 16 (tile0 + q) + 4 g + e: column cc < bs
-    // adds the low-part column of lane cc + bs (a row shift within 16 lanes).
+    // adds the low-part column of lane cc + BS (a row shift within 16 lanes).
     // Each tile's four corrected logits are formed, written (DBG) and folded
     // into the running best before the next tile's, so only one tile's values
     // are live at a time.
@@ -1094,15 +1126,14 @@ __global__ __launch_bounds__(kPersWaves * 64) void head_persist_kernel(HeadArgs 
       float *fl = DBG ? h.final_logits + ((size_t)min(cc, bs - 1) * depth + (j - 1)) * V : nullptr;
 #pragma unroll
       for (int q = 0; q < kPersTiles; ++q) {
-        const float4 l4 = lbs[((size_t)wave * kPersTiles + q) * 64 + lane];
+        const float4 l4 = lbs[wave * NI * 64 + (q * BS + (cc & (BS - 1))) * 4 + g];
         const float lv[4] = {l4.x, l4.y, l4.z, l4.w};
         float val[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const int a = __float_as_int(acc[q][e]);
-          const int lo1 = __builtin_amdgcn_update_dpp(0, a, 0x101, 0xf, 0xf, false);  // lane + 1
-          const int lo2 = __builtin_amdgcn_update_dpp(0, a, 0x102, 0xf, 0xf, false);  // lane + 2
-          val[e] = lv[e] + (acc[q][e] + __int_as_float(BS == 1 || bs == 1 ? lo1 : lo2));
+          const int lo = __builtin_amdgcn_update_dpp(0, a, 0x100 + BS, 0xf, 0xf, false);  // lane + BS
+          val[e] = lv[e] + (acc[q][e] + __int_as_float(lo));
         }
         if (DBG && rowok) {  // the final logits (output of sampled drafting, debug output otherwise)
           const int n = (tile0 + q) * 16 + 4 * g;
@@ -1115,7 +1146,7 @@ __global__ __launch_bounds__(kPersWaves * 64) void head_persist_kernel(HeadArgs 
           }
         }
         Philox4 noise = {{0u, 0u, 0u, 0u}};
-        if (SAMPLE) noise = rng_block(h.seed_lo, h.seed_hi, RNG_DRAFT, h.row0 + cc, j, (tile0 + q) * 4 + g);
+        if (SAMPLE) noise = rng_block(h.seed_lo, h.seed_hi, RNG_DRAFT, cc, j, (tile0 + q) * 4 + g);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const int n = (tile0 + q) * 16 + 4 * g + e;
@@ -1129,22 +1160,25 @@ __global__ __launch_bounds__(kPersWaves * 64) void head_persist_kernel(HeadArgs 
       }
       // every lane's best goes to LDS as it is (no cross-row exchange here):
       // the merge below takes 32 candidates per batch row
-      // (lanes of columns past the batch are written too and never read)
-      (&best_v[wave][0][0])[lane_j] = bv;
-      (&best_i[wave][0][0])[lane_j] = bi;
-      if (SAMPLE) (&best_r[SAMPLE ? wave : 0][0][0])[lane_j] = br;
+      __asm__ volatile("" ::: "memory");  // the wave's L_base values are read before they are written over
+      if (cc < BS) {
+        *best_at(wave, 0, g, cc) = bv;
+        *best_at(wave, 1, g, cc) = __int_as_float(bi);
+        if (SAMPLE) *best_at(wave, 2, g, cc) = br;
+      }
     }
     __builtin_amdgcn_s_waitcnt(0);  // this thread's gate stores are done
     __syncthreads();                // ... and every thread's
-    if (wave == 0) {
-      // wave 0 merges the 32 candidates (8 waves x 4 row groups) of batch row b
-      // in lanes 32 b ..: rotations within each 16-lane row, then across the
-      // two rows of a batch row
-      const int bb = lane_j >> 5, c = lane_j & 31;
+    if (wave < (BS + 1) / 2) {
+      // wave w merges the 32 candidates (8 waves x 4 row groups) of batch rows
+      // 2 w and 2 w + 1, 32 lanes each: rotations within each 16-lane row, then
+      // across the two rows of a batch row
+      const int bb = 2 * wave + (lane_j >> 5), c = lane_j & 31;
       const bool have = bb < bs;
-      float v = have ? best_v[c >> 2][c & 3][bb] : -INFINITY;
-      float raw = (SAMPLE && have) ? best_r[SAMPLE ? c >> 2 : 0][c & 3][bb] : 0.f;
-      int id = have ? best_i[c >> 2][c & 3][bb] : INT_MAX;
+      const int bc = min(bb, BS - 1);
+      float v = have ? *best_at(c >> 2, 0, c & 3, bc) : -INFINITY;
+      float raw = (SAMPLE && have) ? *best_at(c >> 2, 2, c & 3, bc) : 0.f;
+      int id = have ? __float_as_int(*best_at(c >> 2, 1, c & 3, bc)) : INT_MAX;
       auto step = [&](float ov, int oi, float orw) {
         const bool take = better(ov, oi, v, id);
         v = take ? ov : v;
@@ -1157,7 +1191,7 @@ __global__ __launch_bounds__(kPersWaves * 64) void head_persist_kernel(HeadArgs 
       step(row_ror<1>(v), row_ror<1>(id), SAMPLE ? row_ror<1>(raw) : 0.f);
       // the odd rows take the best of the row before them (DPP row_bcast:15:
       // lane 15 of rows 0 and 2 to every lane of rows 1 and 3), so lanes 16 and
-      // 48 hold the workgroup's best of batch rows 0 and 1
+      // 48 hold the workgroup's best of the wave's two batch rows
       step(__int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), 0x142, 0xa, 0xf, false)),
            __builtin_amdgcn_update_dpp(id, id, 0x142, 0xa, 0xf, false),
            SAMPLE ? __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(raw), __float_as_int(raw), 0x142, 0xa, 0xf, false))
@@ -1169,7 +1203,7 @@ __global__ __launch_bounds__(kPersWaves * 64) void head_persist_kernel(HeadArgs 
         }
         // an empty slice (no valid id) publishes the smallest key
         const unsigned long long key = id == INT_MAX ? 0ull : pack_key50(v, id);
-        st_slot(h.kslot + ((size_t)bb * G + blockIdx.x) * kSlotStride, ((unsigned long long)j << 50) | key);
+        st_slot(h.kslot + (size_t)blockIdx.x * kSlotStride + bb, ((unsigned long long)j << 50) | key);
       }
     }
     // ---- wait for every workgroup's top-1: the maximum key is y_j.  Also the
@@ -1177,43 +1211,45 @@ __global__ __launch_bounds__(kPersWaves * 64) void head_persist_kernel(HeadArgs 
     // still polls this position's, so it runs with forced tokens as well.
     // Workgroup 0 reports (y_j, its value) for every position, the last included.
     if (j < depth || blockIdx.x == 0) {
-      if (wave == 0) {
-        unsigned long long w[4 * BS];
-        const bool ok = poll_tagged<4 * BS>(h.kslot, bs * G, (unsigned long long)j, 50, h.abort_flag, h.err, h.poll_limit, w);
-        // lane holds slots lane + 64 q: slot e = b * G + g
-        for (int b = 0; b < bs; ++b) {
-          unsigned long long best = 0;
+      if (wave < BS) {
+        unsigned long long w[4];
+        const bool ok = poll_tagged<BS>(h.kslot, G, bs, wave, (unsigned long long)j, 50, h.abort_flag, h.err, h.poll_limit, w);
+        unsigned long long best = 0;  // of batch row lane % BS, in lines of this wave
 #pragma unroll
-          for (int q = 0; q < 4 * BS; ++q) {
-            const int e = lane + 64 * q;
-            const unsigned long long k = w[q] & ((1ull << 50) - 1);
-            if (e >= b * G && e < (b + 1) * G && e < bs * G) best = k > best ? k : best;
-          }
+        for (int q = 0; q < 4; ++q) {
+          const unsigned long long k = w[q] & ((1ull << 50) - 1);
+          best = k > best ? k : best;
+        }
+        if (BS == 1) {
           best = wave_max_u64(best);
-          if (lane == 0) {
-            const int id = key50_id(best);
-            ys[b] = min(max(id, 0), V - 1);
-            if (blockIdx.x == 0) {
-              const uint32_t u = (uint32_t)(best >> kKeyIdBits);
-              h.topk_ids[(size_t)b * depth + (j - 1)] = id;
-              if (SAMPLE) win_id[SAMPLE ? j - 1 : 0][b] = id;
-              else h.topk_vals[(size_t)b * depth + (j - 1)] = __uint_as_float((u & 0x80000000u) ? (u ^ 0x80000000u) : ~u);
-            }
+        } else {
+#pragma unroll
+          for (int o = 32; o >= BS; o >>= 1) {
+            const unsigned long long k = __shfl_xor(best, o, 64);
+            best = k > best ? k : best;
           }
         }
-        if (lane == 0) s_ok = ok;
+        if (lane < BS) s_key[wave][lane] = best;
+        if (lane == 0) s_ok[wave] = ok;
       }
       __syncthreads();
-      if (!s_ok) return;
+      if (!all_ok()) return;
+      if (blockIdx.x == 0 && tid < bs) {
+        const unsigned long long best = key_of(tid);
+        const uint32_t u = (uint32_t)(best >> kKeyIdBits);
+        h.topk_ids[(size_t)tid * depth + (j - 1)] = key50_id(best);
+        if (!SAMPLE)
+          h.topk_vals[(size_t)tid * depth + (j - 1)] = __uint_as_float((u & 0x80000000u) ? (u ^ 0x80000000u) : ~u);
+      }
     }
   }
   if (SAMPLE && blockIdx.x == 0) {  // reported values: the drafted tokens' raw logits, from their owners
-    __syncthreads();
+    __syncthreads();                // (the ids were stored by this workgroup's first threads)
     for (int e = tid; e < depth * bs; e += kPersWaves * 64) {
-      const int jj = e / bs, b = e % bs;
-      const int id = win_id[SAMPLE ? jj : 0][b];
+      const int b = e / depth, jj = e % depth;
+      const int id = __hip_atomic_load(h.topk_ids + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       const int owner = min(max(id, 0), V - 1) / (16 * kPersWaves * kPersTiles);
-      h.topk_vals[(size_t)b * depth + jj] = ld_coherent(h.praw + ((size_t)jj * bs + b) * h.GC + owner);
+      h.topk_vals[e] = ld_coherent(h.praw + ((size_t)jj * bs + b) * h.GC + owner);
     }
   }
 }
@@ -1224,34 +1260,28 @@ static int persist_groups(const Dims &D) {
   return ((D.V + 15) / 16 + kPersWaves * kPersTiles - 1) / (kPersWaves * kPersTiles);
 }
 
-// The persistent kernel for one or two batch rows of `h` (D.bs <= 2): checks
-// the shapes and the device, and picks the instantiation and its LDS size.
+template <int BS>
+static const void *persist_fn(bool dbg, bool smp) {
+  if (dbg) return smp ? (const void *)head_persist_kernel<BS, true, true> : (const void *)head_persist_kernel<BS, true, false>;
+  return smp ? (const void *)head_persist_kernel<BS, false, true> : (const void *)head_persist_kernel<BS, false, false>;
+}
+
+// Checks the shapes and the device, and picks the instantiation and its LDS size.
 static bool persist_plan(const HeadArgs &h, int n_cu, const void **fn, size_t *lds_out, int *nr_out) {
   const Dims &D = h.D;
-  if (!D.bf16 || D.r != kPersKS * 32 || D.bs < 1 || D.bs > 2 || h.beta != 1 || D.ds % 32 || D.ds > 256 * 8 ||
+  if (!D.bf16 || D.r != kPersKS * 32 || D.bs < 1 || D.bs > kPersMaxBatch || h.beta != 1 || D.ds % 32 || D.ds > 256 * 8 ||
       D.V >= (1 << kKeyIdBits) || D.B > 64 || !h.uslot || !h.kslot || !h.abort_flag || (h.sample && !h.praw))
     return false;
   const int G = persist_groups(D);
-  // every workgroup must own a u row (its u slot doubles as its "gates stored" signal),
-  // and the polls cover at most 4 * kFusedBatch slots per lane
-  if (G > h.GC || G > n_cu || G > D.r || G > 256) return false;  // polls: 4 slots per lane per batch row
-  const int nr = (D.r + 3 * D.ds + G - 1) / G;
+  if (G > h.GC || G > n_cu || G > D.r) return false;  // (the polls cover r = 256 lines)
+  const int nr = (D.r + 3 * D.ds + G - 1) / G, BS = D.bs <= 2 ? D.bs : (D.bs <= 4 ? 4 : 8);
   const size_t lds = (size_t)nr * (D.ds / 8) * 16 + sizeof(float) * (size_t)D.bs * D.ds +
                      sizeof(u32x4) * kPersKS * 64 + sizeof(u32x4) * kPersWaves * kPersKS * 64 +
-                     sizeof(float4) * kPersWaves * kPersTiles * 64 +
+                     sizeof(float4) * kPersWaves * pers_lb_loads(BS) * 64 +
                      sizeof(float) * (size_t)(D.B - 1) * D.bs * ((D.r + G - 1) / G);
   if (lds > 160 * 1024) return false;
   const bool dbg = h.final_logits != nullptr, smp = h.sample != 0;
-  switch ((D.bs == 1 ? 0 : 4) + (dbg ? 2 : 0) + (smp ? 1 : 0)) {
-    case 0: *fn = (const void *)head_persist_kernel<1, false, false>; break;
-    case 1: *fn = (const void *)head_persist_kernel<1, false, true>; break;
-    case 2: *fn = (const void *)head_persist_kernel<1, true, false>; break;
-    case 3: *fn = (const void *)head_persist_kernel<1, true, true>; break;
-    case 4: *fn = (const void *)head_persist_kernel<2, false, false>; break;
-    case 5: *fn = (const void *)head_persist_kernel<2, false, true>; break;
-    case 6: *fn = (const void *)head_persist_kernel<2, true, false>; break;
-    default: *fn = (const void *)head_persist_kernel<2, true, true>; break;
-  }
+  *fn = BS == 1 ? persist_fn<1>(dbg, smp) : (BS == 2 ? persist_fn<2>(dbg, smp) : (BS == 4 ? persist_fn<4>(dbg, smp) : persist_fn<8>(dbg, smp)));
   if (hipFuncSetAttribute(*fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
     (void)hipGetLastError();
     return false;
@@ -1272,54 +1302,20 @@ static bool persist_plan(const HeadArgs &h, int n_cu, const void **fn, size_t *l
   return true;
 }
 
-// The rollout of `h` with the batch rows [b0, b0 + nb) only: every per-row
-// pointer moves to row b0 (the exchange slots too, so each launch has slots
-// of its own, zeroed with the step's header), the batch becomes nb.
-static HeadArgs rows_of(const HeadArgs &h, int b0, int nb) {
-  HeadArgs a = h;
-  const int depth = h.D.B - 1;
-  a.D.bs = nb;
-  a.row0 = h.row0 + b0;
-  a.anchor = h.anchor + b0;
-  if (h.forced) a.forced = h.forced + (size_t)b0 * depth;
-  a.topk_ids = h.topk_ids + (size_t)b0 * depth * h.beta;
-  a.topk_vals = h.topk_vals + (size_t)b0 * depth * h.beta;
-  if (h.final_logits) a.final_logits = h.final_logits + (size_t)b0 * depth * h.D.V;
-  if (h.states) a.states = h.states + (size_t)b0 * depth * h.D.ds;
-  a.P = h.P + (size_t)b0 * depth * h.ldp;
-  a.Lbase = h.Lbase + (size_t)b0 * depth * h.ldl;
-  a.uslot = h.uslot + (size_t)b0 * h.D.r * kSlotStride;
-  a.kslot = h.kslot + (size_t)b0 * h.GC * kSlotStride;
-  return a;
-}
-
 bool launch_head_persistent(const HeadArgs &h, int n_cu, hipStream_t st) {
-  const Dims &D = h.D;
-  // one or two batch rows per launch (more would spill the per-lane state);
-  // three or four rows run as one launch per pair of rows, one after the
-  // other (each re-reads W2: 2 x ~140 us against ~480 us for the launch-pair
-  // rollout of four rows, measured at the Qwen3-4B shape); larger batches
-  // run the launch-pair rollout
-  if (D.bs < 1 || D.bs > kPersMaxBatch) return false;
-  const int npair = (D.bs + 1) / 2;
-  const void *fn[2];
-  size_t lds[2];
-  int nr[2];
-  for (int p = 0; p < npair; ++p) {  // every launch's plan first: all or nothing
-    const int nb = std::min(2, D.bs - 2 * p);
-    if (!persist_plan(rows_of(h, 2 * p, nb), n_cu, &fn[nb - 1], &lds[nb - 1], &nr[nb - 1])) return false;
-  }
-  for (int p = 0; p < npair; ++p) {
-    const int nb = std::min(2, D.bs - 2 * p);
-    HeadArgs a = rows_of(h, 2 * p, nb);
-    int nrv = nr[nb - 1];
-    void *args[] = {&a, &nrv};
-    if (hipLaunchKernel(fn[nb - 1], dim3(persist_groups(a.D)), dim3(kPersWaves * 64), args, lds[nb - 1], st) != hipSuccess) {
-      // (a failure after the first pair leaves nothing wrong behind: the
-      // launch-pair rollout that follows rewrites every row's outputs)
-      (void)hipGetLastError();
-      return false;
-    }
+  // Up to eight batch rows, as many as an exchange line has words.  A drafting
+  // step of the 4B shape with 256 tokens of context, persistent against launch
+  // by launch: 715 and 935 us at 2 rows, 926 and 1057 at 4, 1088 and 1205 at 5,
+  // 1214 and 1273 at 8 (sampled 1294 and 1315): the gap closes with the rows.
+  const void *fn;
+  size_t lds;
+  int nr;
+  if (!persist_plan(h, n_cu, &fn, &lds, &nr)) return false;
+  HeadArgs a = h;
+  void *args[] = {&a, &nr};
+  if (hipLaunchKernel(fn, dim3(persist_groups(a.D)), dim3(kPersWaves * 64), args, lds, st) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
   }
   return true;
 }

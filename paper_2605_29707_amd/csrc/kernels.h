@@ -129,10 +129,11 @@ bool attn_supported(int nq, int nkv, int B);
 
 // ---- Domino head rollout (head.hip)
 constexpr uint32_t kDefaultPollLimit = 1u << 22;  // polls a rollout wait makes before it gives up
-// Spacing of the persistent rollout's exchange slots, in 64-bit words: one
-// slot per 64-byte sector.  Every workgroup polls every slot; packed eight to
-// a sector, the polls of all workgroups queue on a handful of sectors and an
-// all-to-all round takes about 2.5 us, against about 1.6 us at this spacing.
+// Spacing of the persistent rollout's exchange lines, in 64-bit words: a
+// 64-byte sector holds one index of all batch rows (up to eight).  Every
+// workgroup polls every line; with eight indices of one row to a sector the
+// polls of all workgroups queue on a handful of sectors and an all-to-all round
+// takes about 2.5 us, against about 1.6 us at this spacing.
 constexpr int kSlotStride = 8;
 
 struct HeadArgs {
@@ -171,8 +172,8 @@ struct HeadArgs {
   int32_t *err;
   int GC;                // workgroups of the logits kernel
   // persistent rollout exchange (workspace header, zeroed at every step):
-  // u slots [bs][r] and per-workgroup best-key slots [bs][GC], each a 64-bit
-  // word tagged with the position, kSlotStride words apart; abort flag of its
+  // u lines [r] and per-workgroup best-key lines [GC], a batch row a 64-bit
+  // word tagged with the position, a line kSlotStride words; abort flag of its
   // bounded waits
   unsigned long long *uslot, *kslot;
   unsigned *abort_flag;
@@ -181,7 +182,6 @@ struct HeadArgs {
   const void *whh_p, *w1s_p;
   int whh_NT, whh_KS, w1s_NT, w1s_KS;
   float *lout = nullptr;  // beta > 1: where the corrected logits replace L_base (set by launch_head)
-  int row0 = 0;  // batch row of this launch's first row (the Philox stream's row index)
 };
 // Batches up to this run the fused state kernel (one launch a position instead of
 // two): its workgroups each repeat the elementwise update of every row, which at
@@ -190,10 +190,9 @@ constexpr int kHeadFusedBatch = 2;
 int head_logits_grid(const Dims &D);
 int head_best_slots();
 hipError_t launch_head(const HeadArgs &h, hipStream_t st);
-// The persistent rollout where the shapes allow it (bf16, r = 256, batch <= 4,
+// The persistent rollout where the shapes allow it (bf16, r = 256, batch <= 8,
 // branch 1, a grid that fits the device at one workgroup per CU, vocabulary
-// < 2^18): one launch per pair of batch rows; returns false (nothing launched)
-// otherwise.
+// < 2^18); returns false (nothing launched) otherwise.
 bool launch_head_persistent(const HeadArgs &h, int n_cu, hipStream_t st);
 // the state recurrence of every position, teacher-forced (no logits): u into
 // ubuf as above, or with skip_u only the states into `states`

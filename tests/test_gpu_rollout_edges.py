@@ -75,3 +75,23 @@ def test_training_cross_entropy_edges(batch, V, dtype):
     ref = to.train_forward(cfg, oracle.as_f64_weights(w), inp["anchor"], inp["ctx_lens"], inp["ctx_k"], inp["ctx_v"],
                            labels, 0.4, GAMMA)
     _check(gpu, ref, 3e-4)
+
+
+@pytest.mark.parametrize("batch", [5, 7, 8])
+def test_persistent_rollout_of_more_rows(batch, monkeypatch):
+    """Up to eight rows share one persistent launch: against the launch-pair rollout and
+    the oracle, greedy and sampled (5 and 7 rows leave words of the exchange lines unused)."""
+    import test_gpu_parity as tp
+    import test_gpu_sampling as ts
+    tp.test_persistent_rollout_matches_launch_pair_rollout(batch, monkeypatch)
+    monkeypatch.delenv("DOMINO_ROLLOUT", raising=False)
+    cfg = tp.persistent_config(batch)
+    w = synth.make_weights(cfg, seed=45, gain_std=0.1)
+    inp = synth.make_inputs(cfg, seed=45)
+    run = GpuRun(cfg, w, inp["max_ctx"], beta=1)
+    gpu = ts._sampled_step(run, inp, 1.0, 45)
+    from paper_2605_29707_amd import binding as bd
+    assert gpu["err"] == 0 and bd.domino_debug_last_paths(run.model) & bd.PATH_PERSISTENT_ROLLOUT
+    run.close()
+    n, tot = ts._check_sampled(cfg, gpu, inp, oracle.as_f64_weights(w), 1.0, 45, 2e-2)
+    assert n >= tot // 2
