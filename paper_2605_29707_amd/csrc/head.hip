@@ -18,7 +18,7 @@
 // A kernel boundary is the cheapest grid-wide handshake on this device (about
 // 1.6 us against about 4 us for a 256-workgroup spin barrier), so the
 // rollout is 3(B-1) launches and the final selection rather than one persistent
-// kernel (which up to eight batch rows and branch 1 run, below); the top-1
+// kernel (which up to eight batch rows run, below); the top-1
 // of each position is a 64-bit atomic max, so no launch merges lists inside
 // the loop.
 #include "common.h"
@@ -794,7 +794,8 @@ __global__ __launch_bounds__(64) void head_merge_kernel(HeadArgs h, int nlist) {
 // "all gates stored".
 // Waits are bounded: a timeout sets DEV_BARRIER_TIMEOUT and the abort flag,
 // and every workgroup leaves; the kernel always ends.  Workgroup 0 writes the
-// drafted token and its value of every position (no merge kernel).
+// drafted token and its value of every position (no merge kernel; at beta > 1 the
+// selection from the corrected logits follows, as after the launch loop).
 // ---------------------------------------------------------------------------
 constexpr int kPersWaves = 8, kPersTiles = 5, kPersKS = 8, kPersRegTiles = kPersTiles - 1;
 constexpr int kPersMaxBatch = kSlotStride;  // batch rows: a word of an exchange line each
@@ -848,7 +849,7 @@ DEVI bool poll_tagged(const unsigned long long *slots, int n, int bs, int wave, 
 }
 
 // BS: the largest batch the instantiation serves (1, 2, 4 or 8; arrays sized by it);
-// DBG: the final logits are also written out (h.final_logits);
+// DBG: the final logits are also written out (h.final_logits, h.lout);
 // SAMPLE: temperature sampling, the selection key is L / T + Gumbel noise
 // (Philox stream RNG_DRAFT, as in the launch-pair rollout) and the reported
 // value is the chosen token's raw logit
@@ -1123,7 +1124,7 @@ __global__ __launch_bounds__(kPersWaves * 64) void head_persist_kernel(HeadArgs 
       float bv = -INFINITY, br = 0.f;
       int bi = (tile0 * 16 + 4 * g) < V ? tile0 * 16 + 4 * g : INT_MAX;
       const bool full = (tile0 + kPersTiles) * 16 <= V;
-      float *fl = DBG ? h.final_logits + ((size_t)min(cc, bs - 1) * depth + (j - 1)) * V : nullptr;
+      const size_t orow = (size_t)min(cc, bs - 1) * depth + (j - 1);
 #pragma unroll
       for (int q = 0; q < kPersTiles; ++q) {
         const float4 l4 = lbs[wave * NI * 64 + (q * BS + (cc & (BS - 1))) * 4 + g];
@@ -1135,7 +1136,12 @@ __global__ __launch_bounds__(kPersWaves * 64) void head_persist_kernel(HeadArgs 
           const int lo = __builtin_amdgcn_update_dpp(0, a, 0x100 + BS, 0xf, 0xf, false);  // lane + BS
           val[e] = lv[e] + (acc[q][e] + __int_as_float(lo));
         }
-        if (DBG && rowok) {  // the final logits (output of sampled drafting, debug output otherwise)
+        // beta > 1: in the place of L_base, which only this wave reads, for the
+        // selection after the rollout (whole tiles: the padding keeps its zeros)
+        if (DBG && rowok && h.lout && tile0 + q < NT)
+          *(float4 *)(h.lout + orow * h.ldl + (tile0 + q) * 16 + 4 * g) = make_float4(val[0], val[1], val[2], val[3]);
+        if (DBG && rowok && h.final_logits) {  // output of sampled drafting, debug output otherwise
+          float *fl = h.final_logits + orow * V;
           const int n = (tile0 + q) * 16 + 4 * g;
           if ((V & 3) == 0 && n + 4 <= V) {  // rows start 16-byte aligned: four ids per store
             *(float4 *)(fl + n) = make_float4(val[0], val[1], val[2], val[3]);
@@ -1234,7 +1240,7 @@ __global__ __launch_bounds__(kPersWaves * 64) void head_persist_kernel(HeadArgs 
       }
       __syncthreads();
       if (!all_ok()) return;
-      if (blockIdx.x == 0 && tid < bs) {
+      if (blockIdx.x == 0 && tid < bs && !h.lout) {
         const unsigned long long best = key_of(tid);
         const uint32_t u = (uint32_t)(best >> kKeyIdBits);
         h.topk_ids[(size_t)tid * depth + (j - 1)] = key50_id(best);
@@ -1269,7 +1275,7 @@ static const void *persist_fn(bool dbg, bool smp) {
 // Checks the shapes and the device, and picks the instantiation and its LDS size.
 static bool persist_plan(const HeadArgs &h, int n_cu, const void **fn, size_t *lds_out, int *nr_out) {
   const Dims &D = h.D;
-  if (!D.bf16 || D.r != kPersKS * 32 || D.bs < 1 || D.bs > kPersMaxBatch || h.beta != 1 || D.ds % 32 || D.ds > 256 * 8 ||
+  if (!D.bf16 || D.r != kPersKS * 32 || D.bs < 1 || D.bs > kPersMaxBatch || (h.beta > 1 && h.sample) || D.ds % 32 || D.ds > 256 * 8 ||
       D.V >= (1 << kKeyIdBits) || D.B > 64 || !h.uslot || !h.kslot || !h.abort_flag || (h.sample && !h.praw))
     return false;
   const int G = persist_groups(D);
@@ -1280,7 +1286,7 @@ static bool persist_plan(const HeadArgs &h, int n_cu, const void **fn, size_t *l
                      sizeof(float4) * kPersWaves * pers_lb_loads(BS) * 64 +
                      sizeof(float) * (size_t)(D.B - 1) * D.bs * ((D.r + G - 1) / G);
   if (lds > 160 * 1024) return false;
-  const bool dbg = h.final_logits != nullptr, smp = h.sample != 0;
+  const bool dbg = h.final_logits || h.lout, smp = h.sample != 0;
   *fn = BS == 1 ? persist_fn<1>(dbg, smp) : (BS == 2 ? persist_fn<2>(dbg, smp) : (BS == 4 ? persist_fn<4>(dbg, smp) : persist_fn<8>(dbg, smp)));
   if (hipFuncSetAttribute(*fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
     (void)hipGetLastError();
@@ -1302,21 +1308,40 @@ static bool persist_plan(const HeadArgs &h, int n_cu, const void **fn, size_t *l
   return true;
 }
 
+// beta > 1: the lists of every position's corrected logits (h.lout); their merge, or
+// at branch 1 that of the workgroups' top-1
+static void launch_select(const HeadArgs &h, hipStream_t st) {
+  const Dims &D = h.D;
+  const int depth = D.B - 1;
+  int nlist = h.GC;
+  if (h.beta > 1) {
+    nlist = (D.V + kTopWave - 1) / kTopWave;  // (at most GC: the lists fit the workspace)
+    const dim3 grid((nlist + 3) / 4, depth, D.bs);
+    if (h.beta <= 2) hipLaunchKernelGGL(head_topb_kernel<2>, grid, dim3(256), 0, st, h, nlist);
+    else if (h.beta <= 4) hipLaunchKernelGGL(head_topb_kernel<4>, grid, dim3(256), 0, st, h, nlist);
+    else hipLaunchKernelGGL(head_topb_kernel<8>, grid, dim3(256), 0, st, h, nlist);
+  }
+  hipLaunchKernelGGL(head_merge_kernel, dim3(depth, D.bs), dim3(64), 0, st, h, nlist);
+}
+
 bool launch_head_persistent(const HeadArgs &h, int n_cu, hipStream_t st) {
   // Up to eight batch rows, as many as an exchange line has words.  A drafting
   // step of the 4B shape with 256 tokens of context, persistent against launch
   // by launch: 715 and 935 us at 2 rows, 926 and 1057 at 4, 1088 and 1205 at 5,
-  // 1214 and 1273 at 8 (sampled 1294 and 1315): the gap closes with the rows.
+  // 1214 and 1273 at 8 (sampled 1294 and 1315; four candidates a position 639 and
+  // 863 at 1 row, 951 and 1076 at 4, 1229 and 1296 at 8): the gap closes with the rows.
   const void *fn;
   size_t lds;
   int nr;
-  if (!persist_plan(h, n_cu, &fn, &lds, &nr)) return false;
   HeadArgs a = h;
+  a.lout = h.beta > 1 ? const_cast<float *>(h.Lbase) : nullptr;
+  if (!persist_plan(a, n_cu, &fn, &lds, &nr)) return false;
   void *args[] = {&a, &nr};
   if (hipLaunchKernel(fn, dim3(persist_groups(a.D)), dim3(kPersWaves * 64), args, lds, st) != hipSuccess) {
     (void)hipGetLastError();
     return false;
   }
+  if (a.lout) launch_select(a, st);
   return true;
 }
 
@@ -1375,15 +1400,7 @@ static void launch_loop(HeadArgs h, hipStream_t st) {
     launch_state<WT>(h, j, st);
     hipLaunchKernelGGL(logits, dim3(h.GC), dim3(kLogitWaves * 64), lds, st, h, j);
   }
-  int nlist = h.GC;
-  if (h.beta > 1) {
-    nlist = (D.V + kTopWave - 1) / kTopWave;  // (at most GC: the lists fit the workspace)
-    const dim3 grid((nlist + 3) / 4, depth, D.bs);
-    if (h.beta <= 2) hipLaunchKernelGGL(head_topb_kernel<2>, grid, dim3(256), 0, st, h, nlist);
-    else if (h.beta <= 4) hipLaunchKernelGGL(head_topb_kernel<4>, grid, dim3(256), 0, st, h, nlist);
-    else hipLaunchKernelGGL(head_topb_kernel<8>, grid, dim3(256), 0, st, h, nlist);
-  }
-  hipLaunchKernelGGL(head_merge_kernel, dim3(depth, D.bs), dim3(64), 0, st, h, nlist);
+  launch_select(h, st);
 }
 
 template <typename WT>

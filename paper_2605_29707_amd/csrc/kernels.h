@@ -181,7 +181,7 @@ struct HeadArgs {
   // batches above kHeadFusedBatch: packed copies of the two matrices
   const void *whh_p, *w1s_p;
   int whh_NT, whh_KS, w1s_NT, w1s_KS;
-  float *lout = nullptr;  // beta > 1: where the corrected logits replace L_base (set by launch_head)
+  float *lout = nullptr;  // beta > 1: where the corrected logits replace L_base (set at launch)
 };
 // Batches up to this run the fused state kernel (one launch a position instead of
 // two): its workgroups each repeat the elementwise update of every row, which at
@@ -191,7 +191,7 @@ int head_logits_grid(const Dims &D);
 int head_best_slots();
 hipError_t launch_head(const HeadArgs &h, hipStream_t st);
 // The persistent rollout where the shapes allow it (bf16, r = 256, batch <= 8,
-// branch 1, a grid that fits the device at one workgroup per CU, vocabulary
+// a grid that fits the device at one workgroup per CU, vocabulary
 // < 2^18); returns false (nothing launched) otherwise.
 bool launch_head_persistent(const HeadArgs &h, int n_cu, hipStream_t st);
 // the state recurrence of every position, teacher-forced (no logits): u into

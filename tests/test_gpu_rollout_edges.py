@@ -95,3 +95,28 @@ def test_persistent_rollout_of_more_rows(batch, monkeypatch):
     run.close()
     n, tot = ts._check_sampled(cfg, gpu, inp, oracle.as_f64_weights(w), 1.0, 45, 2e-2)
     assert n >= tot // 2
+
+
+@pytest.mark.parametrize("batch,beta", [(1, 4), (2, 2), (3, 8), (7, 3)])
+def test_persistent_rollout_of_more_candidates(batch, beta):
+    """The persistent rollout leaves its corrected logits to the top-beta selection."""
+    import test_gpu_parity as tp
+    from paper_2605_29707_amd import binding as bd
+    cfg = tp.persistent_config(batch).with_(branch=beta, vocab=8196)   # the last tile is a quarter full
+    w = synth.make_weights(cfg, seed=47, gain_std=0.1)
+    inp = synth.make_inputs(cfg, seed=47)
+    run = GpuRun(cfg, w, inp["max_ctx"], beta=beta)
+    bare = run.step(inp, debug=False)
+    gpu = run.step(inp)
+    assert gpu["err"] == 0 and bd.domino_debug_last_paths(run.model) & bd.PATH_PERSISTENT_ROLLOUT
+    run.close()
+    for k in ("topk_ids", "topk_vals"):
+        np.testing.assert_array_equal(bare[k], gpu[k])
+    for b in range(batch):
+        for j in range(cfg.depth):
+            ids, vals = oracle.top_beta(gpu["final_logits"][b, j], beta)
+            np.testing.assert_array_equal(gpu["topk_ids"][b, j], ids, err_msg=f"row {b} depth {j + 1}")
+            np.testing.assert_array_equal(gpu["topk_vals"][b, j], vals.astype(np.float32))
+    ref = oracle.draft_step(cfg, oracle.as_f64_weights(w), inp["anchor"], inp["ctx_lens"], inp["ctx_k"], inp["ctx_v"],
+                            beta, forced=gpu["topk_ids"][:, :, 0])
+    check_against_oracle(cfg, gpu, ref, 3e-4, beta)
