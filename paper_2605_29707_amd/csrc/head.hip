@@ -21,6 +21,8 @@
 // kernel (which up to eight batch rows run, below); the top-1
 // of each position is a 64-bit atomic max, so no launch merges lists inside
 // the loop.
+#include <mutex>
+
 #include "common.h"
 #include "kernels.h"
 #include "mfma.h"
@@ -1308,6 +1310,55 @@ static bool persist_plan(const HeadArgs &h, int n_cu, const void **fn, size_t *l
   return true;
 }
 
+// Two persistent launches of different streams must not share the device: each
+// could hold CUs that the other's missing workgroups need.  So those of one device
+// are ordered by an event: a launch on another stream than the last one's first
+// waits for it.  A capturing stream is left out (its graph runs later, in the
+// order that its owner gives it).
+namespace {
+struct PersistOrder {
+  struct Device {
+    std::mutex m;
+    hipEvent_t done = nullptr;
+    hipStream_t last = nullptr;
+    bool any = false;
+  };
+  static constexpr int kDevices = 64;
+  static Device *device() {
+    static Device *d = new Device[kDevices];  // (never freed: a stream may outlive static destructors)
+    int id = 0;
+    if (hipGetDevice(&id) != hipSuccess || id < 0 || id >= kDevices) return nullptr;
+    return d + id;
+  }
+  Device *d;
+  hipStream_t st;
+  std::unique_lock<std::mutex> lock;
+  explicit PersistOrder(hipStream_t s) : d(device()), st(s) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (!d || hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
+      (void)hipGetLastError();
+      d = nullptr;
+      return;
+    }
+    lock = std::unique_lock<std::mutex>(d->m);
+    if (!d->done && hipEventCreateWithFlags(&d->done, hipEventDisableTiming | hipEventDisableSystemFence) != hipSuccess) {
+      (void)hipGetLastError();
+      d->done = nullptr;
+    }
+    if (d->done && d->any && d->last != st && hipStreamWaitEvent(st, d->done, 0) != hipSuccess) (void)hipGetLastError();
+  }
+  void launched() {
+    if (!d || !d->done) return;
+    if (hipEventRecord(d->done, st) != hipSuccess) {
+      (void)hipGetLastError();
+      return;
+    }
+    d->last = st;
+    d->any = true;
+  }
+};
+}  // namespace
+
 // beta > 1: the lists of every position's corrected logits (h.lout); their merge, or
 // at branch 1 that of the workgroups' top-1
 static void launch_select(const HeadArgs &h, hipStream_t st) {
@@ -1337,10 +1388,12 @@ bool launch_head_persistent(const HeadArgs &h, int n_cu, hipStream_t st) {
   a.lout = h.beta > 1 ? const_cast<float *>(h.Lbase) : nullptr;
   if (!persist_plan(a, n_cu, &fn, &lds, &nr)) return false;
   void *args[] = {&a, &nr};
+  PersistOrder order(st);
   if (hipLaunchKernel(fn, dim3(persist_groups(a.D)), dim3(kPersWaves * 64), args, lds, st) != hipSuccess) {
     (void)hipGetLastError();
     return false;
   }
+  order.launched();
   if (a.lout) launch_select(a, st);
   return true;
 }

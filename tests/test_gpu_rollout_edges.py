@@ -120,3 +120,29 @@ def test_persistent_rollout_of_more_candidates(batch, beta):
     ref = oracle.draft_step(cfg, oracle.as_f64_weights(w), inp["anchor"], inp["ctx_lens"], inp["ctx_k"], inp["ctx_v"],
                             beta, forced=gpu["topk_ids"][:, :, 0])
     check_against_oracle(cfg, gpu, ref, 3e-4, beta)
+
+
+def test_persistent_rollouts_on_two_streams():
+    """Steps of two models on two streams, submitted alternately without waiting: their
+    persistent launches are ordered, so each ends as it does alone."""
+    import test_gpu_parity as tp
+    runs = []
+    for i, (batch, beta) in enumerate([(2, 3), (5, 1)]):
+        cfg = tp.persistent_config(batch).with_(branch=beta)
+        run = GpuRun(cfg, synth.make_weights(cfg, seed=51 + i, gain_std=0.1), cfg.ctx, beta=beta)
+        inp = synth.make_inputs(cfg, seed=51 + i)
+        alone = run.step(inp, debug=False)
+        args = (run.t(inp["anchor"], torch.int32), run.t(inp["ctx_lens"], torch.int32),
+                run.t(inp["ctx_k"], torch.bfloat16), run.t(inp["ctx_v"], torch.bfloat16))
+        runs.append((run, args, alone, torch.cuda.Stream(), beta))
+    torch.cuda.synchronize()
+    for _ in range(5):
+        for run, args, _, st, beta in runs:
+            with torch.cuda.stream(st):
+                run.bd.domino_draft_step(run.model, *args, run.max_ctx, run.ids, run.vals, run.ws, branch=beta)
+    torch.cuda.synchronize()
+    for run, _, alone, _, _ in runs:
+        assert run.bd.domino_workspace_error(run.ws) == 0
+        np.testing.assert_array_equal(run.ids.cpu().numpy(), alone["topk_ids"])
+        np.testing.assert_array_equal(run.vals.cpu().numpy(), alone["topk_vals"])
+        run.close()
