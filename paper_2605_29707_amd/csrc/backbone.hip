@@ -1387,13 +1387,15 @@ void launch_sum_parts(const float *parts, int np, size_t pstride, int rows, int 
   hipLaunchKernelGGL(sum_parts_kernel, dim3(blocks), dim3(256), 0, st, parts, np, pstride, rows, width, y, ldy);
 }
 
-// one thread per 8 columns: a lane's 16 bytes of a fragment in each plane
+// one thread per 8 columns: a lane's 16 bytes of a fragment in each plane; `per`
+// workgroups a row (rows * width passes 2^31 at 64 x 8192 rows of 4096 columns, a
+// row's workgroups and columns do not)
 __global__ __launch_bounds__(256) void sum_parts_planes_kernel(const float *__restrict__ parts, int np,
-                                                               size_t pstride, int rows, int width,
+                                                               size_t pstride, int width, int per,
                                                                u32x4 *__restrict__ planes, int row0, int nrb) {
-  const int KS = width / 32, idx = blockIdx.x * 256 + threadIdx.x;
-  if (idx >= rows * KS * 4) return;
-  const int k = idx % (KS * 4) * 8, r = idx / (KS * 4), m = row0 + r;
+  const int KS = width / 32, r = blockIdx.x / per, k = ((int)(blockIdx.x % per) * 256 + (int)threadIdx.x) * 8;
+  if (k >= width) return;
+  const int m = row0 + r;
   float f[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll 4
   for (int p = 0; p < np; ++p) {
@@ -1410,9 +1412,9 @@ __global__ __launch_bounds__(256) void sum_parts_planes_kernel(const float *__re
 }
 void launch_sum_parts_planes(const float *parts, int np, size_t pstride, int rows, int width, void *planes, int row0,
                              int nrb, hipStream_t st) {
-  const int items = rows * width / 8;
-  hipLaunchKernelGGL(sum_parts_planes_kernel, dim3((items + 255) / 256), dim3(256), 0, st, parts, np, pstride, rows,
-                     width, (u32x4 *)planes, row0, nrb);
+  const int per = (width / 8 + 255) / 256;
+  hipLaunchKernelGGL(sum_parts_planes_kernel, dim3((unsigned)rows * (unsigned)per), dim3(256), 0, st, parts, np,
+                     pstride, width, per, (u32x4 *)planes, row0, nrb);
 }
 
 __global__ void fill_u32_kernel(uint32_t *p, size_t n, uint32_t v) {
