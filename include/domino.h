@@ -131,7 +131,7 @@ void domino_model_destroy(domino_model_t m);
 
 /* Bytes of workspace domino_draft_step needs for `batch` rows, caches of
  * `max_ctx` positions, up to `max_new` projected context rows and top-`branch`
- * outputs.  Returns 0 for invalid arguments. */
+ * outputs: enough for every n_new in [0, max_new].  Returns 0 for invalid arguments. */
 size_t domino_workspace_bytes(domino_model_t m, int32_t batch, int32_t max_ctx, int32_t max_new,
                               int32_t branch);
 
@@ -194,7 +194,8 @@ domino_status domino_draft_step_sampled(domino_model_t m, int32_t batch, const i
                                         float *topk_vals, float *final_logits, const domino_debug *debug,
                                         void *workspace, size_t workspace_bytes, void *stream);
 
-/* Bytes of workspace domino_train_forward needs (0 for invalid arguments). */
+/* Bytes of workspace domino_train_forward needs for every n_new in [0, max_new]
+ * (0 for invalid arguments). */
 size_t domino_train_workspace_bytes(domino_model_t m, int32_t batch, int32_t max_ctx, int32_t max_new);
 
 /*

@@ -213,10 +213,42 @@ Plans make_plans(const domino_model *m, int bs, int max_new) {
   return p;
 }
 
-bool layout(const domino_model *m, int bs, int max_ctx, int max_new, int beta, WsLayout &w) {
+// Rows of the K-split partial outputs of the projections that take the appended rows
+struct PartRows {
+  size_t qkv, fc;
+};
+// The most that `plan` gives any row count in [lo, hi].  Plans choose among tiles by row
+// blocks (16, 32, then steps of 64 rows); between those fewer rows have as many splits
+// or more.  Above `split_rows` nothing is split.
+template <typename Plan>
+size_t most_part_rows(Plan plan, int lo, int hi, int split_rows) {
+  size_t most = (size_t)std::max(hi, 0);
+  for (int a = lo; a <= std::min(hi, split_rows);) {
+    const int end = std::min(hi, a <= 16 ? 16 : a <= 32 ? 32 : (a + 63) / 64 * 64);
+    most = std::max(most, (size_t)std::max(plan(a).ksplit, plan(end).ksplit) * end);
+    a = end + 1;
+  }
+  return most;
+}
+// Of any n_new up to max_new: fewer rows may be split more ways, so that a step of 5
+// may need more than one of 8
+PartRows most_part_rows(const domino_model *m, int bs, int max_new) {
+  auto most = [&](const Packed &pk, int lo, int hi, auto plan) {
+    return most_part_rows([&](int rows) { return plan(m, pk, rows, EPI_STORE, kMaxSplit); }, lo, hi,
+                          m->bf16 ? std::max(kRowsMax, gemm_wide_split_rows(pk.NT, pk.KS, m->n_cu)) : hi);
+  };
+  return {most(m->qkv[0], bs * m->D.B, bs * (m->D.B + max_new), plan_layer),
+          m->fuse_k > 0 ? most(m->fc, 1, bs * max_new, plan_proj) : 0};
+}
+
+// The layout of a step that appends max_new rows; for a query (upto) with room for
+// the partials of any step that appends fewer
+void layout(const domino_model *m, int bs, int max_ctx, int max_new, int beta, WsLayout &w, bool upto = false) {
   Dims D = make_dims(m, bs);
   const int M = bs * D.B, Mh = bs * (D.B - 1);
   const Plans p = make_plans(m, bs, max_new);
+  const PartRows parts = upto ? most_part_rows(m, bs, max_new)
+                              : PartRows{(size_t)p.qkv.ksplit * bs * (D.B + max_new), (size_t)p.fc.ksplit * bs * max_new};
   w.GC = head_logits_grid(D);
   size_t o = 0;
   auto take = [&](size_t bytes) {
@@ -238,8 +270,8 @@ bool layout(const domino_model *m, int bs, int max_ctx, int max_new, int beta, W
   };
   w.A = take(rows_bytes(Ma, D.d));
   w.A2 = m->bf16 ? take(rows_bytes(M, D.d)) : w.A;  // the FFN's input: A's planes keep the appended rows
-  w.FC = take((size_t)p.fc.ksplit * bs * max_new * D.d * 4);
-  w.QKV = take((size_t)p.qkv.ksplit * Ma * qkvw * 4);
+  w.FC = take(parts.fc * D.d * 4);
+  w.QKV = take(parts.qkv * qkvw * 4);
   w.Q = take((size_t)M * D.nq * D.dh * 4);
   w.Kb = take((size_t)M * D.nkv * D.dh * 4);
   w.Vb = take((size_t)M * D.nkv * D.dh * 4);
@@ -260,7 +292,6 @@ bool layout(const domino_model *m, int bs, int max_ctx, int max_new, int beta, W
   w.praw = take((size_t)(D.B - 1) * bs * w.GC * 4);
   w.XF = take(wide_scratch(m, p, bs * max_new, bs * (D.B - 1)));  // also the training forward's W1 S-half rows
   w.total = o;
-  return true;
 }
 
 // Rows per batch row of a verify forward: the smallest block size the
@@ -601,7 +632,7 @@ size_t domino_workspace_bytes(domino_model_t m, int32_t batch, int32_t max_ctx, 
       branch > 8)
     return 0;
   WsLayout w;
-  layout(m, batch, max_ctx, max_new, branch, w);
+  layout(m, batch, max_ctx, max_new, branch, w, true);
   return w.total;
 }
 
@@ -929,8 +960,8 @@ struct TrainLayout {
   WsLayout w;
   size_t S, Y, U, part, lab, ce, total;
 };
-void train_layout(const domino_model *m, int bs, int max_ctx, int max_new, TrainLayout &t) {
-  layout(m, bs, max_ctx, max_new, 1, t.w);
+void train_layout(const domino_model *m, int bs, int max_ctx, int max_new, TrainLayout &t, bool upto = false) {
+  layout(m, bs, max_ctx, max_new, 1, t.w, upto);
   const Dims &D = m->D;
   const size_t Mr = (size_t)bs * (D.B - 1);
   size_t o = t.w.total;
@@ -952,7 +983,7 @@ void train_layout(const domino_model *m, int bs, int max_ctx, int max_new, Train
 size_t domino_train_workspace_bytes(domino_model_t m, int32_t batch, int32_t max_ctx, int32_t max_new) {
   if (!m || !m->has_head || batch < 1 || batch > 64 || max_ctx < 0 || max_new < 0 || max_new > max_ctx) return 0;
   TrainLayout t;
-  train_layout(m, batch, max_ctx, max_new, t);
+  train_layout(m, batch, max_ctx, max_new, t, true);
   return t.total;
 }
 

@@ -328,13 +328,28 @@ constexpr int kWideCols[] = {4, 6, 8, 10, 12, 13};  // weight tiles per workgrou
 
 }  // namespace
 
-// The tile (nw: weight tiles, MT: row blocks of a wave) and the K split by a
-// cost model of the busiest CU, in core cycles, fitted to the gate/up shape at
+// Cost of the busiest CU in core cycles, fitted to the gate/up shape at
 // 64 .. 512 rows and the tiles 6 x 1, 6 x 2, 6 x 4, 12 x 2 and 12 x 4 (measured
 // 1076, 1542, 2680, 2790 and 4463 cycles an iteration): an iteration costs its products
 // (64 per tile and row block) plus 400 plus 11 per KB loaded; a workgroup
 // about 6000 to fill and drain; a K split its partial outputs, written and read
-// back.  SwiGLU, nonlinear in the sum, is never split.
+// back.
+namespace {
+constexpr double kStageCycles = 6000.0;
+double iter_cycles(int ct, int tm) { return 64.0 * ct * tm + 400.0 + 11.0 * (2 * ct + 16 * tm); }
+double part_cycles(int ks, int M, int ntiles, int n_cu) { return 2.0 * ks * (double)M * ntiles * 16 * 4 / n_cu / 10.0; }
+}  // namespace
+
+// A split saves at most the last round of workgroups, and costs its partials: above
+// this many rows those of two splits cost more than a round of the largest tile (a tenth
+// more, for what the comparison below lets pass).
+int gemm_wide_split_rows(int ntiles, int KS, int n_cu) {
+  const double round = (KS + 1) / 2 * iter_cycles(13, 4) + kStageCycles;
+  return (int)std::min(1e9, 1.1 * round / part_cycles(2, 1, ntiles, n_cu));
+}
+
+// The tile (nw: weight tiles, MT: row blocks of a wave) and the K split of least cost.
+// SwiGLU, nonlinear in the sum, is never split.
 GemmPlan plan_gemm_wide(int ntiles, int KS, int M, int epi, int n_cu, int max_split) {
   GemmPlan p;
   p.wide = 1;
@@ -342,20 +357,21 @@ GemmPlan plan_gemm_wide(int ntiles, int KS, int M, int epi, int n_cu, int max_sp
   p.kcm = 1;
   p.pgrid = 0;
   const int nrb = (M + 15) / 16, nch = (KS + 1) / 2;
+  const int splits = epi == EPI_STORE && M <= gemm_wide_split_rows(ntiles, KS, n_cu) ? max_split : 1;
   double best = 1e300;
   for (int tm = 1; tm <= 4; ++tm) {
     const int mg = (nrb + 4 * tm - 1) / (4 * tm);
     for (int ct : kWideCols) {
       if (epi == EPI_SWIGLU && ct % 2) continue;
       const int groups = (ntiles + ct - 1) / ct;
-      const double iter = 64.0 * ct * tm + 400.0 + 11.0 * (2 * ct + 16 * tm);
-      for (int ks = 1; ks <= (epi == EPI_STORE ? max_split : 1); ++ks) {
+      const double iter = iter_cycles(ct, tm);
+      for (int ks = 1; ks <= splits; ++ks) {
         const int cps = (nch + ks - 1) / ks;
         if (ks > 1 && ((ks - 1) * cps >= nch || cps < 4)) continue;  // an empty or a very short split
         const long wgs = (long)groups * mg * ks;
         const double rounds = (double)((wgs + n_cu - 1) / n_cu);
-        const double part = ks > 1 ? 2.0 * ks * (double)M * ntiles * 16 * 4 / n_cu / 10.0 : 0.0;
-        const double cost = rounds * (cps * iter + 6000.0) + part;
+        const double part = ks > 1 ? part_cycles(ks, M, ntiles, n_cu) : 0.0;
+        const double cost = rounds * (cps * iter + kStageCycles) + part;
         if (cost < best * 0.999) {
           best = cost;
           p.nw = ct;

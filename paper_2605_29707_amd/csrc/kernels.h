@@ -59,6 +59,7 @@ void launch_gemm(bool bf16, int epi, const GemmArgs &a, const GemmPlan &p, hipSt
 // (in a.xf), then workgroup tiles of up to 208 columns x 256 rows multiply them
 // with the same packed weights; K-split partials as above.
 GemmPlan plan_gemm_wide(int ntiles, int KS, int M, int epi, int n_cu, int max_split);
+int gemm_wide_split_rows(int ntiles, int KS, int n_cu);  // above this many rows its plans split no K
 // false (nothing launched) when the arguments break the kernel's assumptions
 // (K not 32 KS, no rows, no fragment scratch)
 bool launch_gemm_wide(int epi, const GemmArgs &a, const GemmPlan &p, hipStream_t st);

@@ -19,3 +19,34 @@ for fuse in (0, 5):
         assert batch * n_new * 4096 // 8 <= threads < 2**32, (fuse, batch, n_new, threads)
         assert grids[0][3:5] == ["1", "1"]
 ''', tmp_path)
+
+
+def test_a_workspace_serves_any_number_of_appended_rows(tmp_path):
+    """A program allocates once for max_new and appends what each cycle accepted: no step or
+    training forward of fewer rows is refused, one byte less than a step's own need is."""
+    host_stub.run('''
+def need(call, most):
+    """Least bytes that `call` accepts, by bisection."""
+    lo, hi = 0, most
+    while lo < hi:
+        mid = (lo + hi) // 2
+        lo, hi = (mid + 1, hi) if call(mid) == -2 else (lo, mid)
+    h.log()
+    return lo
+
+shapes = {s: h.config(*h.SHAPES[s]) for s in h.SHAPES}
+shapes["plain"] = h.config(4096, 32, 12288, fuse=0)
+shapes["f32"] = h.config(256, 4, 1024, vocab=4096, fuse=0, dtype=0, nkv=2, head_dim=64)
+for name, cfg in shapes.items():
+    m = h.Model(cfg)
+    for batch in list(range(1, 13)) + [16, 24, 33, 64]:
+        for most in (1, 5, 8, 15, 16, 64):
+            ws, tws = m.ws(batch, 2048, most), m.train_ws(batch, 2048, most)
+            for n in range(most + 1):
+                assert m.step(batch, 2048, n, ws) == 0, (name, batch, most, n)
+                assert m.train(batch, 2048, n, tws) == 0, (name, batch, most, n)
+            h.log()
+    for batch, n in ((1, 0), (1, 5), (2, 9), (9, 16)):
+        own = need(lambda b: m.step(batch, 2048, n, b), m.ws(batch, 2048, n))
+        assert own > 0 and m.step(batch, 2048, n, own - 1) == -2
+''', tmp_path)
