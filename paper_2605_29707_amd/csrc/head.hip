@@ -1312,16 +1312,20 @@ static bool persist_plan(const HeadArgs &h, int n_cu, const void **fn, size_t *l
 
 // Two persistent launches of different streams must not share the device: each
 // could hold CUs that the other's missing workgroups need.  So those of one device
-// are ordered by an event: a launch on another stream than the last one's first
-// waits for it.  A capturing stream is left out (its graph runs later, in the
-// order that its owner gives it).
+// are ordered by an event: every launch first waits for the last one.  Stream handles are
+// not compared: hipStreamPerThread is one handle for a stream of each thread, and a
+// destroyed stream's handle may come back (a wait for the stream's own last event costs
+// nothing measurable: 822.7 and 822.8 us a step of the Qwen3-8B shape).  Where the
+// order cannot be had (`ok` is false), the rollout goes launch by launch, which needs none.
+// A captured launch is not ordered: its graph runs later, in the order that its owner
+// gives it.
 namespace {
 struct PersistOrder {
   struct Device {
     std::mutex m;
     hipEvent_t done = nullptr;
-    hipStream_t last = nullptr;
-    bool any = false;
+    bool any = false;   // `done` has been recorded
+    bool lost = false;  // a launch went out without its record: nothing can wait for it any more
   };
   static constexpr int kDevices = 64;
   static Device *device() {
@@ -1330,31 +1334,35 @@ struct PersistOrder {
     if (hipGetDevice(&id) != hipSuccess || id < 0 || id >= kDevices) return nullptr;
     return d + id;
   }
-  Device *d;
+  Device *d = nullptr;
   hipStream_t st;
   std::unique_lock<std::mutex> lock;
-  explicit PersistOrder(hipStream_t s) : d(device()), st(s) {
+  bool captured = false, ok = false;
+  explicit PersistOrder(hipStream_t s) : st(s) {
+    ok = begin();
+    if (!ok) (void)hipGetLastError();
+  }
+  bool begin() {
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (!d || hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
-      (void)hipGetLastError();
-      d = nullptr;
-      return;
-    }
+    if (hipStreamIsCapturing(st, &cs) != hipSuccess) return false;
+    captured = cs != hipStreamCaptureStatusNone;
+    if (captured) return true;
+    d = device();
+    if (!d) return false;
     lock = std::unique_lock<std::mutex>(d->m);
+    if (d->lost) return false;
     if (!d->done && hipEventCreateWithFlags(&d->done, hipEventDisableTiming | hipEventDisableSystemFence) != hipSuccess) {
-      (void)hipGetLastError();
       d->done = nullptr;
+      return false;
     }
-    if (d->done && d->any && d->last != st && hipStreamWaitEvent(st, d->done, 0) != hipSuccess) (void)hipGetLastError();
+    return !d->any || hipStreamWaitEvent(st, d->done, 0) == hipSuccess;
   }
   void launched() {
-    if (!d || !d->done) return;
-    if (hipEventRecord(d->done, st) != hipSuccess) {
-      (void)hipGetLastError();
-      return;
-    }
-    d->last = st;
+    if (!d) return;
     d->any = true;
+    if (hipEventRecord(d->done, st) == hipSuccess) return;
+    (void)hipGetLastError();
+    d->lost = true;
   }
 };
 }  // namespace
@@ -1389,6 +1397,7 @@ bool launch_head_persistent(const HeadArgs &h, int n_cu, hipStream_t st) {
   if (!persist_plan(a, n_cu, &fn, &lds, &nr)) return false;
   void *args[] = {&a, &nr};
   PersistOrder order(st);
+  if (!order.ok) return false;
   if (hipLaunchKernel(fn, dim3(persist_groups(a.D)), dim3(kPersWaves * 64), args, lds, st) != hipSuccess) {
     (void)hipGetLastError();
     return false;

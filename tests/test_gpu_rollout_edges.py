@@ -146,3 +146,36 @@ def test_persistent_rollouts_on_two_streams():
         np.testing.assert_array_equal(run.ids.cpu().numpy(), alone["topk_ids"])
         np.testing.assert_array_equal(run.vals.cpu().numpy(), alone["topk_vals"])
         run.close()
+
+
+def test_persistent_rollouts_of_two_threads_on_their_own_default_streams():
+    """hipStreamPerThread (handle 2) is a stream of its own in each host thread: the launches
+    of two threads are ordered although they pass the same handle."""
+    import threading
+    import test_gpu_parity as tp
+    runs = []
+    for i, batch in enumerate([1, 6]):
+        cfg = tp.persistent_config(batch)
+        run = GpuRun(cfg, synth.make_weights(cfg, seed=53 + i, gain_std=0.1), cfg.ctx, beta=1)
+        inp = synth.make_inputs(cfg, seed=53 + i)
+        alone = run.step(inp, debug=False)
+        args = (run.t(inp["anchor"], torch.int32), run.t(inp["ctx_lens"], torch.int32),
+                run.t(inp["ctx_k"], torch.bfloat16), run.t(inp["ctx_v"], torch.bfloat16))
+        runs.append((run, args, alone))
+    torch.cuda.synchronize()
+
+    def steps(run, args):
+        for _ in range(5):
+            run.bd.domino_draft_step(run.model, *args, run.max_ctx, run.ids, run.vals, run.ws, stream=2)
+
+    threads = [threading.Thread(target=steps, args=r[:2]) for r in runs]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    for run, _, alone in runs:
+        assert run.bd.domino_workspace_error(run.ws) == 0
+        np.testing.assert_array_equal(run.ids.cpu().numpy(), alone["topk_ids"])
+        np.testing.assert_array_equal(run.vals.cpu().numpy(), alone["topk_vals"])
+        run.close()

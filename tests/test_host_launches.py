@@ -50,3 +50,48 @@ for name, cfg in shapes.items():
         own = need(lambda b: m.step(batch, 2048, n, b), m.ws(batch, 2048, n))
         assert own > 0 and m.step(batch, 2048, n, own - 1) == -2
 ''', tmp_path)
+
+
+ROLLOUT = '''
+PERSIST = "head_persist"
+
+def step(m, batch=1, stream=0, branch=1):
+    """The stream calls of one step's rollout: waits, the persistent launch, records."""
+    h.log()
+    assert m.step(batch, 2048, 0, 1 << 40, branch=branch, stream=stream) == 0
+    return [(r[0] if r[0] != "launch" else PERSIST, int(r[-1])) for r in h.log()
+            if r[0] in ("wait", "record") or PERSIST in r[1]]
+
+m = h.Model(h.config(*h.SHAPES["8b"]))
+def ordered(s): return [("wait", s), (PERSIST, s), ("record", s)]
+'''
+
+
+def test_persistent_rollouts_wait_for_the_last_one(tmp_path):
+    """Whatever its stream: hipStreamPerThread (2) is another stream in another thread, and a
+    handle may be that of a new stream."""
+    host_stub.run(ROLLOUT + '''
+assert step(m) == [(PERSIST, 0), ("record", 0)]
+for s in (0, 77, 77, 2, 2, 0):
+    assert step(m, stream=s) == ordered(s), s
+assert step(m, batch=8, branch=3, stream=5) == ordered(5)
+''', tmp_path)
+
+
+def test_rollouts_that_cannot_be_ordered_go_launch_by_launch(tmp_path):
+    host_stub.run(ROLLOUT + '''
+def loops(**kw):
+    return step(m, **kw) == [] and m.paths() == 0
+
+h.stub.stub_fail(b"hipEventCreateWithFlags", 1)
+assert loops()
+assert step(m) == [(PERSIST, 0), ("record", 0)] and m.paths() == 1
+h.stub.stub_fail(b"hipStreamWaitEvent", 1)
+assert loops(stream=9)
+assert step(m, stream=9) == ordered(9)
+h.stub.stub_fail(b"hipGetDevice", 1)
+assert loops()
+h.stub.stub_fail(b"hipEventRecord", 1)   # a launch that nothing can wait for any more
+assert step(m, stream=9) == [("wait", 9), (PERSIST, 9)]
+assert loops() and loops(stream=9) and loops(batch=3, branch=2)
+''', tmp_path)
