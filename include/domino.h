@@ -23,6 +23,11 @@
  *    that no access leaves its buffer, and are recorded in an error word at
  *    the start of the workspace, read with domino_workspace_error().
  *  - domino_last_error() returns a thread-local message for the last failure.
+ *  - Greedy or sampled drafting of up to four rows with one candidate a
+ *    position, bf16 weights and rank 256 may put a launch that needs the whole
+ *    device into a captured graph.  Replays of such graphs must not overlap
+ *    with other draft steps on the device (else DOMINO_DEV_BARRIER_TIMEOUT);
+ *    uncaptured steps are ordered by the library.
  *  - No C++ exception crosses this boundary.  A model handle may be used from
  *    several streams, but calls that share one workspace must not overlap.
  *  - Storage type: DOMINO_BF16 stores weights and KV caches as bfloat16,

@@ -1317,8 +1317,12 @@ static bool persist_plan(const HeadArgs &h, int n_cu, const void **fn, size_t *l
 // destroyed stream's handle may come back (a wait for the stream's own last event costs
 // nothing measurable: 822.7 and 822.8 us a step of the Qwen3-8B shape).  Where the
 // order cannot be had (`ok` is false), the rollout goes launch by launch, which needs none.
-// A captured launch is not ordered: its graph runs later, in the order that its owner
-// gives it.
+// A captured launch cannot be ordered from here: its graph runs later, and two graphs may
+// run at once.  So a capture takes the persistent launch only where programs have had it in their
+// graphs all along, at up to kPersCapturedBatch rows and one candidate a position
+// (their owner keeps such graphs apart); other steps are captured launch by launch, which
+// replays beside anything.
+constexpr int kPersCapturedBatch = 4;
 namespace {
 struct PersistOrder {
   struct Device {
@@ -1397,7 +1401,7 @@ bool launch_head_persistent(const HeadArgs &h, int n_cu, hipStream_t st) {
   if (!persist_plan(a, n_cu, &fn, &lds, &nr)) return false;
   void *args[] = {&a, &nr};
   PersistOrder order(st);
-  if (!order.ok) return false;
+  if (!order.ok || (order.captured && (h.D.bs > kPersCapturedBatch || h.beta > 1))) return false;
   if (hipLaunchKernel(fn, dim3(persist_groups(a.D)), dim3(kPersWaves * 64), args, lds, st) != hipSuccess) {
     (void)hipGetLastError();
     return false;

@@ -179,3 +179,45 @@ def test_persistent_rollouts_of_two_threads_on_their_own_default_streams():
         np.testing.assert_array_equal(run.ids.cpu().numpy(), alone["topk_ids"])
         np.testing.assert_array_equal(run.vals.cpu().numpy(), alone["topk_vals"])
         run.close()
+
+
+def test_captured_steps_replayed_at_once(monkeypatch):
+    """Graphs of two models' steps (six rows; three candidates), replayed on two streams without
+    waiting, with eager steps between: every replay gives, bit for bit, what an eager
+    launch-by-launch step gives."""
+    import test_gpu_parity as tp
+    runs = []
+    for i, (batch, beta) in enumerate([(6, 1), (2, 3)]):
+        cfg = tp.persistent_config(batch).with_(branch=beta)
+        w, inp = synth.make_weights(cfg, seed=55 + i, gain_std=0.1), synth.make_inputs(cfg, seed=55 + i)
+        monkeypatch.setenv("DOMINO_ROLLOUT", "loop")
+        run = GpuRun(cfg, w, cfg.ctx, beta=beta)
+        alone = run.step(inp, debug=False)
+        run.close()
+        monkeypatch.delenv("DOMINO_ROLLOUT")
+        run = GpuRun(cfg, w, cfg.ctx, beta=beta)
+        args = (run.t(inp["anchor"], torch.int32), run.t(inp["ctx_lens"], torch.int32),
+                run.t(inp["ctx_k"], torch.bfloat16), run.t(inp["ctx_v"], torch.bfloat16))
+        st, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=st):
+            run.bd.domino_draft_step(run.model, *args, run.max_ctx, run.ids, run.vals, run.ws, branch=beta)
+        assert run.bd.domino_debug_last_paths(run.model) == 0
+        runs.append((run, args, alone, st, graph, beta))
+    torch.cuda.synchronize()
+    for turn in range(4):
+        for run, _, _, _, _, _ in runs:
+            run.ids.zero_()
+            run.vals.zero_()
+        torch.cuda.synchronize()
+        for run, _, _, st, graph, _ in runs * 3:
+            with torch.cuda.stream(st):
+                graph.replay()
+        torch.cuda.synchronize()
+        for run, args, alone, _, _, beta in runs:
+            assert run.bd.domino_workspace_error(run.ws) == 0
+            np.testing.assert_array_equal(run.ids.cpu().numpy(), alone["topk_ids"], err_msg=f"turn {turn}")
+            np.testing.assert_array_equal(run.vals.cpu().numpy(), alone["topk_vals"])
+            run.bd.domino_draft_step(run.model, *args, run.max_ctx, run.ids, run.vals, run.ws, branch=beta)
+            torch.cuda.synchronize()
+    for run, *_ in runs:
+        run.close()

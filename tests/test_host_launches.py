@@ -95,3 +95,18 @@ h.stub.stub_fail(b"hipEventRecord", 1)   # a launch that nothing can wait for an
 assert step(m, stream=9) == [("wait", 9), (PERSIST, 9)]
 assert loops() and loops(stream=9) and loops(batch=3, branch=2)
 ''', tmp_path)
+
+
+def test_captured_rollouts(tmp_path):
+    """A graph's replays are not ordered: only up to four rows with one candidate a position
+    are captured as the persistent launch; nothing waits or records during a capture."""
+    host_stub.run(ROLLOUT + '''
+assert step(m, batch=5, branch=2) == [(PERSIST, 0), ("record", 0)]
+h.stub.stub_capture(31, 1)
+for batch, branch in ((1, 1), (4, 1)):
+    assert step(m, batch=batch, branch=branch, stream=31) == [(PERSIST, 31)] and m.paths() == 1
+for batch, branch in ((5, 1), (8, 1), (1, 2), (4, 8)):
+    assert step(m, batch=batch, branch=branch, stream=31) == [] and m.paths() == 0
+h.stub.stub_capture(31, 0)
+assert step(m, batch=8, branch=8, stream=31) == ordered(31)
+''', tmp_path)
