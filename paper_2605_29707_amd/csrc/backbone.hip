@@ -820,8 +820,9 @@ __global__ __launch_bounds__(NW * 64) void attn_flash_kernel(const float *__rest
         for (int x = 0; x < DH / 16; ++x) oacc[x][e] *= ae;
       }
     }
-    // MASKED: a row that has seen no key yet has m_run = -inf; its weights stay 0
-    const float mref = MASKED && m_run == -INFINITY ? 0.f : m_run;
+    // a row that has seen only hidden keys (MASKED) or scores of -inf (a product of a
+    // query and a key that overflows) has m_run = -inf; its weights stay 0
+    const float mref = m_run == -INFINITY ? 0.f : m_run;
     float p[kFlashKB / 16][4], lb = 0.f;
 #pragma unroll
     for (int t = 0; t < kFlashKB / 16; ++t)
