@@ -715,6 +715,9 @@ __global__ __launch_bounds__(kAttnThreads) void attn_partial_kernel(
 // 16 + 4 g .. 16 + 4 g + 3); V's B fragment is read in that order from the
 // transposed copy.  The block's own keys (fp32) come last, in one more block
 // with hi and lo parts in the two buffers and three products per tile.
+// Two waves a SIMD, stated as a launch bound: left to itself the compiler gave the masked
+// 64-row variant four registers too many, and a verify of four chains at 8192 keys took 60.6 us
+// a layer and merge instead of 42.6.
 // MASKED (a verify forward's tree mask, as in attn_partial_kernel): a lane's 16
 // mask bytes of its row and the block keys it scores are loaded with those keys.
 // ---------------------------------------------------------------------------
@@ -734,7 +737,7 @@ DEVI uint32_t pack_lo16(uint32_t a, uint32_t b) { return (a & 0xffffu) | (b << 1
 DEVI uint32_t pack_hi16(uint32_t a, uint32_t b) { return (a >> 16) | (b & 0xffff0000u); }
 
 template <int NW, int PD, bool MASKED>
-__global__ __launch_bounds__(NW * 64) void attn_flash_kernel(const float *__restrict__ Q, const float *__restrict__ Kb,
+__global__ __launch_bounds__(NW * 64, 2) void attn_flash_kernel(const float *__restrict__ Q, const float *__restrict__ Kb,
                                                              const float *__restrict__ Vb, const bf16_t *__restrict__ ck,
                                                              const bf16_t *__restrict__ cv,
                                                              const int32_t *__restrict__ ctx_lens, int max_ctx,
@@ -1289,7 +1292,7 @@ void launch_attention(const Dims &D, const float *Q, const float *Kb, const floa
     if (D.bf16 && D.dh == 128 && (R == 64 || R == 128) && pairs >= 8) {
       const int n_cu = attn_cu_count();
       const int nkeys = max_ctx + D.B;
-      // workgroups resident per CU: two of 4 waves (LDS), one of 8 (registers)
+      // workgroups resident per CU: two of 4 waves, one of 8 (two waves a SIMD, by the launch bounds)
       const long target = std::max(1L, (R == 64 ? 2L : 1L) * n_cu / pairs);
       const int ngrp = (int)std::min(target, (long)(nkeys + kFlashKB - 1) / kFlashKB);
       const int nch = attn_nchunks(max_ctx, D.B);
