@@ -113,15 +113,15 @@ struct LVec<float> {
 // Best (value, id) of the values of NV 16-byte loads of one row, as the 64-bit
 // key of the whole wave: the maximum first (NaN drops out of fmaxf, so it counts
 // as -inf), then the smallest id holding it.  Load q holds ids id0 + q * step ..;
-// ids from v1 on do not count.
+// ids from v1 on do not count (unsigned: loads reach past the largest int vocabulary).
 template <typename LT, int NV>
-DEVI unsigned long long wave_best_key(const u32x4 (&x)[NV], int id0, int step, int v1) {
+DEVI unsigned long long wave_best_key(const u32x4 (&x)[NV], uint32_t id0, uint32_t step, uint32_t v1) {
   constexpr int N = LVec<LT>::N;
   float m[NV], t = -INFINITY;
 #pragma unroll
   for (int q = 0; q < NV; ++q) {
     m[q] = -INFINITY;
-    const int id = id0 + q * step;
+    const uint32_t id = id0 + q * step;
     if (id + N <= v1) {
 #pragma unroll
       for (int e = 0; e < N; ++e) m[q] = fmaxf(m[q], LVec<LT>::get(x[q], e));
@@ -129,32 +129,32 @@ DEVI unsigned long long wave_best_key(const u32x4 (&x)[NV], int id0, int step, i
     t = fmaxf(t, m[q]);
   }
   const float wm = wave_max(t);
-  int best = INT_MAX;
+  uint32_t best = INT_MAX;
 #pragma unroll
   for (int q = 0; q < NV; ++q) {
-    const int id = id0 + q * step;
+    const uint32_t id = id0 + q * step;
     if (id + N <= v1 && m[q] == wm) {
 #pragma unroll
       for (int e = N - 1; e >= 0; --e)
-        if (order_val(LVec<LT>::get(x[q], e)) == wm) best = min(best, id + e);
+        if (order_val(LVec<LT>::get(x[q], e)) == wm) best = min(best, id + (uint32_t)e);
     }
   }
   // (+ 0: a zero's sign is no difference)
-  return wave_max_u64(best == INT_MAX ? 0ull : encode_best(wm + 0.f, best));
+  return wave_max_u64(best == INT_MAX ? 0ull : encode_best(wm + 0.f, (int)best));
 }
 // the same of single values (rows that are not whole 16-byte loads)
 template <int NV>
-DEVI unsigned long long wave_best_key(const float (&x)[NV], int id0, int step, int v1) {
+DEVI unsigned long long wave_best_key(const float (&x)[NV], uint32_t id0, uint32_t step, uint32_t v1) {
   float t = -INFINITY;
 #pragma unroll
   for (int q = 0; q < NV; ++q)
     if (id0 + q * step < v1) t = fmaxf(t, x[q]);
   const float wm = wave_max(t);
-  int best = INT_MAX;
+  uint32_t best = INT_MAX;
 #pragma unroll
   for (int q = NV - 1; q >= 0; --q)
     if (id0 + q * step < v1 && order_val(x[q]) == wm) best = min(best, id0 + q * step);
-  return wave_max_u64(best == INT_MAX ? 0ull : encode_best(wm + 0.f, best));
+  return wave_max_u64(best == INT_MAX ? 0ull : encode_best(wm + 0.f, (int)best));
 }
 
 // Partial argmax over one vocabulary chunk of the rows of nodes that have
@@ -330,20 +330,20 @@ __global__ __launch_bounds__(kWalkThreads) void accept_walk_kernel(int nn, int V
     constexpr int EV = LVec<LT>::N, U = 10;
     unsigned long long best = 0ull;
     if (V % EV == 0) {  // 16-byte rows: U loads of EV values per thread in flight
-      for (int g0 = 0; g0 < V; g0 += kWalkThreads * U * EV) {
+      for (uint32_t g0 = 0; g0 < (uint32_t)V; g0 += kWalkThreads * U * EV) {
         u32x4 x[U];
-        const int id0 = g0 + tid * EV;
+        const uint32_t id0 = g0 + tid * EV;
 #pragma unroll
-        for (int q = 0; q < U; ++q) x[q] = *(const u32x4 *)(row + min(id0 + q * kWalkThreads * EV, V - EV));
+        for (int q = 0; q < U; ++q) x[q] = *(const u32x4 *)(row + min(id0 + q * kWalkThreads * EV, (uint32_t)(V - EV)));
         const unsigned long long o = wave_best_key<LT>(x, id0, kWalkThreads * EV, V);
         best = o > best ? o : best;
       }
     } else {
-      for (int g0 = 0; g0 < V; g0 += kWalkThreads * U) {
+      for (uint32_t g0 = 0; g0 < (uint32_t)V; g0 += kWalkThreads * U) {
         float x[U];
-        const int id0 = g0 + tid;
+        const uint32_t id0 = g0 + tid;
 #pragma unroll
-        for (int q = 0; q < U; ++q) x[q] = ld_logit<LT>(row + min(id0 + q * kWalkThreads, V - 1));
+        for (int q = 0; q < U; ++q) x[q] = ld_logit<LT>(row + min(id0 + q * kWalkThreads, (uint32_t)(V - 1)));
         const unsigned long long o = wave_best_key(x, id0, kWalkThreads, V);
         best = o > best ? o : best;
       }

@@ -76,3 +76,18 @@ def test_sampled_acceptance_edges(V, dtype, offset, mask):
     log(f"V={V} {dtype} offset {offset} {mask}: rows compared {n}/{bs}; accept lengths {ref['accept_len'].tolist()}")
     assert n >= bs // 2
     assert np.all(got["out_tokens"] < keep)
+
+
+@pytest.mark.parametrize("V", [2**31 - 8192, 2**31 - 8191])
+def test_greedy_acceptance_of_the_largest_vocabularies(V):
+    """Ids near 2^31, in 16-byte and in single loads: the leaf's scan steps past the last one."""
+    if torch.cuda.mem_get_info()[0] < 40 << 30:
+        pytest.skip("needs 40 GB of device memory")
+    lg = torch.full((1, 2, V), -1.0, device="cuda:0", dtype=torch.bfloat16)
+    lg[0, 0, V - 5] = lg[0, 1, V - 3] = lg[0, 1, V - 2] = 2.0
+    tok, par = np.array([[7, V - 5]], np.int32), np.array([[-1, 0]], np.int32)
+    got = _accept_gpu(tok, par, lg, 2)
+    assert got["accept_len"].tolist() == [1] and got["accepted_nodes"].tolist() == [[1]]
+    assert got["out_tokens"].tolist() == [[V - 5, V - 3]]
+    del lg
+    torch.cuda.empty_cache()
