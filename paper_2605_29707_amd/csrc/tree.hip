@@ -69,10 +69,10 @@ void launch_build_tree(int bs, int depth, int beta, const int32_t *topk, const i
 // tree, or the end of a fully accepted chain) the bonus token is that row's
 // argmax, which the walk's workgroup scans itself: one row, and only then.
 // workspace: [err:int32][pad to 256 B][partials: 64-bit best keys bs*nn*nchunk]
-// 32 rows x 61 nodes (17 with children) x 151936 bf16 logits, 156 MB read: 40 us
-// while a workgroup took 8 neighbouring node rows (two of them with children) and
-// 43 us for a walk that scanned the leaf's 300 KB with 256 threads; now 29 us
-// and 11.
+// 32 rows x 61 nodes (15 with children) x 151936 bf16 logits: 146 MB of rows and, where
+// the walk ends on a leaf, 0.3 MB more a batch row.  40 us while a workgroup took 8 neighbouring
+// node rows (two of them with children) and 43 us for a walk that scanned the leaf
+// with 256 threads; now 29 us and 12.
 // ---------------------------------------------------------------------------
 constexpr int ACH = 4096;  // vocabulary elements per argmax chunk
 
@@ -142,19 +142,19 @@ DEVI unsigned long long wave_best_key(const u32x4 (&x)[NV], uint32_t id0, uint32
   // (+ 0: a zero's sign is no difference)
   return wave_max_u64(best == INT_MAX ? 0ull : encode_best(wm + 0.f, (int)best));
 }
-// the same of single values (rows that are not whole 16-byte loads)
+// the same of single values (rows that are not whole 16-byte loads): ids grow
+// within a thread, so a strict comparison keeps the smallest id of equal values
 template <int NV>
 DEVI unsigned long long wave_best_key(const float (&x)[NV], uint32_t id0, uint32_t step, uint32_t v1) {
-  float t = -INFINITY;
+  float bv = -INFINITY;
+  uint32_t bi = id0 < v1 ? id0 : INT_MAX;
 #pragma unroll
   for (int q = 0; q < NV; ++q)
-    if (id0 + q * step < v1) t = fmaxf(t, x[q]);
-  const float wm = wave_max(t);
-  uint32_t best = INT_MAX;
-#pragma unroll
-  for (int q = NV - 1; q >= 0; --q)
-    if (id0 + q * step < v1 && order_val(x[q]) == wm) best = min(best, id0 + q * step);
-  return wave_max_u64(best == INT_MAX ? 0ull : encode_best(wm + 0.f, (int)best));
+    if (id0 + q * step < v1 && x[q] > bv) {  // (a NaN is no more than -inf)
+      bv = x[q];
+      bi = id0 + q * step;
+    }
+  return wave_max_u64(bi == INT_MAX ? 0ull : encode_best(bv + 0.f, (int)bi));
 }
 
 // Partial argmax over one vocabulary chunk of the rows of nodes that have
@@ -162,14 +162,20 @@ DEVI unsigned long long wave_best_key(const float (&x)[NV], uint32_t id0, uint32
 // workgroup lists those rows of its batch row (a few loads that hit the L2) and
 // takes entries y, y + gridDim.y, ... of the list, two rows in flight: the
 // work is split by rows that are read, wherever they lie among the leaves.
-// Rows are 16-byte aligned when V is a multiple of 8 (bf16) or 4 (fp32); then
-// every value comes from 16-byte loads, otherwise one value per load.  The
-// first workgroup also clears the error word (only the walk, a later launch,
-// raises errors).
+// kVals = 0: every value comes from 16-byte loads (rows are 16-byte aligned when V is
+// a multiple of 8 (bf16) or 4 (fp32)); otherwise one value per load, kVals a
+// thread (1 where a row has no more than 256).  The first workgroup also clears the
+// error word (only the walk, a later launch, raises errors).
+//
+// Many small rows are bound by the workgroups in flight, so the registers are held
+// to 64 (eight workgroups a CU; 16 single values take 100: five), and a workgroup with one
+// row loads no second one: chains of 128 rows x 4000 fp32 logits 11.8 us with 80
+// registers and two rows always, 7.0 now.  Single values are compared in one pass, not two
+// as vectors are: 32 rows x 50257 bf16 logits 22.1 and 13.3 us.
 constexpr int kWalkMaxNodes = 1024;
 
-template <typename LT>
-__global__ __launch_bounds__(256) void argmax_partial_kernel(int nn, int V, const LT *__restrict__ logits,
+template <typename LT, int kVals>
+__global__ __launch_bounds__(256, kVals > 1 ? 4 : 8) void argmax_partial_kernel(int nn, int V, const LT *__restrict__ logits,
                                                              const int32_t *__restrict__ par,
                                                              unsigned long long *__restrict__ part, int32_t *err) {
   constexpr int EV = LVec<LT>::N, VPT = ACH / EV / 256;  // 16-byte loads per thread and row
@@ -209,33 +215,46 @@ __global__ __launch_bounds__(256) void argmax_partial_kernel(int nn, int V, cons
       part[((size_t)b * nn + s_list[k]) * nch + ch] = o;
     }
   };
-  if (V % EV == 0) {
-    u32x4 x[2][VPT];
-    const int id0 = v0 + tid * EV;
-    auto load = [&](u32x4 (&y)[VPT], int k) {  // clamped within the list and the row: every load valid
-      const LT *row = logits + ((size_t)b * nn + s_list[min(k, n - 1)]) * V;
-#pragma unroll
-      for (int q = 0; q < VPT; ++q) y[q] = __builtin_nontemporal_load((const u32x4 *)(row + min(id0 + q * 256 * EV, V - EV)));
-    };
+  // entries k, k + ys, ...: the next row's loads go out before this one's
+  // values are used; a workgroup with one row loads no other
+  auto rows = [&](auto &x, auto load, auto key) {
     int k = blockIdx.y;
     if (k >= n) return;  // uniform
     load(x[0], k);
-    for (; k < n; k += 2 * ys) {
-      load(x[1], k + ys);
-      finish(k, 0, wave_best_key<LT>(x[0], id0, 256 * EV, v1));
-      load(x[0], k + 2 * ys);
-      if (k + ys < n) finish(k + ys, 1, wave_best_key<LT>(x[1], id0, 256 * EV, v1));
+    if (k + ys >= n) {
+      finish(k, 0, key(x[0]));
+      return;
     }
-    return;
-  }
-  int slot = 0;
-  for (int k = blockIdx.y; k < n; k += ys, slot ^= 1) {
-    const LT *row = logits + ((size_t)b * nn + s_list[k]) * V;
-    constexpr int PER = ACH / 256;
-    float x[PER];
+    for (; k < n; k += 2 * ys) {  // clamped within the list: every load valid
+      load(x[1], k + ys);
+      finish(k, 0, key(x[0]));
+      load(x[0], k + 2 * ys);
+      if (k + ys < n) finish(k + ys, 1, key(x[1]));
+    }
+  };
+  auto row = [&](int k) { return logits + ((size_t)b * nn + s_list[min(k, n - 1)]) * V; };
+  if constexpr (kVals == 0) {
+    u32x4 x[2][VPT];
+    const int id0 = v0 + tid * EV;
+    auto load = [&](u32x4 (&y)[VPT], int k) {
+      const LT *r = row(k);
 #pragma unroll
-    for (int q = 0; q < PER; ++q) x[q] = ld_logit<LT>(row + min(v0 + tid + q * 256, v1 - 1));
-    finish(k, slot, wave_best_key(x, v0 + tid, 256, v1));
+      for (int q = 0; q < VPT; ++q) y[q] = __builtin_nontemporal_load((const u32x4 *)(r + min(id0 + q * 256 * EV, V - EV)));
+    };
+    rows(x, load, [&](const u32x4 (&y)[VPT]) { return wave_best_key<LT>(y, id0, 256 * EV, v1); });
+  } else {
+    LT x[2][kVals];
+    auto load = [&](LT (&y)[kVals], int k) {
+      const LT *r = row(k);
+#pragma unroll
+      for (int q = 0; q < kVals; ++q) y[q] = r[min(v0 + tid + q * 256, v1 - 1)];
+    };
+    rows(x, load, [&](const LT (&y)[kVals]) {
+      float f[kVals];
+#pragma unroll
+      for (int q = 0; q < kVals; ++q) f[q] = to_f32(y[q]);
+      return wave_best_key(f, v0 + tid, 256, v1);
+    });
   }
 }
 
@@ -246,12 +265,12 @@ __global__ __launch_bounds__(256) void argmax_partial_kernel(int nn, int V, cons
 // first child of each node whose token is that R.  The walk from the root is
 // then a chase through LDS.  Only if it stops on a node without children (a
 // leaf of a tree, or the end of a fully accepted chain) is that row's argmax
-// needed, which the workgroup scans itself: 16 waves, so that one CU has a whole
-// 300 KB row in flight in two passes.
-
-constexpr int kWalkThreads = 1024;
-
-template <typename LT>
+// needed, which the workgroup scans itself: with 8 waves, and 16 where the row is longer
+// than two passes of 8 (160 KB in 16-byte loads).  16 waves against 8 for one chain:
+// 9.5 and 7.3 us at 32000 bf16 logits, 11.9 and 11.8 at 128256 (a tree 10.9 and 12.3); for
+// 512 chains of 100 logits 11.8 and 7.5.
+constexpr int kWalkLoads = 10;  // in flight a thread
+template <typename LT, int kWalkThreads>
 __global__ __launch_bounds__(kWalkThreads) void accept_walk_kernel(int nn, int V, int B,
                                                                    const int32_t *__restrict__ tok,
                                                                    const int32_t *__restrict__ par,
@@ -327,7 +346,7 @@ __global__ __launch_bounds__(kWalkThreads) void accept_walk_kernel(int nn, int V
   }
   if (leaf) {  // the bonus token: the argmax of this row, scanned here
     const LT *row = logits + ((size_t)b * nn + cur) * V;
-    constexpr int EV = LVec<LT>::N, U = 10;
+    constexpr int EV = LVec<LT>::N, U = kWalkLoads;
     unsigned long long best = 0ull;
     if (V % EV == 0) {  // 16-byte rows: U loads of EV values per thread in flight
       for (uint32_t g0 = 0; g0 < (uint32_t)V; g0 += kWalkThreads * U * EV) {
@@ -375,15 +394,25 @@ void launch_accept_parts(int bs, int nn, int V, int B, const int32_t *tok, const
                          const void *logits, bool bf16, int32_t *acc_len, int32_t *acc_nodes,
                          int32_t *out_tok, void *part, int32_t *err, hipStream_t st) {
   const int nch = (V + ACH - 1) / ACH;
-  // about 2048 workgroups (8 a CU): a row each while there are few, several each for large batches
-  const int ys = (int)std::max(1L, std::min((long)nn, 2048L / ((long)nch * bs)));
+  // as many workgroups as the chip holds (8 a CU, 5 of those with 16 single values a thread):
+  // a row each while there are few, several each for large batches
+  const bool wide = V % (bf16 ? 8 : 4) == 0;
+  const long fit = 256L * (wide || V <= 256 ? 8 : 5);
+  const int ys = (int)std::max(1L, std::min((long)nn, fit / ((long)nch * bs)));
   const dim3 grid(nch, ys, bs);
   auto go = [&](auto *lg) {
     using LT = std::remove_cv_t<std::remove_pointer_t<decltype(lg)>>;
     unsigned long long *p = (unsigned long long *)part;
-    hipLaunchKernelGGL(argmax_partial_kernel<LT>, grid, dim3(256), 0, st, nn, V, lg, par, p, err);
-    hipLaunchKernelGGL(accept_walk_kernel<LT>, dim3(bs), dim3(kWalkThreads), 0, st, nn, V, B, tok, par,
-                       (const unsigned long long *)p, lg, acc_len, acc_nodes, out_tok, err);
+    auto argmax = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, nn, V, lg, par, p, err); };
+    if (wide) argmax(argmax_partial_kernel<LT, 0>);
+    else if (V <= 256) argmax(argmax_partial_kernel<LT, 1>);
+    else argmax(argmax_partial_kernel<LT, ACH / 256>);
+    auto walk = [&](auto kernel, int threads) {
+      hipLaunchKernelGGL(kernel, dim3(bs), dim3(threads), 0, st, nn, V, B, tok, par, (const unsigned long long *)p, lg,
+                         acc_len, acc_nodes, out_tok, err);
+    };
+    if (V <= 2L * 512 * kWalkLoads * (wide ? LVec<LT>::N : 1)) walk(accept_walk_kernel<LT, 512>, 512);
+    else walk(accept_walk_kernel<LT, 1024>, 1024);
   };
   if (bf16) go((const bf16_t *)logits);
   else go((const float *)logits);

@@ -19,7 +19,9 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("V,dtype,bs,beta", [(9, "f32", 1, 1), (12, "bf16", 3, 2),
                                                      (4097, "bf16", 40, 8), (8200, "bf16", 33, 3),
-                                                     (8200, "f32", 5, 4), (4100, "bf16", 2, 1)])
+                                                     (8200, "f32", 5, 4), (4100, "bf16", 2, 1),
+                                                     # one value a thread, a chunk of one; 16 waves of single values
+                                                     (251, "bf16", 160, 1), (257, "f32", 2, 4), (50257, "bf16", 3, 2)])
 def test_greedy_acceptance_edges(V, dtype, bs, beta):
     rng = np.random.default_rng(V + bs)
     cfg = synth.get_config("tiny").with_(batch=bs, branch=beta, vocab=V)

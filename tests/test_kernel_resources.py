@@ -36,6 +36,9 @@ def kernels(tmp_path_factory):
 @pytest.mark.parametrize("pattern,count,regs", [
     # two workgroups of four waves a CU, one of eight
     (r"dk::attn_flash_kernel<", 4, 256),
+    # eight workgroups of four waves a CU; five with 16 single values a thread
+    (r"dk::argmax_partial_kernel<\w+, [01]>", 4, 64),
+    (r"dk::argmax_partial_kernel<\w+, 16>", 2, 102),
 ])
 def test_registers_and_scratch(kernels, pattern, count, regs):
     found = {n: v for n, v in kernels.items() if re.match(pattern, n)}
