@@ -266,9 +266,9 @@ __global__ __launch_bounds__(256, kVals > 1 ? 4 : 8) void argmax_partial_kernel(
 // then a chase through LDS.  Only if it stops on a node without children (a
 // leaf of a tree, or the end of a fully accepted chain) is that row's argmax
 // needed, which the workgroup scans itself: with 8 waves, and 16 where the row is longer
-// than two passes of 8 (160 KB in 16-byte loads).  16 waves against 8 for one chain:
-// 9.5 and 7.3 us at 32000 bf16 logits, 11.9 and 11.8 at 128256 (a tree 10.9 and 12.3); for
-// 512 chains of 100 logits 11.8 and 7.5.
+// than one and a half passes of 8 (120 KB in 16-byte loads).  16 waves against 8 for one
+// chain: 9.5 and 7.3 us at 32000 bf16 logits, 11.9 and 11.8 at 128256 (a tree 10.9 and
+// 12.3); for 512 chains of 100 logits 11.8 and 7.5.
 constexpr int kWalkLoads = 10;  // in flight a thread
 template <typename LT, int kWalkThreads>
 __global__ __launch_bounds__(kWalkThreads) void accept_walk_kernel(int nn, int V, int B,
@@ -395,10 +395,13 @@ void launch_accept_parts(int bs, int nn, int V, int B, const int32_t *tok, const
                          int32_t *out_tok, void *part, int32_t *err, hipStream_t st) {
   const int nch = (V + ACH - 1) / ACH;
   // as many workgroups as the chip holds (8 a CU, 5 of those with 16 single values a thread):
-  // a row each while there are few, several each for large batches
+  // a row each while there are few, several each for large batches.  Where one a chunk
+  // and batch row are more than that, two, of half the rows each, while the last
+  // round weighs (64 rows x 151936 bf16 logits 65 us with one, 56 with two; 300 x
+  // 100000 158 and 161).  Not for fp32 rows in 16-byte loads (102 and 114).
   const bool wide = V % (bf16 ? 8 : 4) == 0;
-  const long fit = 256L * (wide || V <= 256 ? 8 : 5);
-  const int ys = (int)std::max(1L, std::min((long)nn, fit / ((long)nch * bs)));
+  const long fit = 256L * (wide || V <= 256 ? 8 : 5), one = (long)nch * bs;
+  const int ys = (int)std::min((long)nn, one <= fit ? fit / one : one <= 3 * fit && (bf16 || !wide) ? 2L : 1L);
   const dim3 grid(nch, ys, bs);
   auto go = [&](auto *lg) {
     using LT = std::remove_cv_t<std::remove_pointer_t<decltype(lg)>>;
@@ -411,7 +414,7 @@ void launch_accept_parts(int bs, int nn, int V, int B, const int32_t *tok, const
       hipLaunchKernelGGL(kernel, dim3(bs), dim3(threads), 0, st, nn, V, B, tok, par, (const unsigned long long *)p, lg,
                          acc_len, acc_nodes, out_tok, err);
     };
-    if (V <= 2L * 512 * kWalkLoads * (wide ? LVec<LT>::N : 1)) walk(accept_walk_kernel<LT, 512>, 512);
+    if (2L * V <= 3L * 512 * kWalkLoads * (wide ? LVec<LT>::N : 1)) walk(accept_walk_kernel<LT, 512>, 512);
     else walk(accept_walk_kernel<LT, 1024>, 1024);
   };
   if (bf16) go((const bf16_t *)logits);
