@@ -12,12 +12,15 @@
 //          row, the (max, sum exp) pair of its vocabulary slice for the base and
 //          the final logits, and the wave holding the label writes the
 //          label's two logits.  A workgroup walks the rows 16 at a time with the
-//          next 16's operands in flight and one barrier each.  240 rows of
-//          151936 logits: 165 us while every workgroup formed every u itself,
+//          next 16's operands loaded during the products and one barrier each.  240
+//          rows of 151936 logits: 165 us while every workgroup formed every u itself,
 //          loaded after each barrier and used expf, 120 while the waves' pairs
-//          were merged through LDS; now 108, against 35 us for the bytes (W2
-//          and L_base) and 17 for the products: two waves a SIMD, which spend
-//          most of it on the exponentials between the barriers.
+//          were merged through LDS, 102 while the L_base values in flight were structs,
+//          which the compiler kept in private memory and so waited for at once; now 94, against
+//          35 us for the bytes (W2 and L_base) and 17 for the products.  Two waves a
+//          SIMD, 256 registers each, are not quite enough: one of the five L_base
+//          fragments and some addresses spill (32 bytes of scratch a lane), and its store waits for
+//          the loads, so that only the products hide them and the exponentials do not.
 //   ce_row a workgroup per row merges the pairs (CE = log-sum-exp - label logit);
 //   loss   one wave: the position-weighted means (weights exp(-k / gamma), k = 0
 //          for the first draft position) and the curriculum mix
@@ -88,14 +91,14 @@ __global__ __launch_bounds__(kCeWaves * 64) void train_ce_kernel(TrainArgs t) {
   __shared__ u32x4 us[2][KS * 64 * XF];        // U tile as B fragments
   // L_base of the tile in work, a lane's own values: parked here because the
   // registers hold this wave's W2 fragments and the next tile's loads
-  __shared__ float4 lbs[kCeWaves][kTPW][64];
+  __shared__ floatx4 lbs[kCeWaves][kTPW][64];
 
   int tiles[kTPW];
 #pragma unroll
   for (int q = 0; q < kTPW; ++q) tiles[q] = (blockIdx.x * kCeWaves + wave) * kTPW + q;
   // this wave's W2 fragments, loaded once and reused for every row tile: the
-  // last of five tiles in LDS, because with all of them in registers some value
-  // spills, and a spill's reload waits for every load issued before it, the next
+  // last of five tiles in LDS, because with all of them in registers values of the
+  // products spill, and a spill's reload waits for every load issued before it, the next
   // rows' operands included (153 us instead of 120)
   constexpr int kReg = kTPW > 4 ? 4 : kTPW;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -117,7 +120,7 @@ __global__ __launch_bounds__(kCeWaves * 64) void train_ce_kernel(TrainArgs t) {
   // weight tile (rows are padded to whole tiles: the float4 stays inside the row)
   const u32x4 *uf = (const u32x4 *)t.uf;
   u32x4 ur[kUV];
-  float4 lb[kTPW];
+  floatx4 lb[kTPW];
   int label = 0;
   auto load = [&](int rt) {
     rt = min(rt, nrt - 1);
@@ -126,7 +129,7 @@ __global__ __launch_bounds__(kCeWaves * 64) void train_ce_kernel(TrainArgs t) {
     const int rowc = min(16 * rt + cc, Mr - 1);
 #pragma unroll
     for (int q = 0; q < kTPW; ++q)
-      lb[q] = *(const float4 *)(t.Lbase + (size_t)rowc * t.ldl + min(tiles[q], NT - 1) * 16 + 4 * g);
+      lb[q] = *(const floatx4 *)(t.Lbase + (size_t)rowc * t.ldl + min(tiles[q], NT - 1) * 16 + 4 * g);
     label = t.labels[rowc];
   };
   load(0);
@@ -169,12 +172,12 @@ __global__ __launch_bounds__(kCeWaves * 64) void train_ce_kernel(TrainArgs t) {
       constexpr bool kMasked = decltype(masked)::value;
 #pragma unroll
       for (int q = 0; q < kTPW; ++q) {
-        const float4 l4 = lbs[wave][q][lane];
+        const floatx4 l4 = lbs[wave][q][lane];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const int n = tiles[q] * 16 + 4 * g + e;
           const bool ok = !kMasked || n < V;
-          const float base = e == 0 ? l4.x : (e == 1 ? l4.y : (e == 2 ? l4.z : l4.w));
+          const float base = l4[e];
           const float fin = base + acc[q][0][e];
           if (FINAL && ok && row < Mr) t.final_logits[(size_t)row * V + n] = fin;
           lab_b = n == lab ? base : lab_b;
@@ -194,11 +197,11 @@ __global__ __launch_bounds__(kCeWaves * 64) void train_ce_kernel(TrainArgs t) {
       const float rb = mb == -INFINITY ? 0.f : mb, rf = mf == -INFINITY ? 0.f : mf;
 #pragma unroll
       for (int q = 0; q < kTPW; ++q) {
-        const float4 l4 = lbs[wave][q][lane];
+        const floatx4 l4 = lbs[wave][q][lane];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const bool ok = !kMasked || tiles[q] * 16 + 4 * g + e < V;
-          const float base = ok ? order_val(e == 0 ? l4.x : (e == 1 ? l4.y : (e == 2 ? l4.z : l4.w))) : -INFINITY;
+          const float base = ok ? order_val(l4[e]) : -INFINITY;
           sb += __builtin_amdgcn_exp2f((base - rb) * kLog2e);
           sf += __builtin_amdgcn_exp2f((acc[q][0][e] - rf) * kLog2e);
         }

@@ -33,15 +33,17 @@ def kernels(tmp_path_factory):
 
 
 # (name, most registers, most scratch): 256 registers leave two waves a SIMD, 64 eight
-@pytest.mark.parametrize("pattern,count,regs", [
+@pytest.mark.parametrize("pattern,count,regs,spill", [
     # two workgroups of four waves a CU, one of eight
-    (r"dk::attn_flash_kernel<", 4, 256),
+    (r"dk::attn_flash_kernel<", 4, 256, 0),
     # eight workgroups of four waves a CU; five with 16 single values a thread
-    (r"dk::argmax_partial_kernel<\w+, [01]>", 4, 64),
-    (r"dk::argmax_partial_kernel<\w+, 16>", 2, 102),
+    (r"dk::argmax_partial_kernel<\w+, [01]>", 4, 64, 0),
+    (r"dk::argmax_partial_kernel<\w+, 16>", 2, 102, 0),
+    # the operands in flight in registers: one fragment spills, no array of them lies in private memory
+    (r"dk::train_ce_kernel<", 6, 256, 32),
 ])
-def test_registers_and_scratch(kernels, pattern, count, regs):
+def test_registers_and_scratch(kernels, pattern, count, regs, spill):
     found = {n: v for n, v in kernels.items() if re.match(pattern, n)}
     assert len(found) == count, sorted(kernels)
     for name, (vgprs, scratch) in found.items():
-        assert vgprs <= regs and scratch == 0, (name, vgprs, scratch)
+        assert vgprs <= regs and scratch <= spill, (name, vgprs, scratch)
