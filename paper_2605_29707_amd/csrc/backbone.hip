@@ -11,26 +11,6 @@
 
 namespace dk {
 
-template <typename WT>
-__global__ __launch_bounds__(256) void embed_block_kernel(const WT *__restrict__ embed,
-                                                          const int32_t *__restrict__ anchor,
-                                                          float *__restrict__ X, int B, int d, int V,
-                                                          int mask_id, int32_t *err) {
-  const int row = blockIdx.x;
-  const int b = row / B, j = row % B;
-  int tok = mask_id;
-  if (j == 0) {
-    tok = anchor[b];
-    if (tok < 0 || tok >= V) {
-      if (threadIdx.x == 0) raise_error(err, DEV_BAD_TOKEN);
-      tok = tok < 0 ? 0 : V - 1;
-    }
-  }
-  const WT *src = embed + (size_t)tok * d;
-  float *dst = X + (size_t)row * d;
-  for (int c = threadIdx.x; c < d; c += blockDim.x) dst[c] = to_f32(src[c]);
-}
-
 // x_out[in_row] = x[in_row] + the `np` (<= 16) partial outputs (split order),
 // y[i] = RMSNorm(x_out[in_row]) * gain.  With skip_anchor, output row i reads
 // input row i + i/(B-1) + 1 (the draft rows of each block); a null x_out skips
@@ -1117,17 +1097,6 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float *__restri
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
-void launch_embed_block(const Dims &D, const void *embed, const int32_t *anchor, float *X,
-                        int32_t *err, hipStream_t st) {
-  dim3 grid(D.bs * D.B);
-  if (D.bf16)
-    hipLaunchKernelGGL(embed_block_kernel<bf16_t>, grid, dim3(256), 0, st, (const bf16_t *)embed, anchor,
-                       X, D.B, D.d, D.V, D.mask_id, err);
-  else
-    hipLaunchKernelGGL(embed_block_kernel<float>, grid, dim3(256), 0, st, (const float *)embed, anchor, X,
-                       D.B, D.d, D.V, D.mask_id, err);
-}
-
 template <typename WT, int MAXP>
 static void add_norm_t(const Dims &D, const float *x, float *x_out, int ldx, const float *parts, int np, size_t pstride,
                        const void *gain, float *y, int ldy, int rows, int width, bool skip_anchor,

@@ -107,16 +107,14 @@ __global__ __launch_bounds__(NW * 64) void gemm_rows_kernel(GemmArgs a, int nrb)
       for (int e = 0; e < 4; ++e) gain[e] = ((const bf16_t *)a.res_gain)[n0 + e];
     }
   }
-  if constexpr (EPI == EPI_SWIGLU) {
-    if (a.rs_ssq) {  // row sums of squares: thread (q, m) adds the groups q, q + 4 NW, ...
+  if constexpr (EPI == EPI_SWIGLU) {  // row sums of squares: thread (q, m) adds the groups q, q + 4 NW, ...
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
-        const int m = min(mt * 16 + (tid & 15), a.M - 1);
-        float t = 0.f;
+    for (int mt = 0; mt < MT; ++mt) {
+      const int m = min(mt * 16 + (tid & 15), a.M - 1);
+      float t = 0.f;
 #pragma unroll 8
-        for (int q = tid >> 4; q < a.rs_ng; q += NW * 4) t += a.rs_ssq[(size_t)q * a.M + m];
-        rs_part[tid >> 4][mt * 16 + (tid & 15)] = t;
-      }
+      for (int q = tid >> 4; q < a.rs_ng; q += NW * 4) t += a.rs_ssq[(size_t)q * a.M + m];
+      rs_part[tid >> 4][mt * 16 + (tid & 15)] = t;
     }
   }
 
@@ -178,13 +176,10 @@ __global__ __launch_bounds__(NW * 64) void gemm_rows_kernel(GemmArgs a, int nrb)
       const int tile = grp * CT + t / MT * 2, m = (t % MT) * 16 + cc;
       if (tile + 1 >= a.ntiles || m >= a.M) continue;
       const floatx4 vg = total((t / MT * 2) * MT + t % MT), vu = total((t / MT * 2 + 1) * MT + t % MT);
-      float rs = 1.f;
-      if (a.rs_ssq) {
-        float ss = 0.f;
+      float ss = 0.f;
 #pragma unroll
-        for (int q = 0; q < NW * 4; ++q) ss += rs_part[q][m];
-        rs = 1.0f / sqrtf(ss / (float)a.rs_d + a.rs_eps);
-      }
+      for (int q = 0; q < NW * 4; ++q) ss += rs_part[q][m];
+      const float rs = 1.0f / sqrtf(ss / (float)a.rs_d + a.rs_eps);
       float o[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) o[e] = silu_r(vg[e] * rs) * (vu[e] * rs);
@@ -296,6 +291,7 @@ bool launch_gemm_rows(int epi, const GemmArgs &a, const GemmPlan &p, hipStream_t
   // whole k-steps, one or two row blocks, planes for the input (and the output where it is planes)
   if (a.K != a.KS * 32 || a.M <= 0 || a.M > 16 * p.MT || p.MT > 2 || !a.xf || a.X) return false;
   if (epi != EPI_STORE && (!a.yf || a.N % 32)) return false;
+  if (epi == EPI_SWIGLU && (!a.rs_ssq || a.rs_ng <= 0 || a.rs_d <= 0)) return false;
   if (epi == EPI_RESID && (!a.res_in || !a.res_out || !a.res_ssq || !a.res_gain || a.ldy % 4 || a.N != a.ntiles * 16))
     return false;
   const int nrb = (a.M + 15) / 16;

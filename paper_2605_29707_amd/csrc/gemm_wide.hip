@@ -78,9 +78,9 @@ __global__ __launch_bounds__(256) void split_frag_kernel(const float *__restrict
 }
 
 // Workgroup order (a 1-D grid, workgroup L on XCD L % 8): the workgroups of
-// one (column group, K split) pair u, one per row group, are L = (8 c + mz) *
-// ... such that they share L % 8 and are dispatched 8 apart, so the second row
-// group finds the weight tiles in its XCD's L2 instead of reading them again.
+// one (column group, K split) pair u = 8 c + x, one per row group mz, are
+// L = 8 (c mgroups + mz) + x: they share L % 8 and are dispatched 8 apart, so the second
+// row group finds the weight tiles in its XCD's L2 instead of reading them again.
 struct WideMap {
   int groups, ksplit, mgroups;
 };
@@ -261,23 +261,20 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(1,
         float o[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) o[e] = silu_w(acc[c][j][e]) * acc[c + (c + 1 < CT ? 1 : 0)][j][e];
-        if (a.yf) {  // the next projection's fragment planes: 8 bytes of the lane's 16 (N is a multiple of 32)
-          const int KSo = a.N / 32;
-          const size_t at =
-              (((size_t)(m >> 4) * KSo + (col >> 5)) * 64 + 16 * ((col >> 3) & 3) + (m & 15)) * 2 + ((col >> 2) & 1);
-          const float o8[8] = {o[0], o[1], o[2], o[3], 0.f, 0.f, 0.f, 0.f};
-          bf16x8 hi, lo;
-          split8(o8, hi, lo);
-          const u32x4 hu = __builtin_bit_cast(u32x4, hi), lu = __builtin_bit_cast(u32x4, lo);
-          uint2 *pf = (uint2 *)a.yf;
-          pf[at] = make_uint2(hu[0], hu[1]);
-          pf[(size_t)nrb * KSo * 128 + at] = make_uint2(lu[0], lu[1]);
-          continue;
-        }
-        float *y = Y + (size_t)m * a.ldy + col;
+        // rounded to fp32 before the split: the last product is not to be fused into its subtraction
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (col + e < a.N) y[e] = o[e];
+        for (int e = 0; e < 4; ++e) __asm__("" : "+v"(o[e]));
+        // the next projection's fragment planes: 8 bytes of the lane's 16 (N is a multiple of 32)
+        const int KSo = a.N / 32;
+        const size_t at =
+            (((size_t)(m >> 4) * KSo + (col >> 5)) * 64 + 16 * ((col >> 3) & 3) + (m & 15)) * 2 + ((col >> 2) & 1);
+        const float o8[8] = {o[0], o[1], o[2], o[3], 0.f, 0.f, 0.f, 0.f};
+        bf16x8 hi, lo;
+        split8(o8, hi, lo);
+        const u32x4 hu = __builtin_bit_cast(u32x4, hi), lu = __builtin_bit_cast(u32x4, lo);
+        uint2 *pf = (uint2 *)a.yf;
+        pf[at] = make_uint2(hu[0], hu[1]);
+        pf[(size_t)nrb * KSo * 128 + at] = make_uint2(lu[0], lu[1]);
       }
     } else {
       if (tile >= a.ntiles) continue;
@@ -395,7 +392,7 @@ bool launch_gemm_wide(int epi, const GemmArgs &a, const GemmPlan &p, hipStream_t
   // the activation loads assume whole k-steps (K = 32 KS) and at least one row;
   // the model's config checks guarantee both for every projection
   if (a.K != a.KS * 32 || a.M <= 0 || (a.X && a.ldx < a.K) || !a.xf) return false;
-  if (a.yf && (epi != EPI_SWIGLU || a.N % 32)) return false;
+  if ((epi == EPI_SWIGLU) != (a.yf != nullptr) || (a.yf && a.N % 32)) return false;
   const int nrb = (a.M + 15) / 16;
   const size_t items = (size_t)nrb * a.KS * 64;
   if (a.X)  // not split by its producer

@@ -27,8 +27,8 @@ struct GemmArgs {
                        // (gemm_wide_scratch_bytes(M, K) bytes): written by the producer (X null)
                        // or by the launch itself, from X
   void *yf = nullptr;  // rows and wide kernels: output as fragment planes (N / 32 k-steps):
-                       // of SwiGLU instead of Y, of the residual times the gain
-  // Deferred RMSNorm of the activations (rows kernel, EPI_SWIGLU): the planes hold
+                       // SwiGLU's (in place of Y), the residual's times the gain
+  // Deferred RMSNorm of the activations (rows kernel, EPI_SWIGLU always): the planes hold
   // x * gain and every output row m is scaled by rsqrt(sum_g rs_ssq[g][m] / rs_d +
   // rs_eps), the per-row sums of squares left by the producing EPI_RESID.
   const float *rs_ssq = nullptr;
@@ -89,8 +89,6 @@ struct Dims {
   const double *inv_freq;  // device [dh/2]: theta^(-2i/dh), fp64
 };
 
-void launch_embed_block(const Dims &D, const void *embed, const int32_t *anchor, float *X,
-                        int32_t *err, hipStream_t st);
 // x_out[map(row)] = x[map(row)] + sum of np partials (pstride floats apart),
 // y[row] = rmsnorm(x_out[map(row)]) * gain; with skip_anchor, output row i
 // reads input row i + i/(B-1) + 1 (the draft rows of each block).  x_out
