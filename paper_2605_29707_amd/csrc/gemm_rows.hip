@@ -10,18 +10,17 @@
 // workgroup, straight into registers beside the CT weight fragments, D k-steps
 // ahead.  There is no LDS and no barrier until the waves' sums meet at the end
 // (added in wave order).  The skinny kernel (gemm.hip) stages fp32 activations
-// through LDS, split by every workgroup, with a barrier per chunk: at 16 rows of
-// the 8B shape gate/up takes 32.4 us here against 36.7 there (a bare read of its
-// weights in this launch shape 31.0), QKV 9.6 against 11.0, down 17.3 against 19.1.
+// through LDS, split by every workgroup, with a barrier per chunk: in a step of 16
+// rows of the 8B shape gate/up takes 33.5 us here against 36.9 there (a bare read of its
+// weights in this launch shape 31.0), QKV 10.3 against 12.0, down 18.5 against 19.4.
 //
 // O ends with the residual update (EPI_RESID): one tile over all of K per
-// workgroup, so no sum crosses workgroups (9.4 us and the epilogue, against 8.2
-// for a K split whose partials then cost 5 us more, be it in a launch of their
-// own or behind a ticket).  The RMSNorm that follows is deferred: the epilogue
+// workgroup, so no sum crosses workgroups (10.4 us with the epilogue, against 13.1
+// for K splits that meet behind a ticket).  The RMSNorm that follows is deferred: the epilogue
 // leaves x times the norm's gain as the next projection's planes and each
 // tile's row sums of squares, and gate/up scales its sums by
 // rsqrt(sum / d + eps): the norm factor of a row is one number.  Down is three
-// times longer and keeps its K split (17.3 us against 23.9 unsplit); the next
+// times longer and keeps its K split (4 splits 18.5 us, 2 of the same tiles 26.8); the next
 // RMSNorm's launch adds its partials.
 #include "common.h"
 #include "kernels.h"
@@ -251,7 +250,8 @@ bool launch_mt(int epi, const GemmArgs &a, const GemmPlan &p, int nrb, hipStream
 // its workgroups' weights and activations (every k-step 1 KB a tile and 2 KB a
 // row block) and the split's partial outputs, written and read back, which count
 // sixteenfold (they come after the last product, and a consumer waits for them:
-// QKV 3 tiles x 2 splits 9.6 us, 6 x 4 11.4; down 4 x 4 17.3, 8 x 8 19.4).  On the
+// QKV 3 tiles x 2 splits 10.3 us, 6 x 4 11.0, 3 unsplit 15.1; down 4 x 4 18.5 and 5.2 for
+// the RMSNorm that adds its partials, 8 x 8 19.0 and 6.9).  On the
 // 8B shape at 16 rows it takes 6 tiles for gate/up, 3 x 2 splits for QKV and 4 x
 // 4 for down, each the fastest of those measured.  EPI_RESID: one tile, no split.
 GemmPlan plan_gemm_rows(int ntiles, int KS, int M, int epi, int n_cu, int max_split) {

@@ -771,7 +771,7 @@ __global__ __launch_bounds__(64) void head_merge_kernel(HeadArgs h, int nlist) {
 // ---------------------------------------------------------------------------
 // Persistent rollout (bf16 weights, r = 256, up to eight batch rows, greedy or
 // sampled): one launch of at most one workgroup per CU runs all B-1 positions
-// (137 us at one row of the Qwen3 vocabulary, 302 at four, which took 412 as two
+// (134 us at one row of the Qwen3 vocabulary, 294 at four, which took 412 as two
 // launches of two rows).  Each workgroup keeps its slice of W2 for the whole rollout (kPersTiles tiles per wave, the last one in
 // LDS, the rest in registers: 77.8 MB over 238 workgroups) and its rows of [W1[:, d:]; W_hh] in LDS, so W2 leaves HBM once
 // per step instead of once per position.  Bound by the serial chain of a

@@ -55,9 +55,10 @@ struct GemmPlan {
 // may be split up to max_split ways into partial outputs.
 GemmPlan plan_gemm(int ntiles, int KS, int M, int epi, int n_cu, int max_split);
 void launch_gemm(bool bf16, int epi, const GemmArgs &a, const GemmPlan &p, hipStream_t st);
-// Wide activations (bf16 weights; more than kSkinnyMaxRows rows): the activations are first split into hi/lo bf16 fragment planes
-// (in a.xf), then workgroup tiles of up to 208 columns x 256 rows multiply them
-// with the same packed weights; K-split partials as above.
+// Wide activations (bf16 weights): the activations are hi/lo bf16 fragment planes in a.xf, written by
+// their producer or, where a.X is given, split from it by a launch of its own; workgroup
+// tiles of up to 208 columns x 256 rows multiply them with the same packed weights; K-split
+// partials as above.
 GemmPlan plan_gemm_wide(int ntiles, int KS, int M, int epi, int n_cu, int max_split);
 int gemm_wide_split_rows(int ntiles, int KS, int n_cu);  // above this many rows its plans split no K
 // false (nothing launched) when the arguments break the kernel's assumptions
